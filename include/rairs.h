@@ -128,8 +128,8 @@ int rairs_index_upload(const rairs_host_index_t *host, void *hip_stream, rairs_i
  * workspace of the handle's own that grows on demand (a growth synchronises the device and
  * calls hipMalloc; steady-state calls allocate nothing).
  * Everything is ordered after the earlier work of hip_stream and complete when hip_stream is;
- * inside, the table build and the grouping of queries by list run on a second stream that the
- * handle owns (default priority), forked from and joined to hip_stream with events.  Calls on one
+ * inside, a large batch runs the table build and the grouping of queries by list on a second stream
+ * that the handle owns (default priority), forked from and joined to hip_stream with events.  Calls on one
  * handle share its workspace and that stream: they must not overlap.
  */
 int rairs_search(rairs_index_t *h, const float *d_queries, int64_t nq, int k, int nprobe,
@@ -174,8 +174,8 @@ int rairs_search_noalloc(rairs_index_t *h, const float *d_queries, int64_t nq, i
 
 /*
  * RairsSearch for one query at a time or a few (the one-query-at-a-time experiment of Section 6.2),
- * captured once as a HIP graph and replayed: a small batch is bound by its fifteen kernel launches,
- * which a graph submits as one.  rairs_graph_create runs the search once eagerly, then captures it
+ * captured once as a HIP graph and replayed: a small batch is bound by its kernel launches, which a
+ * graph submits as one.  rairs_graph_create runs the search once eagerly, then captures it
  * on `hip_stream` (a stream of the caller's; not NULL) with these device pointers and parameters
  * baked in, into a workspace that the graph owns (hipMalloc; released by rairs_graph_free).  A
  * replay reads whatever d_queries holds when it runs and overwrites d_out_ids / d_out_dists; the
@@ -238,7 +238,9 @@ int rairs_refine(rairs_index_t *h, const float *d_queries, const int64_t *d_cand
  * sample of its first probed list, then the list-major MFMA kernel over all probed lists (tables
  * in registers for M = 16, 48, 64, in LDS for any other M), selection of the bigK best survivors,
  * and the exact one-workgroup-per-query kernel for queries whose survivors do not fit their buffer.
- * RAIRS_SCAN_EXACT: the exact kernel for everything.  Results are identical in both modes.
+ * Small batches of rairs_search whose queries share few lists score by table lookups, several
+ * workgroups per query, instead.  RAIRS_SCAN_EXACT: the exact kernel for everything.  Results are
+ * identical in all of them.
  */
 enum { RAIRS_SCAN_AUTO = 0, RAIRS_SCAN_EXACT = 1 };
 int rairs_set_scan_mode(rairs_index_t *h, int mode);
@@ -247,7 +249,9 @@ int rairs_set_scan_mode(rairs_index_t *h, int mode);
 
 /* SCAN is the whole SeilSearch stage (probe bitmap, sample bound, grouping, main scan kernel,
    selection, overflow redo); SCAN_KERNEL is its dominant kernel alone: the list-major MFMA scan,
-   or the exact scan when that one runs instead. */
+   or the exact scan when that one runs instead.  In a small batch's search the kernel that computes the
+   coarse distances also builds the tables (LUT: that kernel, COARSE: that and the selection of the
+   lists), and the selection of the candidates belongs to REFINE. */
 enum { RAIRS_STAGE_COARSE = 0, RAIRS_STAGE_LUT = 1, RAIRS_STAGE_SCAN = 2, RAIRS_STAGE_REFINE = 3,
        RAIRS_STAGE_SCAN_KERNEL = 4, RAIRS_NSTAGES = 5 };
 
@@ -288,7 +292,7 @@ int rairs_get_scan_stats(rairs_index_t *h, int64_t *stats);
 
 /*
  * Name of the dominant kernel that SeilSearch launches for this index in the current scan mode:
- * "scan_mfma_kernel" (2:4-sparse int8 matrix instruction, tables in registers),
+ * (for batches; small ones run "few_scan_kernel" whatever the index) "scan_mfma_kernel" (2:4-sparse int8 matrix instruction, tables in registers),
  * "scan_mfma_lds_kernel" (dense int8 matrix instruction, tables in LDS) or "scan_exact_kernel"
  * (table lookups on the vector units).  A static string; NULL for a NULL handle.
  */

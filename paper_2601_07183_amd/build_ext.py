@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librairs.so")
-SOURCES = ["api.hip", "kernels.hip", "scan_exact.hip", "scan_mfma.hip"]
+SOURCES = ["api.hip", "kernels.hip", "scan_exact.hip", "scan_mfma.hip", "search_few.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

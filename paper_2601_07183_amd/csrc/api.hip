@@ -5,6 +5,8 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
+#include <functional>
 #include <new>
 #include <vector>
 
@@ -390,6 +392,22 @@ static int upload_impl(const rairs_host_index_t *x, void *hip_stream, rairs_inde
         e2.part_cnt = (int32_t)hp.size() - e2.part_begin;
         hp.push_back(e2.seg_begin + e2.seg_cnt);
     }
+    {
+        // blocks that a query has to score per list, and the most that any p lists hold together
+        std::vector<int64_t> nb((size_t)x->nlist, 0);
+        for (int l = 0; l < x->nlist; l++) {
+            for (int sidx = hl[(size_t)l].seg_begin; sidx < hl[(size_t)l].seg_begin + hl[(size_t)l].seg_cnt; sidx++)
+                nb[(size_t)l] += hs[(size_t)sidx].nblk;
+            h->seg_blocks_total += nb[(size_t)l];
+        }
+        const int most = x->nlist < FEW_MAX_NPROBE ? x->nlist : FEW_MAX_NPROBE;
+        std::partial_sort(nb.begin(), nb.begin() + most, nb.end(), std::greater<int64_t>());
+        int64_t sum = 0;
+        for (int p = 0; p <= FEW_MAX_NPROBE; p++) {
+            h->seg_blocks_max[p] = (int32_t)(sum < FEW_MAX_BLOCKS ? sum : FEW_MAX_BLOCKS);
+            if (p < most) sum += nb[(size_t)p];
+        }
+    }
     h->nsegs = (int64_t)hs.size();
     h->max_parts = 1;
     for (int l = 0; l < x->nlist; l++)
@@ -614,6 +632,76 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     w.s_scores = w.surv_buf = take(samp_bytes > surv_bytes ? samp_bytes : surv_bytes);
     w.total = off;
     return w;
+}
+
+// ---- the few-query search -----------------------------------------------------------------------
+
+// Batches up to this much work take the few-query search: code dwords per lane over the blocks of
+// all (query, probed list) pairs, plus the fixed cost of a query (its probe and finish workgroups)
+// in the same unit, at about 0.11 ns each.  The list-major search of a small batch takes 200 to 350 us
+// whatever its size.  Measured, few-query / list-major, 1M x 128 index, nprobe 23: 100 queries 94 /
+// 358 us, 400: 284 / 345, 800: 585 / 355; 2M x 96, nprobe 39: 400 queries 164 / 321, 1,000: 353 /
+// 313; 20,000 x 32, nprobe 4: 200 queries 31 / 211.
+#ifndef FEW_MAX_WORK
+#define FEW_MAX_WORK 2500000ll
+#endif
+#define FEW_QUERY_WORK 512ll
+#define FEW_TARGET_WGS 2048         // scan workgroups that a batch is spread over
+#define FEW_MAX_QUERIES 65535
+#ifndef FEW_SAMPLE_TIMES
+#define FEW_SAMPLE_TIMES 20
+#endif
+
+struct FewLayout {
+    size_t keys, lut, bitmap, blocks, nblocks, bound, counts, surv, flags, surv_cnt, dco, total;
+    int bmwords, wgs, max_blocks, sample_blocks, region;
+};
+
+static FewLayout few_layout(const rairs_index *h, int64_t nq, int nprobe, int refine_k)
+{
+    const IndexView &v = h->v;
+    FewLayout w;
+    w.bmwords = (v.nlist + 31) / 32;
+    w.max_blocks = (h->seg_blocks_max[nprobe] + 4) & ~3;
+    // a workgroup scores 16 blocks per round: one round for a single query (also one whose lists are
+    // the longest ones: workgroups without blocks exit at once), more once the batch itself fills
+    // the chip
+    int64_t wgs = (FEW_TARGET_WGS + nq - 1) / nq;
+    if (wgs > (w.max_blocks + 15) / 16) wgs = (w.max_blocks + 15) / 16;
+    w.wgs = (int)(wgs < 1 ? 1 : (wgs > FEW_MAX_WGS ? FEW_MAX_WGS : wgs));
+    // twenty times bigK items, between 1,024 and 4,096: sixteen waves score the sample of a query
+    int sb = (FEW_SAMPLE_TIMES * refine_k + 31) / 32;
+    w.sample_blocks = sb < 32 ? 32 : (sb > RAIRS_SAMPLE_MAX_BLOCKS ? RAIRS_SAMPLE_MAX_BLOCKS : sb);
+    size_t off = 0;
+    auto take = [&off](size_t bytes) { size_t at = off; off = align_up(off + bytes, 256); return at; };
+    w.keys = take((size_t)nq * v.nlist * 4);
+    w.lut = take((size_t)nq * v.M * 16);
+    w.bitmap = take((size_t)nq * w.bmwords * 4);
+    w.blocks = take((size_t)nq * w.max_blocks * 4);
+    w.nblocks = take((size_t)nq * 4);
+    w.bound = take((size_t)nq * 4);
+    w.counts = take((size_t)nq * w.wgs * 8);
+    // entries that a workgroup may leave: more is cut to the bigK best, which takes a sort
+    w.region = 4 * refine_k < FEW_CAP ? 4 * refine_k : FEW_CAP;
+    w.surv = take((size_t)nq * w.wgs * w.region * 8);
+    w.flags = take((size_t)nq * 4);
+    w.surv_cnt = take((size_t)nq * 4);
+    w.dco = take((size_t)nq * 8);
+    w.total = off;
+    return w;
+}
+
+// Whether a batch takes the few-query search.  Its buffers have to fit what the list-major search of
+// the same batch asks for, so that one figure (rairs_workspace_bytes) covers both.
+static bool use_few(const rairs_index *h, int64_t nq, int nprobe, int refine_k, size_t list_major_bytes)
+{
+    const IndexView &v = h->v;
+    if (h->force_exact || !rairs_mfma_supported(v) || v.nlist < 64 || v.nlist > FEW_MAX_NLIST ||
+        nprobe > FEW_MAX_NPROBE || nq > FEW_MAX_QUERIES || v.ntotal == 0 || h->seg_blocks_max[nprobe] >= FEW_MAX_BLOCKS)
+        return false;
+    const int64_t blocks = (h->seg_blocks_total * nprobe + v.nlist - 1) / v.nlist;     // of a query, on average
+    if (nq * (blocks * v.nd + FEW_QUERY_WORK) > FEW_MAX_WORK) return false;
+    return few_layout(h, nq, nprobe, refine_k).total <= list_major_bytes;
 }
 
 // ---- the no-allocation entry point's scratch ------------------------------------------------
@@ -942,6 +1030,41 @@ extern "C" int rairs_refine(rairs_index_t *h, const float *d_queries, const int6
 
 // ---- RairsSearch (Alg. 2) -----------------------------------------------------------------------
 
+// The few-query search: four kernels on the caller's stream.  Stage timing: the front kernel computes
+// the coarse distances and the tables (stage LUT: that kernel; stage COARSE: that and the probe
+// kernel), the finish kernel selects and refines (stage REFINE).
+static int search_few(rairs_index *h, char *ws, int ws_source, const float *d_queries, int64_t nq, int k, int nprobe,
+                      int refine_k, int64_t *d_out_ids, float *d_out_dists, hipStream_t s)
+{
+    const FewLayout w = few_layout(h, nq, nprobe, refine_k);
+    FewArgs a;
+    memset(&a, 0, sizeof(a));
+    a.q = d_queries; a.nq = nq; a.k = k; a.nprobe = nprobe; a.refine_k = refine_k; a.bmwords = w.bmwords;
+    a.sample_blocks = w.sample_blocks; a.wgs = w.wgs; a.region = w.region; a.max_blocks = w.max_blocks;
+    a.keys = (uint32_t *)(ws + w.keys); a.lut = (uint8_t *)(ws + w.lut); a.bitmap = (uint32_t *)(ws + w.bitmap);
+    a.blocks = (int32_t *)(ws + w.blocks); a.nblocks = (uint32_t *)(ws + w.nblocks); a.bound = (int32_t *)(ws + w.bound);
+    a.counts = (uint2 *)(ws + w.counts); a.surv = (uint64_t *)(ws + w.surv);
+    a.flags = (uint32_t *)(ws + w.flags); a.surv_cnt = (uint32_t *)(ws + w.surv_cnt); a.dco = (int64_t *)(ws + w.dco);
+    a.out_ids = d_out_ids; a.out_dists = d_out_dists;
+    h->last_dco = a.dco;
+    h->last_dco_n = nq;
+    h->last_pass_n = nq; h->last_flags_off = w.flags; h->last_cnt_off = w.surv_cnt; h->last_log_chunks = 0;
+    const int plevel = ws_source != WS_GRAPH ? h->prof : 0;
+    hipEvent_t *ev = h->ev[h->ev_count % RAIRS_EV_RING];
+    FewEvents se = {nullptr, nullptr, nullptr, nullptr};
+    h->prof_valid = 0;
+    if (plevel == RAIRS_PROFILE_STAGES) {
+        se.lut0 = ev[EV_LUT0]; se.lut1 = ev[EV_LUT1]; se.probed = ev[EV_PROBED]; se.scanned = ev[EV_SCANNED];
+        RAIRS_HIP(hipEventRecord(ev[EV_START], s));
+    }
+    int rc = rairs_launch_few(h->v, a, s, plevel ? &ev[EV_KERNEL0] : nullptr, se);
+    if (rc) return rc;
+    if (plevel == RAIRS_PROFILE_STAGES) RAIRS_HIP(hipEventRecord(ev[EV_END], s));
+    if (plevel) h->ev_count++;
+    h->prof_valid = plevel ? 1 : 0;
+    return RAIRS_OK;
+}
+
 static int search_impl(rairs_index *h, int ws_source, const float *d_queries, int64_t nq, int k, int nprobe,
                        int refine_k, int64_t *d_out_ids, float *d_out_dists, void *hip_stream)
 {
@@ -957,6 +1080,8 @@ static int search_impl(rairs_index *h, int ws_source, const float *d_queries, in
     char *ws = nullptr;
     if ((rc = acquire_ws(h, ws_source, w.total, &ws))) return rc;
     hipStream_t s = (hipStream_t)hip_stream;
+    if (step == nq && use_few(h, nq, nprobe, refine_k, w.total))
+        return search_few(h, ws, ws_source, d_queries, nq, k, nprobe, refine_k, d_out_ids, d_out_dists, s);
     int64_t *dco_all = (int64_t *)(ws + w.dco);
     h->last_dco = dco_all;
     h->last_dco_n = nq;
@@ -1237,6 +1362,7 @@ extern "C" int rairs_get_scan_stats(rairs_index_t *h, int64_t *stats)
         stats[1] += cnt[i];
         if ((int64_t)cnt[i] > stats[2]) stats[2] = cnt[i];
     }
+    if (h->last_log_chunks == 0) { stats[4] = stats[1]; return RAIRS_OK; }
     std::vector<uint32_t> fill((size_t)h->last_log_chunks);
     RAIRS_HIP(hipMemcpy(fill.data(), (char *)h->last_ws + h->last_fill_off, fill.size() * 4, hipMemcpyDeviceToHost));
     for (size_t i = 0; i < fill.size(); i++) stats[4] += fill[i];

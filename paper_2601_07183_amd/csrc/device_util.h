@@ -20,6 +20,17 @@ static inline int rairs_select_wave_cap(int refine_k)
     return cap < 256 ? 256 : (cap > SELW_CAP_MAX ? SELW_CAP_MAX : cap);
 }
 
+// order-preserving map of an fp32 value to an unsigned key, and back
+static __device__ __forceinline__ uint32_t f32_key(float x)
+{
+    const uint32_t b = __float_as_uint(x);
+    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+static __device__ __forceinline__ float key_f32(uint32_t k)
+{
+    return __uint_as_float((k & 0x80000000u) ? (k ^ 0x80000000u) : ~k);
+}
+
 // Ascending bitonic sort of n (power of two) 64-bit keys in LDS by the whole workgroup.
 // Callers synchronise before; the array is consistent for all threads on return.
 static __device__ void bitonic_sort_lds(uint64_t *a, int n)
@@ -148,6 +159,47 @@ static __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t x)
     RAIRS_SUM_STEP(lane_xor1)
 #undef RAIRS_SUM_STEP
     return x;
+}
+
+// Inclusive prefix sum over the 64 lanes, by register moves: shifts within rows of 16 lanes, then the
+// last lane of each row (and of the lower half) broadcast to the rows behind it.
+static __device__ __forceinline__ uint32_t wave_incl_sum_u32(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);      // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);      // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);      // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);      // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// Minimum and maximum of the 64 lanes' values, in every lane.
+static __device__ __forceinline__ void wave_min_max_u32(uint32_t &lo, uint32_t &hi)
+{
+#define RAIRS_MM_STEP(A_, B_) lo = (A_) < lo ? (A_) : lo; hi = (B_) > hi ? (B_) : hi;
+    {
+        uint32_t a = lo, b = hi;
+        asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\tv_permlane32_swap_b32 %2, %3\n\ts_nop 1" : "+v"(lo), "+v"(a), "+v"(hi), "+v"(b));
+        RAIRS_MM_STEP(a, b)
+    }
+    {
+        uint32_t a = lo, b = hi;
+        asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\tv_permlane16_swap_b32 %2, %3\n\ts_nop 1" : "+v"(lo), "+v"(a), "+v"(hi), "+v"(b));
+        RAIRS_MM_STEP(a, b)
+    }
+#define RAIRS_MM_XOR(XOR_)                                                                        \
+    {                                                                                             \
+        const uint32_t a = __builtin_bit_cast(uint32_t, XOR_(__builtin_bit_cast(float, lo)));     \
+        const uint32_t b = __builtin_bit_cast(uint32_t, XOR_(__builtin_bit_cast(float, hi)));     \
+        RAIRS_MM_STEP(a, b)                                                                       \
+    }
+    RAIRS_MM_XOR(lane_xor8)
+    RAIRS_MM_XOR(lane_xor4)
+    RAIRS_MM_XOR(lane_xor2)
+    RAIRS_MM_XOR(lane_xor1)
+#undef RAIRS_MM_XOR
+#undef RAIRS_MM_STEP
 }
 
 // The k <= 64 smallest of n distinct 64-bit keys in a wave's own LDS region (all-ones entries are

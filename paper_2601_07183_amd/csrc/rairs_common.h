@@ -83,10 +83,19 @@ struct IndexView {
     const void *raw;              // [ntotal][d] fp32 or u8
 };
 
+// Limits and sizes of the few-query search (search_few.hip).
+#define FEW_MAX_NPROBE 256
+#define FEW_MAX_NLIST 16384
+#define FEW_MAX_WGS 512             // scan workgroups per query
+#define FEW_MAX_BLOCKS (1 << 24)   // blocks per query
+#define FEW_CAP 2048                // entries of a scan workgroup's buffer
+
 struct rairs_index {
     IndexView v;
     void *dev_alloc[24];
     int64_t nsegs, nparts;
+    int64_t seg_blocks_total;     // blocks of all segments of all lists (a shared block counts in both of its lists)
+    int32_t seg_blocks_max[FEW_MAX_NPROBE + 1];  // [p]: most of them that any p lists hold together
     int max_parts;                // most parts in any list (bounds the work-unit table)
     int ndev_alloc;
     int64_t code_bytes, total_bytes;
@@ -104,7 +113,7 @@ struct rairs_index {
     int force_exact;
     int64_t last_pass_n;          // queries of the last MFMA pass (0: none)
     size_t last_flags_off, last_cnt_off, last_fill_off;
-    int last_log_chunks;
+    int last_log_chunks;          // 0: the last pass kept no log (few-query search: every survivor is counted once)
     int prof, prof_valid;
     float stage_ms[RAIRS_NSTAGES];
     // stage events of the last RAIRS_EV_RING profiled searches (slot = search number mod ring)
@@ -241,3 +250,32 @@ int rairs_launch_select(const IndexView &v, const MfmaScanArgs &a, hipStream_t s
 int rairs_launch_scan_repair(const IndexView &v, const MfmaScanArgs &ma, const ExactScanArgs &a, hipStream_t s);
 int rairs_launch_refine(const IndexView &v, const float *q, const int64_t *cand_ids, int64_t nq,
                         int refine_k, int k, int64_t *out_ids, float *out_dists, hipStream_t s);
+
+// the whole search for batches whose queries share few lists (search_few.hip)
+struct FewArgs {
+    const float *q;               // [nq][d]
+    int64_t nq;
+    int k, nprobe, refine_k, bmwords;
+    int sample_blocks;            // blocks that seed a query's bound
+    int wgs;                      // scan workgroups per query
+    int region;                   // entries that a scan workgroup may leave, refine_k <= region <= FEW_CAP
+    int max_blocks;               // blocks that a query can have to score, a multiple of 4
+    // workspace
+    uint32_t *keys;               // [nq][nlist] order-preserving keys of the coarse distances
+    uint8_t *lut;                 // [nq][M][16]
+    uint32_t *bitmap;             // [nq][bmwords]
+    int32_t *blocks;              // [nq][max_blocks] blocks to score
+    uint32_t *nblocks;            // [nq]
+    int32_t *bound;               // [nq]
+    uint2 *counts;                // [nq][wgs] {entries, items scored}
+    uint64_t *surv;               // [nq][wgs][region] score << 32 | id
+    uint32_t *flags, *surv_cnt;   // [nq] for the measurement helpers: 0; entries
+    int64_t *dco;                 // [nq]
+    int64_t *out_ids;             // [nq][k]
+    float *out_dists;             // [nq][k]
+};
+// stage events (null: not recorded): around the front kernel, behind the probe and the scan kernel
+struct FewEvents {
+    hipEvent_t lut0, lut1, probed, scanned;
+};
+int rairs_launch_few(const IndexView &v, const FewArgs &a, hipStream_t s, hipEvent_t *ev, const FewEvents &se);
