@@ -520,8 +520,8 @@ extern "C" int rairs_index_bytes(const rairs_index_t *h, int64_t *code_bytes, in
 
 #define RAIRS_SAMPLE_BLOCKS 16
 
-// Survivor buffer entries per query (entries at or below the query's final bound; more than this
-// sends the query to the exact kernel) and survivor log entries per query on average (the scan logs
+// Survivor buffer entries per query (entries at or below the query's final bound; what is beyond
+// this, up to SURV_CAP_MAX in all, goes to the unused rest of the log) and survivor log entries per query on average (the scan logs
 // about bigK ln(items / sample) entries per query; if the log runs out, every query of the pass
 // is redone by the exact kernel).
 static int surv_cap_for(int refine_k)
@@ -978,7 +978,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     else if ((rc = rairs_launch_group(v, ma, s))) return rc;
     if ((rc = rairs_launch_scan_mfma(v, ma, s, ev))) return rc;
     if ((rc = rairs_launch_select(v, ma, s))) return rc;
-    // a query with more entries at or below its final bound than the buffer holds (thousands of
+    // a query with more entries at or below its final bound than buffer and spill hold (thousands of
     // items with the same score), or every query if the log ran out of chunks, is redone by the
     // exact kernel (which counts that query's DCO again, to the same value); normally none is
     // flagged and every workgroup of that launch exits at once

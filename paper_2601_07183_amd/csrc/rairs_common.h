@@ -232,7 +232,7 @@ struct MfmaScanArgs {
     uint2 *log;                   // [log_chunks][RAIRS_LOG_CHUNK] survivor log {slot, score << 16 | query of the pass}
     uint32_t *chunk_fill;         // [log_chunks] entries written to each chunk
     uint32_t *log_cursor;         // [1] chunks handed out
-    uint32_t *log_overflow;       // [1] set if the log ran out of chunks
+    uint32_t *log_overflow;       // [2] set if the log ran out of chunks; entries spilled from full survivor buffers
     int log_chunks;
     unsigned long long *dco;      // [nq] items scored per query, counted as blocks are contracted; may be null
     int any_order;                // the bigK candidates may be written in any order (the whole search: refine orders them anyway)

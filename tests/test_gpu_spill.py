@@ -1,0 +1,43 @@
+"""Survivors beyond a query's buffer: the spill behind the survivor log, up to its edges."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle
+from paper_2601_07183_amd import datagen
+from paper_2601_07183_amd import index_build as ib
+
+pytestmark = pytest.mark.gpu
+
+
+# a buffer holds 1,024 entries at bigK = 64, the workgroup-wide select takes up to 4,096; a query with
+# more is redone exactly.  Clumps of identical vectors in one pair of lists, multiples of 32, so that
+# all of them are in shared blocks and a query of the clump has exactly that many survivors.
+@pytest.mark.parametrize("counts,redone", [((1024, 1056), 0), ((1056, 2048), 0), ((4096, 64), 0), ((4128, 1056), 7)])
+def test_spilled_survivors(counts, redone):
+    from paper_2601_07183_amd import binding
+    va = datagen.random_vectors(60, 1, 8)
+    vb = va + np.float32(40)
+    e = np.zeros((1, 8), np.float32)
+    e[0, 0] = 0.5
+    x = np.concatenate([np.tile(va, (counts[0], 1)), np.tile(vb, (counts[1], 1))])
+    cents = np.concatenate([va + e, va - e, vb + e, vb - e]).astype(np.float32)
+    asg = np.array([[0, 1]] * counts[0] + [[2, 3]] * counts[1], dtype=np.int32)
+    cb = ib.train_pq(datagen.random_vectors(61, 300, 8), 4, 5, 2)
+    noise = datagen.random_vectors(62, 15, 8) * np.float32(0.01)
+    q = (np.concatenate([np.tile(va, (7, 1)), np.tile(vb, (8, 1))]) + noise).astype(np.float32)
+    hx = ib.add_vectors(x, cents, cb, assign=asg)
+    want = oracle.search(oracle.OracleIndex(hx), q, 10, 2, 64)
+    ix = binding.Index(hx)
+    try:
+        dq = torch.from_numpy(q).cuda()
+        for _ in range(2):
+            print("case:", counts, flush=True)
+            ids, dists = ix.search(dq, 10, 2, 64)
+            torch.cuda.synchronize()
+            assert (ids.cpu().numpy() == want.ids).all()
+            assert (dists.cpu().numpy() == want.dists).all()
+            assert (ix.dco(len(q)) == want.dco).all()
+            assert ix.scan_stats()["redone"] == redone
+    finally:
+        ix.free()
