@@ -239,7 +239,8 @@ static int upload_impl(const rairs_host_index_t *x, void *hip_stream, rairs_inde
     float *cnorm = nullptr;
     UP_CHECK(dev_alloc(h, (void **)&cent, cent_bytes));
     UP_CHECK(dev_alloc(h, (void **)&cent_t, cent_bytes));
-    UP_CHECK(dev_alloc(h, (void **)&cnorm, (size_t)x->nlist * sizeof(float)));
+    const size_t cent_tiles = ((size_t)x->nlist + 31) / 32, cent_steps = ((size_t)x->d + 15) / 16;
+    UP_CHECK(dev_alloc(h, (void **)&cnorm, cent_tiles * 32 * sizeof(float)));
     UP_CHECK(dev_alloc(h, (void **)&cb, cb_bytes));
     UP_CHECK(dev_alloc(h, (void **)&codes, (size_t)h->code_bytes));
     UP_CHECK(dev_alloc(h, (void **)&ids, (size_t)x->nblocks * 32 * 4));
@@ -252,7 +253,7 @@ static int upload_impl(const rairs_host_index_t *x, void *hip_stream, rairs_inde
     // that lanes walking over lists read coalesced.  The GEMM form works on centred copies,
     // c' = fl(c - mean of the centroids): distances do not change, but the rounding-error margin
     // scales with |q'|^2 + |c'|^2, which centring makes as small as the data allow.
-    std::vector<float> hmean((size_t)x->d), hct((size_t)x->nlist * x->d), hn((size_t)x->nlist);
+    std::vector<float> hmean((size_t)x->d), hn(cent_tiles * 32, 0.0f);
     for (int i = 0; i < x->d; i++) {
         double m = 0.0;
         for (int l = 0; l < x->nlist; l++) m += (double)x->centroids[(size_t)l * x->d + i];
@@ -264,24 +265,24 @@ static int upload_impl(const rairs_host_index_t *x, void *hip_stream, rairs_inde
         double n2 = 0.0;
         for (int i = 0; i < x->d; i++) {
             const float c = x->centroids[(size_t)l * x->d + i] - hmean[(size_t)i];
-            hct[(size_t)i * x->nlist + l] = c;
             n2 += (double)c * (double)c;
         }
         hn[(size_t)l] = x->metric == RAIRS_METRIC_IP ? 0.0f : (float)n2;
         if (n2 > nmax) nmax = n2;
     }
     v.cmax2 = (float)nmax;
-    float *cent_ct = nullptr, *cmean = nullptr;
-    UP_CHECK(dev_alloc(h, (void **)&cent_ct, cent_bytes));
+    float *cmean = nullptr;
+    void *cent_ops = nullptr;
+    UP_CHECK(dev_alloc(h, &cent_ops, cent_tiles * cent_steps * 3 * 64 * 16));
     UP_CHECK(dev_alloc(h, (void **)&cmean, (size_t)x->d * sizeof(float)));
     hipError_t e = hipSuccess;
     UP_HIP(hipMemcpyAsync(cent, x->centroids, cent_bytes, hipMemcpyHostToDevice, s));
-    UP_HIP(hipMemcpyAsync(cent_ct, hct.data(), cent_bytes, hipMemcpyHostToDevice, s));
     UP_HIP(hipMemcpyAsync(cmean, hmean.data(), (size_t)x->d * sizeof(float), hipMemcpyHostToDevice, s));
     UP_HIP(hipMemcpyAsync(cnorm, hn.data(), hn.size() * sizeof(float), hipMemcpyHostToDevice, s));
     UP_CHECK(rairs_launch_transpose(cent, x->nlist, x->d, cent_t, s));
+    UP_CHECK(rairs_launch_pack_centroids(cent, cmean, x->d, x->nlist, cent_ops, s));
     UP_HIP(hipStreamSynchronize(s));
-    v.centroids_ct = cent_ct; v.cmean = cmean;
+    v.centroid_ops = cent_ops; v.cmean = cmean;
     UP_HIP(hipMemcpyAsync(cb, x->codebook, cb_bytes, hipMemcpyHostToDevice, s));
     if (x->nblocks)
         UP_HIP(hipMemcpyAsync(other, x->other, (size_t)x->nblocks * 32 * 4, hipMemcpyHostToDevice, s));
@@ -540,6 +541,7 @@ static int log_per_query_for(int refine_k)
 struct WsLayout {
     size_t dmat, cflags, probe_ids, probe_dists, bitmap, lut, cand, dco;
     size_t lcount, loff, lcursor, toff, unit_list, unit_rec, next_task, qlist, tau, bound, surv_cnt, flags, work, hist, surv_buf, log, chunk_fill, log_misc, total;
+    size_t hmin;                  // 0: none (more lists than RAIRS_HMIN_MAX_NLIST)
     size_t s_off, s_toff, s_q, s_tiles, s_scores, s_first;      // matrix-core sample (0 bytes when not used)
     int sample_blocks;
     int log_chunks;
@@ -572,6 +574,8 @@ static int sample_blocks_for(const IndexView &v, int refine_k, bool grouped)
     if (blocks < RAIRS_SAMPLE_BLOCKS) blocks = RAIRS_SAMPLE_BLOCKS;
     return blocks < RAIRS_SAMPLE_MAX_BLOCKS ? blocks : RAIRS_SAMPLE_MAX_BLOCKS;
 }
+
+static uint32_t *ws_hmin(char *ws, const WsLayout &w) { return w.hmin ? (uint32_t *)(ws + w.hmin) : nullptr; }
 
 // Workspace of one pass of `nq` queries out of a batch of `nq_total` (the DCO counts cover the
 // batch).  Two pairs of buffers whose lifetimes never overlap on the caller's stream share their
@@ -627,9 +631,14 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     w.s_tiles = take(grouped ? ((size_t)nq / 32 + (size_t)v.nlist + 1) * 4 : 0);
     const size_t dmat_bytes = (size_t)nq * v.nlist * 4, log_bytes = (size_t)w.log_chunks * RAIRS_LOG_CHUNK * 8;
     w.dmat = w.log = take(dmat_bytes > log_bytes ? dmat_bytes : log_bytes);
-    const size_t samp_bytes = grouped ? (size_t)nq * w.sample_blocks * 64 : 0;
+    // (behind the sample's scores, which may be written while the selection still reads them, the half
+    // tiles' minima of the score matrix: at most a quarter of 16,384 words per query, so that with the
+    // sample, which then has at most 8,192 lists, the sum stays within the survivors' 1,024 entries)
+    const size_t samp_bytes = align_up(grouped ? (size_t)nq * w.sample_blocks * 64 : 0, 256);
+    const size_t hmin_bytes = v.nlist <= RAIRS_HMIN_MAX_NLIST ? (size_t)nq * rairs_half_tiles(v.nlist) * 4 : 0;
     const size_t surv_bytes = (size_t)nq * w.surv_cap * 8;
-    w.s_scores = w.surv_buf = take(samp_bytes > surv_bytes ? samp_bytes : surv_bytes);
+    w.s_scores = w.surv_buf = take(samp_bytes + hmin_bytes > surv_bytes ? samp_bytes + hmin_bytes : surv_bytes);
+    w.hmin = hmin_bytes ? w.s_scores + samp_bytes : 0;
     w.total = off;
     return w;
 }
@@ -827,7 +836,7 @@ extern "C" int rairs_coarse(rairs_index_t *h, const float *d_queries, int64_t nq
     for (int64_t q0 = 0; q0 < nq; q0 += step) {
         int64_t n = nq - q0 < step ? nq - q0 : step;
         rc = rairs_launch_coarse(h->v, d_queries + (size_t)q0 * h->v.d, n, nprobe,
-                                 (float *)(ws + w.dmat), d_probe_ids + (size_t)q0 * nprobe,
+                                 (float *)(ws + w.dmat), ws_hmin(ws, w), d_probe_ids + (size_t)q0 * nprobe,
                                  d_probe_dists ? d_probe_dists + (size_t)q0 * nprobe : nullptr,
                                  (uint32_t *)(ws + w.cflags), s);
         if (rc) return rc;
@@ -951,7 +960,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     }
     if (grouped && probed_on_side) {
         int32_t *s_first = (int32_t *)(ws + w.s_first);
-        if ((rc = rairs_launch_coarse_first(v, (const float *)(ws + w.dmat), n, s_first, s))) return rc;
+        if ((rc = rairs_launch_coarse_first(v, (const float *)(ws + w.dmat), ws_hmin(ws, w), n, s_first, s))) return rc;
         if ((rc = rairs_launch_sample_group(v, s_first, 1, n, s_off, s_toff, s_q, s_tiles, s))) return rc;
         RAIRS_HIP(hipStreamWaitEvent(s, lut_done, 0));
         if ((rc = rairs_launch_sample_scores(v, lut, sample_blocks, n, s_off, s_toff, s_q, s_tiles, s_scores, s)))
@@ -1123,7 +1132,7 @@ static int search_impl(rairs_index *h, int ws_source, const float *d_queries, in
         // sample, ranking -- thus stays on one stream, with no event hop in it.
         const bool early = overlap && !h->force_exact && rairs_mfma_supported(v) &&
                            grouped_sample(v, n, refine_k) && rairs_coarse_has_scores(v, nprobe, q);
-        if ((rc = rairs_launch_coarse(v, q, n, nprobe, (float *)(ws + w.dmat), probe_ids,
+        if ((rc = rairs_launch_coarse(v, q, n, nprobe, (float *)(ws + w.dmat), ws_hmin(ws, w), probe_ids,
                                       (float *)(ws + w.probe_dists), (uint32_t *)(ws + w.cflags), s,
                                       early ? h->ev_scored : nullptr, early ? side : nullptr)))
             return rc;
@@ -1391,7 +1400,7 @@ extern "C" int rairs_assign(rairs_index_t *h, const float *d_vectors, int64_t n,
         const float *x = d_vectors + (size_t)q0 * h->v.d;
         int32_t *cand = (int32_t *)(ws + w.probe_ids);
         // FindNearestLists is the search path's coarse quantizer
-        if ((rc = rairs_launch_coarse(h->v, x, m, nc, (float *)(ws + w.dmat), cand, nullptr,
+        if ((rc = rairs_launch_coarse(h->v, x, m, nc, (float *)(ws + w.dmat), ws_hmin(ws, w), cand, nullptr,
                                       (uint32_t *)(ws + w.cflags), s))) return rc;
         if ((rc = rairs_launch_air_assign(h->v, x, m, nc, lambda, strict ? 1 : 0, cand,
                                           d_pairs + (size_t)q0 * 2, s))) return rc;

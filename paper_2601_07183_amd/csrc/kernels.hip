@@ -104,7 +104,6 @@ int rairs_launch_transpose(const float *d_in, int rows, int cols, float *d_out, 
 //              a superset of the true winners, so both routes return the same bits; a query whose
 //              shortlist does not fit falls back to the full route.
 
-typedef float v16f __attribute__((ext_vector_type(16)));
 
 // direct-form score (squared distance, or minus the inner product) of a query to list l of the
 // transposed centroid matrix ct[d][nlist]
@@ -156,7 +155,7 @@ __global__ __launch_bounds__(WG) void coarse_select_kernel(uint32_t *dmat,
                                                            int nlist, int nprobe,
                                                            int32_t *__restrict__ probe_ids,
                                                            float *__restrict__ probe_dists,
-                                                           const uint32_t *__restrict__ only_flagged,
+                                                           const uint32_t *__restrict__ only_flagged, int64_t nq,
                                                            const float *__restrict__ q,
                                                            const float *__restrict__ ct, int d, int metric)
 {
@@ -165,16 +164,27 @@ __global__ __launch_bounds__(WG) void coarse_select_kernel(uint32_t *dmat,
     __shared__ int wcnt[WG / 64];
     __shared__ uint64_t sel[RAIRS_MAX_NPROBE];
     const int tid = threadIdx.x;
-    if (only_flagged && only_flagged[blockIdx.x] == 0) return;
+    __shared__ uint32_t flagged[WG];
+    // with flags, a workgroup takes the queries blockIdx.x + i * gridDim.x, at most WG of them, and
+    // looks at all their flags at once
+    uint32_t mine = only_flagged ? 0u : tid == 0 ? 1u : 0u;
+    const int64_t qt = (int64_t)blockIdx.x + (int64_t)tid * gridDim.x;
+    if (only_flagged && qt < nq) mine = only_flagged[qt];
+    flagged[tid] = mine;
+    if (!__syncthreads_or((int)mine)) return;
+    for (int qn = 0; qn < WG; qn++) {
+    if (flagged[qn] == 0u) continue;                    // uniform
+    const int64_t qi = (int64_t)blockIdx.x + (int64_t)qn * gridDim.x;
+    __syncthreads();                                    // the shared state is the next query's
     if (q) {
         // the row's distances first (same arithmetic as coarse_dist_kernel), by this workgroup
-        uint32_t *drow = dmat + (size_t)blockIdx.x * nlist;
-        const float *qq = q + (size_t)blockIdx.x * d;
+        uint32_t *drow = dmat + (size_t)qi * nlist;
+        const float *qq = q + (size_t)qi * d;
         for (int l = tid; l < nlist; l += WG) drow[l] = f32_key(direct_l2_t(qq, ct, d, nlist, l, metric));
         __threadfence_block();
         __syncthreads();
     }
-    const uint32_t *row = dmat + (size_t)blockIdx.x * nlist;
+    const uint32_t *row = dmat + (size_t)qi * nlist;
 
     uint32_t prefix = 0, mask = 0, remaining = (uint32_t)nprobe;
     for (int shift = 24; shift >= 0; shift -= 8) {
@@ -241,198 +251,16 @@ __global__ __launch_bounds__(WG) void coarse_select_kernel(uint32_t *dmat,
     bitonic_sort_lds(sel, n2);
     for (int i = tid; i < nprobe; i += WG) {
         uint64_t key = sel[i];
-        probe_ids[(size_t)blockIdx.x * nprobe + i] = (int32_t)(uint32_t)key;
+        probe_ids[(size_t)qi * nprobe + i] = (int32_t)(uint32_t)key;
         if (probe_dists) {
             const float sc = key_f32((uint32_t)(key >> 32));
-            probe_dists[(size_t)blockIdx.x * nprobe + i] = metric ? -sc : sc;    // reported: the product itself
+            probe_dists[(size_t)qi * nprobe + i] = metric ? -sc : sc;    // reported: the product itself
         }
+    }
     }
 }
 
-// Shortlist route, scores: keys[q][l] = f32_key(|c'_l|^2 - 2 q'.c'_l) with v_mfma_f32_32x32x2f32,
-// where q' = fl(q - cmean) and c' = fl(c - cmean) are the centred query and centroid.
-// A workgroup takes 128 queries (32 per wave, kept in registers: lane (row i, half k) holds
-// q_i[k*D/2 + s], s < D/2) and walks over tiles of 32 lists.  A tile's centroids are staged in LDS
-// in operand order, element (s, k, j) = ct[k*D/2 + s][l0 + j] at s*64 + k*32 + j, so that the B
-// operand of step s is one conflict-free 4-byte read per lane; the next tile is fetched into
-// registers while the current one is multiplied (two LDS buffers, one barrier per tile).
-// Result register r of lane (k, j) is row 8*(r/4) + 4*k + r%4, column j.
-#define GEMM_QWG 128
-template <int D>
-__global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(D <= 128 ? 3 : 2))) void coarse_gemm_kernel(const float *__restrict__ q,
-                                                         const float *__restrict__ ct,
-                                                         const float *__restrict__ cmean,
-                                                         const float *__restrict__ cnorm, int nlist,
-                                                         int csplits, int tiles_per_split, int64_t nq,
-                                                         uint32_t *__restrict__ keys, float alpha)
-{
-    constexpr int H = D / 2;
-    constexpr int PER = D * 32 / WG;                    // staged elements per thread and tile
-    __shared__ float Bs[2][D * 32];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 31, k = lane >> 5;
-    // workgroups that share an L2 (consecutive ids go round the 8 dies) take the same lists
-    int qblock, csplit;
-    if ((csplits & 7) == 0) {
-        const int per = csplits >> 3, x = blockIdx.x & 7, y = blockIdx.x >> 3;
-        csplit = x * per + y % per;
-        qblock = y / per;
-    } else {
-        csplit = blockIdx.x % csplits;
-        qblock = blockIdx.x / csplits;
-    }
-    const int64_t q0 = (int64_t)qblock * GEMM_QWG + wave * 32;
-    const int64_t qrow = q0 + i < nq ? q0 + i : nq - 1;
-    float A[H];                                         // centred: fl(q - cmean)
-    {
-        const float4 *src = (const float4 *)(q + (size_t)qrow * D + k * H);
-        const float4 *mu = (const float4 *)(cmean + k * H);
-#pragma unroll
-        for (int s4 = 0; s4 < H / 4; s4++) {
-            const float4 x = src[s4], m = mu[s4];
-            A[4 * s4] = x.x - m.x; A[4 * s4 + 1] = x.y - m.y; A[4 * s4 + 2] = x.z - m.z; A[4 * s4 + 3] = x.w - m.w;
-        }
-    }
-    const int ntiles = (nlist + 31) >> 5;
-    const int t_begin = csplit * tiles_per_split;
-    const int t_end = t_begin + tiles_per_split < ntiles ? t_begin + tiles_per_split : ntiles;
-    if (t_begin >= t_end) return;                       // uniform for the workgroup
-    // staging: thread -> column sj, rows sr + 8 * e (row = dimension k*H + s)
-    const int sj = threadIdx.x & 31, sr = threadIdx.x >> 5;
-    float st[PER];
-    // (a uniform row pointer plus one 32-bit offset per thread: sixteen 64-bit addresses per
-    // thread would cost the registers that decide whether a third wave fits a SIMD)
-    auto fetch = [&](int t) {
-        const int l = t * 32 + sj;
-        const uint32_t off = (uint32_t)sr * (uint32_t)nlist + (uint32_t)(l < nlist ? l : nlist - 1);
-#pragma unroll
-        for (int e = 0; e < PER; e++) {
-            const float *rows = ct + (size_t)(8 * e) * nlist;       // uniform
-            st[e] = rows[off];
-        }
-    };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int e = 0; e < PER; e++) {
-            const int row = sr + 8 * e, kk = row >= H ? 1 : 0, ss = row - kk * H;
-            Bs[buf][ss * 64 + kk * 32 + sj] = st[e];
-        }
-    };
-    fetch(t_begin);
-    stage(0);
-    __syncthreads();
-    int buf = 0;
-    // all 32 rows of the wave are queries of the batch (else: the last block, stores checked one by one)
-    const bool whole = q0 + 32 <= nq;
-    for (int t = t_begin; t < t_end; t++) {
-        const bool more = t + 1 < t_end;
-        if (more) fetch(t + 1);
-        const int l = t * 32 + i;
-        const float cn = cnorm[l < nlist ? l : nlist - 1];          // asked for before the products, used after
-        v16f acc;
-#pragma unroll
-        for (int r = 0; r < 16; r++) acc[r] = 0.0f;
-        const float *bl = &Bs[buf][lane];
-#pragma unroll
-        for (int s = 0; s < H; s++)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[s], bl[s * 64], acc, 0, 0, 0);
-        // alpha = 2: |c'|^2 - 2 q'.c'; alpha = 1 with zero norms: -q.c
-        if (l < nlist) {
-            if (whole) {
-                // a uniform row pointer per result register plus one 32-bit offset per lane
-                const uint32_t off = (uint32_t)(4 * k) * (uint32_t)nlist + (uint32_t)l;
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    uint32_t *rowp = keys + (size_t)(q0 + 8 * (r >> 2) + (r & 3)) * nlist;      // uniform
-                    rowp[off] = f32_key(cn - alpha * acc[r]);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    const int64_t qq = q0 + 8 * (r >> 2) + 4 * k + (r & 3);
-                    if (qq < nq) keys[(size_t)qq * nlist + l] = f32_key(cn - alpha * acc[r]);
-                }
-            }
-        }
-        if (more) stage(buf ^ 1);
-        __syncthreads();
-        buf ^= 1;
-    }
-}
-
-// The same scores for any dimension that is a multiple of 8: the dimensions are taken in chunks of
-// GEMM_CD; a wave holds the chunk of its 32 queries in registers, the chunk of a list tile is staged
-// in LDS, and the NT tiles of the workgroup keep their accumulators across the chunks.
-#define GEMM_CD 128
-template <int NT>
-__global__ __launch_bounds__(WG) void coarse_gemm_chunk_kernel(const float *__restrict__ q,
-                                                               const float *__restrict__ ct,
-                                                               const float *__restrict__ cmean,
-                                                               const float *__restrict__ cnorm, int d,
-                                                               int nlist, int ngroups, int64_t nq,
-                                                               uint32_t *__restrict__ keys, float alpha)
-{
-    __shared__ float Bs[GEMM_CD * 32];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 31, k = lane >> 5;
-    const int qblock = blockIdx.x / ngroups, grp = blockIdx.x % ngroups;
-    const int64_t q0 = (int64_t)qblock * GEMM_QWG + wave * 32;
-    const int64_t qrow = q0 + i < nq ? q0 + i : nq - 1;
-    const int ntiles = (nlist + 31) >> 5;
-    const int sj = threadIdx.x & 31, sr = threadIdx.x >> 5;
-    v16f acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; t++)
-#pragma unroll
-        for (int r = 0; r < 16; r++) acc[t][r] = 0.0f;
-    for (int c0 = 0; c0 < d; c0 += GEMM_CD) {
-        const int cd = d - c0 < GEMM_CD ? d - c0 : GEMM_CD;      // multiple of 8
-        const int h = cd >> 1;                                   // multiple of 4
-        float A[GEMM_CD / 2];
-        {
-            const float4 *src = (const float4 *)(q + (size_t)qrow * d + c0 + k * h);
-            const float4 *mu = (const float4 *)(cmean + c0 + k * h);
-#pragma unroll
-            for (int s4 = 0; s4 < GEMM_CD / 8; s4++) {
-                float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f), m = x;
-                if (4 * s4 < h) { x = src[s4]; m = mu[s4]; }
-                A[4 * s4] = x.x - m.x; A[4 * s4 + 1] = x.y - m.y; A[4 * s4 + 2] = x.z - m.z; A[4 * s4 + 3] = x.w - m.w;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < NT; t++) {
-            const int tile = grp * NT + t;
-            if (tile < ntiles) {                                 // uniform for the workgroup
-                __syncthreads();                                 // the previous chunk has been consumed
-                const int l = tile * 32 + sj;
-                const float *src = ct + (size_t)c0 * nlist + (l < nlist ? l : nlist - 1);
-#pragma unroll
-                for (int e = 0; e < GEMM_CD / 8; e++) {
-                    const int row = sr + 8 * e;
-                    if (row < cd) {
-                        const int kk = row >= h ? 1 : 0, ss = row - kk * h;
-                        Bs[ss * 64 + kk * 32 + sj] = src[(size_t)row * nlist];
-                    }
-                }
-                __syncthreads();
-#pragma unroll
-                for (int s = 0; s < GEMM_CD / 2; s++)
-                    if (s < h) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[s], Bs[s * 64 + lane], acc[t], 0, 0, 0);
-            }
-        }
-    }
-#pragma unroll
-    for (int t = 0; t < NT; t++) {
-        const int l = (grp * NT + t) * 32 + i;
-        if (l < nlist) {
-            const float cn = cnorm[l];
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-                const int64_t qq = q0 + 8 * (r >> 2) + 4 * k + (r & 3);
-                const float two = alpha * acc[t][r];
-                if (qq < nq) keys[(size_t)qq * nlist + l] = f32_key(cn - two);
-            }
-        }
-    }
-}
+#include "coarse_gemm.h"
 
 // Shortlist route, selection.  One wave per query (four per workgroup, each with its own LDS
 // region and no workgroup barrier): find the nprobe-th smallest key, widen it by the margin, gather
@@ -446,15 +274,63 @@ __global__ __launch_bounds__(WG) void coarse_gemm_chunk_kernel(const float *__re
 // the direct form has s <= (nprobe-th smallest s) + 2 e.  The kernel uses 16 (d + 4) u N, twice
 // that, against accumulation orders inside the matrix core that are not documented.
 //
-// The nprobe-th smallest key is found in one pass over the row when a sample allows it: the
+// Where nprobe is well below the number of half tiles (16 lists; by_min), the nprobe-th smallest of
+// the half tiles' minima bounds the nprobe-th smallest key from above -- nprobe different lists are at
+// or below it -- and only half tiles whose minimum is within the margin of it are read at all: some
+// 12 KB of a 64 KB row at 98 of 16,384 lists, after 4 KB of minima.  (Whole rows / this, 10,000
+// queries: 98 of 16,384 lists 360 / 114 us, 39 of 4,096 56 / 37, 23 of 1,024 36 / 24.  Up to 3/4 of
+// the half tiles, where the entries at or below the estimate are about twice nprobe; beyond it
+// they grow fast.)
+// Else the nprobe-th smallest key is found in one pass over the row when a sample allows it: the
 // ksamp-th smallest key `est` of the row's first `nsamp` keys is, with ksamp chosen well above the
 // sample's share of nprobe, above the nprobe-th smallest of the row; every key <= est is gathered
 // (with its list) and sorted, which yields the nprobe-th smallest exactly.  If fewer than nprobe
 // keys were gathered, or they do not fit, or est is below the widened threshold, the wave falls back
 // to a radix select over the whole row (four passes), which always works.
 #define SHORTLIST_SAMPLE 512
-template <bool IP>
+
+// A wave's shortlist cut to what the margin asks for: ng <= 256 entries (key << 32 | list), at least
+// nprobe of them, in the wave's own LDS region.  They go back into registers, the nprobe-th smallest
+// key is found bit by bit, and the lists up to the widened threshold are packed: no sort.  Returns
+// their number; 0, and nothing is changed, if the threshold is above est.
+static __device__ __forceinline__ uint32_t shortlist_pack(uint64_t *sel, uint32_t ng, int nprobe, float margin,
+                                                          uint32_t est, int lane)
+{
+    wave_lds_sync();
+    uint64_t mine[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const uint32_t i = 64u * u + lane;
+        mine[u] = i < ng ? sel[i] : ~0ull;
+    }
+    uint32_t kth = 0;                                    // largest t with fewer than nprobe keys below it
+    for (int bit = 31; bit >= 0; bit--) {
+        const uint32_t cand = kth | (1u << bit);
+        uint32_t below = 0;
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (64u * u < ng) below += (uint32_t)__popcll(__ballot((uint32_t)(mine[u] >> 32) < cand));
+        if (below < (uint32_t)nprobe) kth = cand;
+    }
+    const uint32_t thr = f32_key(key_f32(kth) + margin);
+    if (thr > est) return 0;
+    wave_lds_sync();                                     // every lane holds its entries
+    uint32_t nc = 0;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        if (64u * u < ng) {
+            const bool in = 64u * u + lane < ng && (uint32_t)(mine[u] >> 32) <= thr;
+            const unsigned long long m = __ballot(in);
+            if (in) sel[nc + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint64_t)(uint32_t)mine[u];
+            nc += (uint32_t)__popcll(m);
+        }
+    }
+    return nc;
+}
+
+template <bool IP, int HR>                              // by_min over up to HR * 64 half tiles; 0: not
 __global__ __launch_bounds__(WG) void coarse_shortlist_kernel(const uint32_t *__restrict__ keys,
+                                                              const uint32_t *__restrict__ hmin, int nhalf,
                                                               const float *__restrict__ q,
                                                               const float *__restrict__ cent, int d,
                                                               int nlist, int nprobe, int cap,
@@ -484,12 +360,74 @@ __global__ __launch_bounds__(WG) void coarse_shortlist_kernel(const uint32_t *__
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) qn += __shfl_xor(qn, off);
-    const float margin = 16.0f * (float)(d + 4) * 5.9604645e-8f * (qn + cmax2);
+    // (the last term: products near the smallest normal number lose their lower pieces)
+    const float margin = 16.0f * (float)(d + 4) * 5.9604645e-8f * (qn + cmax2) + 1.0e-36f * (float)d;
     const bool margin_ok = !(margin != margin) && margin < 3.0e38f;
 
     uint32_t nc = 0;                                     // lists in the shortlist (their ids in sel[0..nc))
     bool have = false;
-    if (nsamp > 0 && margin_ok) {
+    if (HR > 0 && margin_ok) {
+        uint32_t h[HR > 0 ? HR : 1];
+        uint32_t lo = 0xFFFFFFFFu, est = 0u;
+#pragma unroll
+        for (int u = 0; u < HR; u++) {
+            const int i = 64 * u + lane;
+            h[u] = hmin[(size_t)qi * nhalf + (i < nhalf ? i : nhalf - 1)];
+            lo = h[u] < lo ? h[u] : lo;
+            est = h[u] > est ? h[u] : est;
+            if (i >= nhalf) h[u] = 0xFFFFFFFFu;
+        }
+        wave_min_max_u32(lo, est);
+        lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)lo);
+        est = (uint32_t)__builtin_amdgcn_readfirstlane((int)est);
+        // (an upper estimate an eighth too loose is good enough: a few steps of bisection)
+        const uint32_t enough = (uint32_t)nprobe + (uint32_t)nprobe / 8u + 1u;
+        while (lo < est) {                              // at least nprobe minima are <= est throughout
+            const uint32_t mid = lo + (est - lo) / 2u;
+            uint32_t upto = 0;
+#pragma unroll
+            for (int u = 0; u < HR; u++) upto += (uint32_t)__popcll(__ballot(h[u] <= mid));
+            if (upto < (uint32_t)nprobe) lo = mid + 1u;
+            else { est = mid; if (upto <= enough) break; }
+        }
+        const uint32_t thr = f32_key(key_f32(est) + margin);
+        uint32_t nh = 0;                                // half tiles to read
+#pragma unroll
+        for (int u = 0; u < HR; u++) {
+            const bool in = 64 * u + lane < nhalf && h[u] <= thr;
+            const unsigned long long m = __ballot(in);
+            const uint32_t pos = nh + (uint32_t)__popcll(m & lt_mask);
+            if (in && pos < 256u) hist[pos] = (uint32_t)(64 * u + lane);
+            nh += (uint32_t)__popcll(m);
+        }
+        wave_lds_sync();
+        if (nh <= 256u) {
+            const int grp = lane >> 4, l16 = lane & 15;
+            uint32_t ng = 0;
+            for (uint32_t t0 = 0; t0 < nh; t0 += 16) {   // sixteen half tiles at a time, four per 16 lanes
+                uint32_t kk[4];
+                int l[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const uint32_t t = t0 + 4u * u + grp;
+                    const int ht = (int)hist[t < nh ? t : nh - 1];
+                    l[u] = 32 * (ht >> 1) + 4 * (ht & 1) + 8 * (l16 >> 2) + (l16 & 3);
+                    kk[u] = row[l[u] < nlist ? l[u] : nlist - 1];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    const bool in = t0 + 4u * u + grp < nh && l[u] < nlist && kk[u] <= thr;
+                    const unsigned long long m = __ballot(in);
+                    const uint32_t pos = ng + (uint32_t)__popcll(m & lt_mask);
+                    if (in && pos < (uint32_t)cap) sel[pos] = ((uint64_t)kk[u] << 32) | (uint32_t)l[u];
+                    ng += (uint32_t)__popcll(m);
+                }
+            }
+            // (hardly more than there have to be: all of them are re-scored)
+            if (ng <= (uint32_t)cap && ng <= 256u) nc = ng <= (uint32_t)nprobe + 8u ? ng : shortlist_pack(sel, ng, nprobe, margin, 0xFFFFFFFFu, lane);
+            have = nc > 0;
+        }
+    } else if (nsamp > 0 && margin_ok) {
         // est: the ksamp-th smallest of the sample, by bisection on the key bits (keys in registers)
         // (fetching the row's first 1,024 keys once, for the sample and for the gathering pass
         // below, was slower: 16 more registers held across the bisection)
@@ -530,38 +468,8 @@ __global__ __launch_bounds__(WG) void coarse_shortlist_kernel(const uint32_t *__
             }
         }
         if (ng >= (uint32_t)nprobe && ng <= 256u && ng <= (uint32_t)cap) {
-            // few entries: no sort.  They go back into registers, the nprobe-th smallest key is
-            // found bit by bit, and the entries up to the widened threshold are packed.
-            wave_lds_sync();
-            uint64_t mine[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                const uint32_t i = 64u * u + lane;
-                mine[u] = i < ng ? sel[i] : ~0ull;
-            }
-            uint32_t kth = 0;                            // largest t with fewer than nprobe keys below it
-            for (int bit = 31; bit >= 0; bit--) {
-                const uint32_t cand = kth | (1u << bit);
-                uint32_t below = 0;
-#pragma unroll
-                for (int u = 0; u < 4; u++)
-                    if (64u * u < ng) below += (uint32_t)__popcll(__ballot((uint32_t)(mine[u] >> 32) < cand));
-                if (below < (uint32_t)nprobe) kth = cand;
-            }
-            const uint32_t thr = f32_key(key_f32(kth) + margin);
-            if (thr <= est) {
-                wave_lds_sync();                         // every lane holds its entries
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    if (64u * u < ng) {
-                        const bool in = 64u * u + lane < ng && (uint32_t)(mine[u] >> 32) <= thr;
-                        const unsigned long long m = __ballot(in);
-                        if (in) sel[nc + (uint32_t)__popcll(m & lt_mask)] = (uint64_t)(uint32_t)mine[u];
-                        nc += (uint32_t)__popcll(m);
-                    }
-                }
-                have = true;
-            }
+            nc = shortlist_pack(sel, ng, nprobe, margin, est, lane);
+            have = nc > 0;
         } else if (ng >= (uint32_t)nprobe && ng <= (uint32_t)cap) {
             const int n2 = next_pow2((int)ng < 2 ? 2 : (int)ng);
             for (int e = (int)ng + lane; e < n2; e += 64) sel[e] = ~0ull;
@@ -758,33 +666,28 @@ static bool coarse_shortlist_ok(const IndexView &v, int nprobe)
 }
 
 // The list with the smallest key of every query's row of the score matrix: where the bound's sample
-// is taken when it is to start before the probe lists exist.  The keys carry the matrix core's
+// is taken when it is to start before the probe lists exist (found through the half tiles' minima).  The keys carry the matrix core's
 // rounding, so this list is nearly always, but not provably, the nearest; whoever uses it checks
 // that it is among the query's probe lists.  One wave per query.
-__global__ __launch_bounds__(WG) void coarse_first_kernel(const uint32_t *__restrict__ keys, int nlist,
+__global__ __launch_bounds__(WG) void coarse_first_kernel(const uint32_t *__restrict__ keys,
+                                                          const uint32_t *__restrict__ hmin, int nlist, int nhalf,
                                                           int64_t nq, int32_t *__restrict__ first)
 {
     const int lane = threadIdx.x & 63;
     const int64_t qi = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
     if (qi >= nq) return;
-    const uint32_t *row = keys + (size_t)qi * nlist;
     uint64_t best = ~0ull;
-    for (int l0 = 0; l0 < nlist; l0 += 64 * 16) {
-        uint32_t kk[16];
-#pragma unroll
-        for (int u = 0; u < 16; u++) {
-            const int l = l0 + 64 * u + lane;
-            kk[u] = row[l < nlist ? l : nlist - 1];
-        }
-#pragma unroll
-        for (int u = 0; u < 16; u++) {
-            const int l = l0 + 64 * u + lane;
-            const uint64_t x = ((uint64_t)kk[u] << 32) | (uint32_t)l;
-            if (l < nlist && x < best) best = x;
-        }
+    for (int i = lane; i < nhalf; i += 64) {
+        const uint64_t x = ((uint64_t)hmin[(size_t)qi * nhalf + i] << 32) | (uint32_t)i;
+        best = x < best ? x : best;
     }
     best = wave_min_u64(best);
-    if (lane == 0) first[qi] = (int32_t)(uint32_t)best;
+    // the list of that half tile that has the key
+    const int ht = (int)(uint32_t)best, l16 = lane & 15;
+    const int l = 32 * (ht >> 1) + 4 * (ht & 1) + 8 * (l16 >> 2) + (l16 & 3);
+    const unsigned long long m = __ballot(lane < 16 && l < nlist && keys[(size_t)qi * nlist + (l < nlist ? l : 0)] == (uint32_t)(best >> 32));
+    const int src = m ? __ffsll((long long)m) - 1 : 0;
+    if (lane == src) first[qi] = l < nlist ? l : 0;
 }
 
 bool rairs_coarse_has_scores(const IndexView &v, int nprobe, const float *q)
@@ -792,15 +695,16 @@ bool rairs_coarse_has_scores(const IndexView &v, int nprobe, const float *q)
     return coarse_shortlist_ok(v, nprobe) && ((uintptr_t)q & 15) == 0;
 }
 
-int rairs_launch_coarse_first(const IndexView &v, const float *dmat, int64_t nq, int32_t *first, hipStream_t s)
+int rairs_launch_coarse_first(const IndexView &v, const float *dmat, const uint32_t *hmin, int64_t nq, int32_t *first,
+                              hipStream_t s)
 {
     hipLaunchKernelGGL(coarse_first_kernel, dim3((unsigned)((nq + WG / 64 - 1) / (WG / 64))), dim3(WG), 0, s,
-                       (const uint32_t *)dmat, v.nlist, nq, first);
+                       (const uint32_t *)dmat, hmin, v.nlist, rairs_half_tiles(v.nlist), nq, first);
     RAIRS_HIP(hipGetLastError());
     return RAIRS_OK;
 }
 
-int rairs_launch_coarse(const IndexView &v, const float *q, int64_t nq, int nprobe, float *dmat,
+int rairs_launch_coarse(const IndexView &v, const float *q, int64_t nq, int nprobe, float *dmat, uint32_t *hmin,
                         int32_t *probe_ids, float *probe_dists, uint32_t *flags, hipStream_t s,
                         hipEvent_t scored, hipStream_t s_select)
 {
@@ -809,13 +713,13 @@ int rairs_launch_coarse(const IndexView &v, const float *q, int64_t nq, int npro
         hipLaunchKernelGGL(coarse_dist_kernel, dim3((unsigned)nq, groups), dim3(WG), 0, s, q,
                            v.centroids_t, v.d, v.nlist, (uint32_t *)dmat, nullptr, v.metric);
         hipLaunchKernelGGL(coarse_select_kernel, dim3((unsigned)nq), dim3(WG), 0, s, (uint32_t *)dmat, v.nlist,
-                           nprobe, probe_ids, probe_dists, nullptr, nullptr, nullptr, 0, v.metric);
+                           nprobe, probe_ids, probe_dists, nullptr, nq, nullptr, nullptr, 0, v.metric);
         RAIRS_HIP(hipGetLastError());
         return RAIRS_OK;
     }
     // each workgroup: 128 queries x a run of list tiles; enough workgroups to fill the chip twice
     // over, but at least 4 tiles per run so that the query registers are loaded rarely
-    const int ntiles = (v.nlist + 31) / 32;
+    const int ntiles = (v.nlist + 31) / 32, ksteps = (v.d + 15) / 16, nhalf = rairs_half_tiles(v.nlist);
     const unsigned qblocks = (unsigned)((nq + GEMM_QWG - 1) / GEMM_QWG);
     int csplits = (int)((1024 + qblocks - 1) / qblocks);
     if (csplits > (ntiles + 3) / 4) csplits = (ntiles + 3) / 4;
@@ -825,43 +729,44 @@ int rairs_launch_coarse(const IndexView &v, const float *q, int64_t nq, int npro
     const dim3 grid(qblocks * csplits);
     uint32_t *keys = (uint32_t *)dmat;
     const float alpha = v.metric ? 1.0f : 2.0f;
-#define GEMM_CASE(D)                                                                              \
-    case D:                                                                                       \
-        hipLaunchKernelGGL(coarse_gemm_kernel<D>, grid, dim3(WG), 0, s, q, v.centroids_ct, v.cmean, v.cnorm, \
-                           v.nlist, csplits, tiles_per_split, nq, keys, alpha);                   \
-        break
-    switch (v.d) {
-        GEMM_CASE(32);
-        GEMM_CASE(64);
-        GEMM_CASE(96);
-        GEMM_CASE(128);
-        GEMM_CASE(256);
-    default: {
-        // any other multiple of 8: chunked kernel, four list tiles per workgroup when that still
-        // gives the chip enough workgroups, else one
-        const int g4 = (ntiles + 3) / 4;
-        if ((int64_t)qblocks * g4 >= 512)
-            hipLaunchKernelGGL(coarse_gemm_chunk_kernel<4>, dim3(qblocks * g4), dim3(WG), 0, s, q,
-                               v.centroids_ct, v.cmean, v.cnorm, v.d, v.nlist, g4, nq, keys, alpha);
+    const v4u *cop = (const v4u *)v.centroid_ops;
+#define GEMM_LAUNCH(KS_)                                                                          \
+    hipLaunchKernelGGL(coarse_gemm_kernel<KS_>, grid, dim3(WG), 0, s, q, cop, v.cmean, v.cnorm, v.d, v.nlist, ksteps, \
+                       csplits, tiles_per_split, nq, keys, hmin, alpha)
+    if (ksteps <= 2) GEMM_LAUNCH(2);
+    else if (ksteps <= 4) GEMM_LAUNCH(4);
+    else if (ksteps <= 6) GEMM_LAUNCH(6);
+    else if (ksteps <= 8) GEMM_LAUNCH(8);
+    else {
+        // longer rows, in chunks: two list tiles per workgroup, so that a query's pieces are made for
+        // both, when that still gives the chip enough workgroups, else one
+        const int g2 = (ntiles + 1) / 2;
+        if ((int64_t)qblocks * g2 >= 512)
+            hipLaunchKernelGGL(coarse_gemm_chunk_kernel<2>, dim3(qblocks * g2), dim3(WG), 0, s, q, cop, v.cmean, v.cnorm,
+                               v.d, v.nlist, ksteps, g2, nq, keys, hmin, alpha);
         else
-            hipLaunchKernelGGL(coarse_gemm_chunk_kernel<1>, dim3(qblocks * ntiles), dim3(WG), 0, s, q,
-                               v.centroids_ct, v.cmean, v.cnorm, v.d, v.nlist, ntiles, nq, keys, alpha);
+            hipLaunchKernelGGL(coarse_gemm_chunk_kernel<1>, dim3(qblocks * ntiles), dim3(WG), 0, s, q, cop, v.cmean, v.cnorm,
+                               v.d, v.nlist, ksteps, ntiles, nq, keys, hmin, alpha);
     }
-    }
-#undef GEMM_CASE
+#undef GEMM_LAUNCH
     if (scored) {
         // the score matrix is complete; the selection goes on on the other stream
         RAIRS_HIP(hipEventRecord(scored, s));
         RAIRS_HIP(hipStreamWaitEvent(s_select, scored, 0));
         s = s_select;
     }
-    // LDS room per query: the lists inside the margin (half more than nprobe, at least 64), or,
-    // when the sample route is used, the keys up to the sample's estimate (about 2-4 x nprobe)
+    // LDS room per query: the lists inside the margin (half more than nprobe, at least 64), or the
+    // keys up to the estimate: at most about twice nprobe from the half tiles' minima (as many as
+    // hold nprobe lists at 3/4 of them, and an eighth), about 2-4 x nprobe from the sample
     const int extra = nprobe / 2 > 64 ? nprobe / 2 : 64;
     int cap = next_pow2(nprobe + extra);
     if (cap < 64) cap = 64;
     int nsamp = 0, ksamp = 0;
-    if (nprobe <= 496 && v.nlist >= 4 * SHORTLIST_SAMPLE / 2 && 8 * nprobe <= v.nlist) {
+    const bool by_min = hmin && nprobe <= 200 && 4 * nprobe <= 3 * nhalf && nhalf <= 64 * 16;
+    if (by_min) {
+        const int cap2 = next_pow2(5 * nprobe / 2 + 32);
+        if (cap2 > cap) cap = cap2;
+    } else if (nprobe <= 496 && v.nlist >= 4 * SHORTLIST_SAMPLE / 2 && 8 * nprobe <= v.nlist) {
         nsamp = SHORTLIST_SAMPLE;
         // the sample's expected share of the nprobe best, plus three standard deviations and a bit
         const double share = (double)nprobe * nsamp / v.nlist;
@@ -871,22 +776,30 @@ int rairs_launch_coarse(const IndexView &v, const float *q, int64_t nq, int npro
         if (cap2 > cap) cap = cap2;
     }
     const size_t sel_bytes = (size_t)cap * 8 * (WG / 64);
-#define SHORTLIST_LAUNCH(IP_)                                                                     \
+#define SHORTLIST_LAUNCH(IP_, HR_)                                                                \
     do {                                                                                          \
         if (sel_bytes > 32 * 1024)                                                                \
-            RAIRS_HIP(hipFuncSetAttribute((const void *)coarse_shortlist_kernel<IP_>,              \
+            RAIRS_HIP(hipFuncSetAttribute((const void *)coarse_shortlist_kernel<IP_, HR_>,        \
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sel_bytes)); \
-        hipLaunchKernelGGL(coarse_shortlist_kernel<IP_>, dim3((unsigned)((nq + WG / 64 - 1) / (WG / 64))), \
-                           dim3(WG), sel_bytes, s, keys, q, v.centroids, v.d, v.nlist, nprobe, cap, nsamp, \
+        hipLaunchKernelGGL((coarse_shortlist_kernel<IP_, HR_>), dim3((unsigned)((nq + WG / 64 - 1) / (WG / 64))), \
+                           dim3(WG), sel_bytes, s, keys, hmin, nhalf, q, v.centroids, v.d, v.nlist, nprobe, cap, nsamp, \
                            ksamp, v.cmean, v.cmax2, nq, probe_ids, probe_dists, flags);           \
     } while (0)
-    if (v.metric) SHORTLIST_LAUNCH(true);
-    else SHORTLIST_LAUNCH(false);
+#define SHORTLIST_METRIC(HR_)                                                                     \
+    do { if (v.metric) SHORTLIST_LAUNCH(true, HR_); else SHORTLIST_LAUNCH(false, HR_); } while (0)
+    if (!by_min) SHORTLIST_METRIC(0);
+    else if (nhalf <= 64) SHORTLIST_METRIC(1);
+    else if (nhalf <= 256) SHORTLIST_METRIC(4);
+    else SHORTLIST_METRIC(16);
+#undef SHORTLIST_METRIC
 #undef SHORTLIST_LAUNCH
     // queries whose shortlist did not fit (many lists at nearly the same distance): full route,
-    // both steps by the query's own workgroup
-    hipLaunchKernelGGL(coarse_select_kernel, dim3((unsigned)nq), dim3(WG), 0, s, (uint32_t *)dmat, v.nlist, nprobe,
-                       probe_ids, probe_dists, flags, q, v.centroids_t, v.d, v.metric);
+    // both steps by one workgroup per query; at most 2,048 workgroups look at the flags (a workgroup
+    // per query: 22 us for 65,536 unflagged ones)
+    int64_t sgrid = nq < 2048 ? nq : 2048;
+    if (sgrid * WG < nq) sgrid = (nq + WG - 1) / WG;
+    hipLaunchKernelGGL(coarse_select_kernel, dim3((unsigned)sgrid), dim3(WG), 0, s, (uint32_t *)dmat, v.nlist, nprobe,
+                       probe_ids, probe_dists, flags, nq, q, v.centroids_t, v.d, v.metric);
     RAIRS_HIP(hipGetLastError());
     return RAIRS_OK;
 }

@@ -55,9 +55,9 @@ struct IndexView {
     int64_t ntotal, nblocks, nrefs;
     const float *centroids;       // [nlist][d]
     const float *centroids_t;     // [d][nlist]
-    const float *centroids_ct;    // [d][nlist] centred: fl(c - cmean)
+    const void *centroid_ops;     // the centred centroids fl(c - cmean) in matrix-core operand order (coarse_gemm.h)
     const float *cmean;           // [d] mean of the centroids
-    const float *cnorm;           // [nlist] squared norms of the centred centroids
+    const float *cnorm;           // [nlist, padded to whole tiles of 32] squared norms of the centred centroids
     float cmax2;                  // largest of them
     const float *codebook;        // [M][16][d/M]
     // codes: per block nd x 64 dwords; lane = parity * 32 + item; dword w of lane (g, item) packs
@@ -147,13 +147,19 @@ int rairs_launch_transpose(const float *d_in, int rows, int cols, float *d_out, 
 // dmat: [nq][nlist] words of scratch; flags: [nq] words of scratch (null: full route only)
 // scored (may be null; only with rairs_coarse_has_scores): recorded on s once the score matrix of
 // the matrix-core route is complete; the selection kernels then run on s_select behind it
-int rairs_launch_coarse(const IndexView &v, const float *q, int64_t nq, int nprobe, float *dmat,
+// hmin: [nq][rairs_half_tiles(nlist)] words of scratch for the minima of the score matrix by half
+// tiles, or null (then the selection reads whole rows, and rairs_launch_coarse_first cannot follow)
+static inline int rairs_half_tiles(int nlist) { return 2 * ((nlist + 31) / 32); }
+#define RAIRS_HMIN_MAX_NLIST 16384
+int rairs_launch_pack_centroids(const float *cent, const float *cmean, int d, int nlist, void *cop, hipStream_t s);
+int rairs_launch_coarse(const IndexView &v, const float *q, int64_t nq, int nprobe, float *dmat, uint32_t *hmin,
                         int32_t *probe_ids, float *probe_dists, uint32_t *flags, hipStream_t s,
                         hipEvent_t scored = nullptr, hipStream_t s_select = nullptr);
 // whether rairs_launch_coarse takes the matrix-core route for these arguments (given flags), i.e.
 // leaves the keys of all (query, list) pairs in dmat; and the list of each row's smallest key
 bool rairs_coarse_has_scores(const IndexView &v, int nprobe, const float *q);
-int rairs_launch_coarse_first(const IndexView &v, const float *dmat, int64_t nq, int32_t *first, hipStream_t s);
+int rairs_launch_coarse_first(const IndexView &v, const float *dmat, const uint32_t *hmin, int64_t nq, int32_t *first,
+                              hipStream_t s);
 int rairs_launch_bitmap(const IndexView &v, const int32_t *probe_ids, int64_t nq, int nprobe,
                         uint32_t *bitmap, int bmwords, uint32_t *hist, hipStream_t s);
 int rairs_launch_lut(const IndexView &v, const float *q, int64_t nq, uint8_t *lut, float *bias_sum,
