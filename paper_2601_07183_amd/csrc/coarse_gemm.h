@@ -47,15 +47,17 @@ static __device__ __forceinline__ void split_bf16x3(const float (&x)[8], v8bf (&
     }
 }
 
-// Eight centred values of a row, dimensions i0 .. i0 + 7 (zero from d on; d is a multiple of 8).
+// Eight centred values of a row, dimensions i0 .. i0 + 7 (zero from d on; d is a multiple of 4).
 static __device__ __forceinline__ void load_centred8(const float *row, const float *mean, int i0, int d, float (&x)[8])
 {
-    const int i = i0 < d ? i0 : 0;
-    const v4f a = *(const v4f *)(row + i), b = *(const v4f *)(row + i + 4);
-    const v4f m = *(const v4f *)(mean + i), n = *(const v4f *)(mean + i + 4);
-    const float y[8] = {a.x - m.x, a.y - m.y, a.z - m.z, a.w - m.w, b.x - n.x, b.y - n.y, b.z - n.z, b.w - n.w};
 #pragma unroll
-    for (int e = 0; e < 8; e++) x[e] = i0 < d ? y[e] : 0.0f;
+    for (int h = 0; h < 2; h++) {
+        const int i = i0 + 4 * h;
+        const bool in = i < d;
+        const v4f a = *(const v4f *)(row + (in ? i : 0)), m = *(const v4f *)(mean + (in ? i : 0));
+#pragma unroll
+        for (int e = 0; e < 4; e++) x[4 * h + e] = in ? a[e] - m[e] : 0.0f;
+    }
 }
 
 // The lists' operands (at upload): one wave per tile and step.

@@ -172,7 +172,8 @@ __global__ __launch_bounds__(WG) void coarse_select_kernel(uint32_t *dmat,
     if (only_flagged && qt < nq) mine = only_flagged[qt];
     flagged[tid] = mine;
     if (!__syncthreads_or((int)mine)) return;
-    for (int qn = 0; qn < WG; qn++) {
+    const int takes = only_flagged ? (int)((nq - blockIdx.x + gridDim.x - 1) / gridDim.x) : 1;
+    for (int qn = 0; qn < takes; qn++) {
     if (flagged[qn] == 0u) continue;                    // uniform
     const int64_t qi = (int64_t)blockIdx.x + (int64_t)qn * gridDim.x;
     __syncthreads();                                    // the shared state is the next query's
@@ -662,7 +663,7 @@ __global__ __launch_bounds__(WG) void coarse_shortlist_kernel(const uint32_t *__
 #define SHORTLIST_MAX_NPROBE 1024
 static bool coarse_shortlist_ok(const IndexView &v, int nprobe)
 {
-    return v.d % 8 == 0 && nprobe <= SHORTLIST_MAX_NPROBE && v.nlist >= 64;
+    return v.d % 4 == 0 && nprobe <= SHORTLIST_MAX_NPROBE && v.nlist >= 64;     // (rows of 16-byte aligned quads)
 }
 
 // The list with the smallest key of every query's row of the score matrix: where the bound's sample

@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
     (64, 8, (1, 3, 4, 64), "l2"), (97, 24, (1, 5, 6, 97), "l2"), (1023, 128, (1, 10, 47, 48, 49, 130), "l2"),
     (1024, 96, (10, 48, 64, 300), "ip"), (1026, 136, (23, 49, 50), "l2"), (4096, 32, (39, 191, 192, 200, 201), "l2"),
     (4130, 64, (200, 201, 260), "ip"), (1000, 960, (45, 47), "l2"), (512, 256, (24, 25), "l2"), (16384, 16, (98, 200), "l2"),
-    (16416, 16, (98,), "l2")])
+    (16416, 16, (98,), "l2"),
+    (500, 100, (12, 40), "l2"), (300, 4, (7, 30), "ip"), (260, 140, (9, 30), "l2"), (130, 18, (9,), "l2")])
 def test_probe_lists(nlist, d, nprobes, metric):
     from paper_2601_07183_amd import binding
     g = np.random.Generator(np.random.PCG64(nlist + d))
@@ -25,8 +26,8 @@ def test_probe_lists(nlist, d, nprobes, metric):
     cents[1:nlist:7] = cents[0:nlist - 1:7]                        # equal centroids: ties go to the smaller id
     x = cents[:40] + np.float32(0.1) * g.standard_normal((40, d)).astype(np.float32)
     asg = np.sort(g.integers(0, nlist, size=(40, 2)), axis=1).astype(np.int32)
-    M = d // 8
-    cb = ib.train_pq(datagen.random_vectors(5, 64, d), M + M % 2, 5, 2) if d % (M + M % 2) == 0 else ib.train_pq(datagen.random_vectors(5, 64, d), d // 2, 5, 2)
+    M = next(m for m in (16, 12, 10, 8, 6, 4, 2) if d % m == 0)
+    cb = ib.train_pq(datagen.random_vectors(5, 64, d), M, 5, 2)
     hx = ib.add_vectors(x.astype(np.float32), cents, cb, assign=asg, metric=metric)
     nq = 150
     q = (cents[g.integers(0, nlist, nq)] + 0.7 * g.standard_normal((nq, d))).astype(np.float32)
