@@ -1,4 +1,5 @@
-"""The coarse quantizer's shortlist route at the edges of its tiles and of its ways to a threshold."""
+"""The coarse quantizer's shortlist route at the edges of its tiles and of its ways to a threshold, and the
+assignment where its fp32 filter hands over to the definition."""
 import numpy as np
 import pytest
 import torch
@@ -74,5 +75,31 @@ def test_values_out_of_range():
             want, wd = oracle.coarse(ox, q[i], 9)
             assert (pid[i].cpu().numpy() == want).all(), i
             assert (pd[i].cpu().numpy() == wd).all(), i
+    finally:
+        ix.free()
+
+
+# rows that are no quads, equal centroids (exact ties of the loss), all candidate counts of the last
+# group of four, a huge and a negative lambda, values that overflow or underflow in fp32
+@pytest.mark.parametrize("d", [6, 20, 64, 130])
+def test_assign_ties_and_ranges(d):
+    from paper_2601_07183_amd import binding
+    g = np.random.Generator(np.random.PCG64(d))
+    cents = np.round(3.0 * g.standard_normal((70, d))).astype(np.float32)
+    cents[1::5] = cents[0:-1:5]
+    asg = np.sort(g.integers(0, 70, size=(40, 2)), axis=1).astype(np.int32)
+    cb = ib.train_pq(datagen.random_vectors(5, 64, d), 2, 5, 2)
+    hx = ib.add_vectors(cents[:40].copy(), cents, cb, assign=asg)
+    x = np.concatenate([np.round(2.0 * g.standard_normal((300, d))), g.standard_normal((200, d))]).astype(np.float32)
+    x[7] *= np.float32(1e-22)
+    x[8] *= np.float32(1e17)
+    ix = binding.Index(hx)
+    try:
+        for nc in (1, 2, 4, 5, 10, 16, 17, 32):
+            for lam, strict in ((0.5, True), (0.5, False), (1e30, True), (-1.0, True)):
+                print("case: assign", d, nc, lam, strict, flush=True)
+                got = ix.assign(torch.from_numpy(x).cuda(), nc, lam, strict)
+                torch.cuda.synchronize()
+                assert (got.cpu().numpy() == oracle.rair_assign(cents, x, nc, lam, strict)).all()
     finally:
         ix.free()
