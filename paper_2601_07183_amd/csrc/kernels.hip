@@ -1000,9 +1000,11 @@ int rairs_launch_pq_encode(const float *cb, int d, int M, const float *x, int64_
 // r_i = centroid_i - v, in float64 with both sums sequential over the dimensions; the pair is written
 // ordered by list id.
 // Sixteen lanes per vector, which first take the losses in fp32 (any order, fused) and a bound on their
-// error: with u = 2^-24 and |<r_0, r_i>| <= (||r_0||^2 + ||r_i||^2) / 2, rounding the differences and
-// the sums of d terms costs at most (d + 8) u (||r_i||^2 + |lambda| (||r_0||^2 + ||r_i||^2) / 2), taken
-// four times as large (the last term: products that underflow).  If one candidate is ahead of every
+// error: with u = 2^-24 and |<r_0, r_i>| <= (||r_0||^2 + ||r_i||^2) / 2, rounding the differences, the
+// sums of d terms, lambda and its product costs at most (d + 16) u (||r_i||^2 + |lambda| (||r_0||^2 +
+// ||r_i||^2) / 2), taken four times as large.  Products that underflow lose up to 2^-126 each, of which
+// those of <r_0, r_i> count |lambda| times: (d + 16) (1 + |lambda|) 2^-125.  (A lambda for which that is
+// no number leaves every vector to the definition.)  If one candidate is ahead of every
 // other by more than their errors it is the minimum in float64 too, which is so for all but about one
 // vector in a hundred; the others go through the definition, a lane per candidate.
 // (The definition for all, a thread per vector and candidate, was bound by its loads: every lane of a
@@ -1023,6 +1025,7 @@ __global__ __launch_bounds__(WG) void air_assign_kernel(IndexView v, const float
     const int32_t *cv = cand + (size_t)vec * nc;
     const float *xv = x + (size_t)vec * d, *p0 = v.centroids + (size_t)cv[0] * d;
     const float lam = (float)lambda, eps = 4.0f * (float)(d + 16) * 5.9604645e-8f, alam = __builtin_fabsf(lam);
+    const float tiny = (float)(d + 16) * 2.3509887e-38f * (1.0f + alam);
     float best = 0.0f, best_hi = 0.0f, best_lo = 0.0f, others = __builtin_inff(), l20 = 0.0f;
     int besti = -1;
     bool bad = false;
@@ -1074,7 +1077,7 @@ __global__ __launch_bounds__(WG) void air_assign_kernel(IndexView v, const float
             if (i == 0) l20 = s;
             if (i < nc && i >= strict) {                 // uniform
                 const float loss = s + lam * t;
-                const float err = eps * (s + alam * (l20 + s)) + 1.0e-36f;
+                const float err = eps * (s + alam * (l20 + s)) + tiny;
                 const float lo = loss - err, hi = loss + err;
                 bad = bad || !(lo <= hi) || !(__builtin_fabsf(loss) < 3.0e38f);
                 if (besti < 0 || loss < best) {

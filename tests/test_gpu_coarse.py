@@ -80,7 +80,8 @@ def test_values_out_of_range():
 
 
 # rows that are no quads, equal centroids (exact ties of the loss), all candidate counts of the last
-# group of four, a huge and a negative lambda, values that overflow or underflow in fp32
+# group of four, a huge and a negative lambda, values that overflow in fp32 (and a tiny vector, whose
+# residuals are the centroids')
 @pytest.mark.parametrize("d", [6, 20, 64, 130])
 def test_assign_ties_and_ranges(d):
     from paper_2601_07183_amd import binding
@@ -103,3 +104,31 @@ def test_assign_ties_and_ranges(d):
                 assert (got.cpu().numpy() == oracle.rair_assign(cents, x, nc, lam, strict)).all()
     finally:
         ix.free()
+
+
+# centroids and vectors so small that products of residuals underflow in fp32, beside a lambda that
+# brings their sum back into its range: the filter has to leave these to the definition
+@pytest.mark.parametrize("nlist,d", [(40, 4), (40, 6), (70, 20), (70, 64)])
+def test_assign_residuals_that_underflow(nlist, d):
+    from paper_2601_07183_amd import binding
+    g = np.random.Generator(np.random.PCG64(nlist + d))
+    cb = ib.train_pq(datagen.random_vectors(5, 64, d), 2, 5, 2)
+    asg = np.sort(g.integers(0, nlist, size=(40, 2)), axis=1).astype(np.int32)
+    for scale in (1e-16, 1e-19, 1e-21, 3e-23):
+        cents = (scale * g.standard_normal((nlist, d))).astype(np.float32)
+        if scale < 1e-22:                                # the nearest three: only the third is the minimum
+            cents[:] = np.float32(1e-21)
+            cents[0], cents[1], cents[2] = 2e-23, 2.8e-23, 0.0
+            cents[2, 0] = 4.2e-23
+        x = (0.2 * scale * g.standard_normal((300, d))).astype(np.float32)
+        x[0] = 0.0
+        hx = ib.add_vectors(x[:40].copy(), cents, cb, assign=asg)
+        ix = binding.Index(hx)
+        try:
+            for lam, nc in ((1e10, 3), (1e10, 10), (-1e12, 10), (1e20, 10), (1e33, 5), (0.5, 10)):
+                print("case: assign", d, scale, lam, nc, flush=True)
+                got = ix.assign(torch.from_numpy(x).cuda(), nc, lam, True)
+                torch.cuda.synchronize()
+                assert (got.cpu().numpy() == oracle.rair_assign(cents, x, nc, lam, True)).all()
+        finally:
+            ix.free()
