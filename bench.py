@@ -555,11 +555,11 @@ def main():
     # contraction = 32 ops, so the ops the kernel stands for are items x M x 32 (partly filled
     # query tiles and list tails count as lost).  The register-table kernel issues the 2:4-sparse
     # int8 matrix instruction, the LDS-table kernel the dense one: each is priced against the
-    # peak of ITS instruction.  The exact kernel does its lookups on the vector units.
+    # peak of ITS instruction.  The exact kernel and that of small batches do their lookups on the vector units.
     kernel = ix.scan_kernel_name()
     kms = stage["scan_kernel"]
     lookups = float(dco.sum()) * w.M
-    if kernel == "scan_exact_kernel":
+    if kernel in ("scan_exact_kernel", "few_scan_kernel"):
         bound, unit = "alu", "T lane-ops/s"
         achieved, peak = lookups * 2 / (kms * 1e-3) / 1e12, LANE_OPS_PEAK / 1e12   # a lookup and an add per code
     else:

@@ -239,10 +239,11 @@ int rairs_refine(rairs_index_t *h, const float *d_queries, const int64_t *d_cand
  * in registers for M = 16, 48, 64, in LDS for any other M), selection of the bigK best survivors,
  * and the exact one-workgroup-per-query kernel for queries whose survivors do not fit their buffer.
  * Small batches of rairs_search whose queries share few lists score by table lookups, several
- * workgroups per query, instead.  RAIRS_SCAN_EXACT: the exact kernel for everything.  Results are
- * identical in all of them.
+ * workgroups per query, instead.  RAIRS_SCAN_EXACT: the exact kernel for everything.
+ * RAIRS_SCAN_LIST_MAJOR: as RAIRS_SCAN_AUTO, small batches too.  Results are identical in all of
+ * them.
  */
-enum { RAIRS_SCAN_AUTO = 0, RAIRS_SCAN_EXACT = 1 };
+enum { RAIRS_SCAN_AUTO = 0, RAIRS_SCAN_EXACT = 1, RAIRS_SCAN_LIST_MAJOR = 2 };
 int rairs_set_scan_mode(rairs_index_t *h, int mode);
 
 /* ---- measurement --------------------------------------------------------------------------- */
@@ -291,10 +292,12 @@ int rairs_get_dco(rairs_index_t *h, int64_t *dco, int64_t nq);
 int rairs_get_scan_stats(rairs_index_t *h, int64_t *stats);
 
 /*
- * Name of the dominant kernel that SeilSearch launches for this index in the current scan mode:
- * (for batches; small ones run "few_scan_kernel" whatever the index) "scan_mfma_kernel" (2:4-sparse int8 matrix instruction, tables in registers),
- * "scan_mfma_lds_kernel" (dense int8 matrix instruction, tables in LDS) or "scan_exact_kernel"
- * (table lookups on the vector units).  A static string; NULL for a NULL handle.
+ * Name of the dominant kernel that SeilSearch launches for this index: "scan_mfma_kernel" (2:4-sparse
+ * int8 matrix instruction, tables in registers), "scan_mfma_lds_kernel" (dense int8 matrix
+ * instruction, tables in LDS) or "scan_exact_kernel" (table lookups on the vector units), by index and
+ * scan mode; "few_scan_kernel" (table lookups, several workgroups per query) if the handle's last
+ * search took the path of small batches (rairs_scan, rairs_set_scan_mode: the first three again).  A
+ * static string; NULL for a NULL handle.
  */
 const char *rairs_scan_kernel_name(const rairs_index_t *h);
 

@@ -287,8 +287,9 @@ class Index:
                                       _dev(dists, torch.float32, "dists"), _stream_ptr(stream)))
         return ids, dists
 
-    def set_scan_mode(self, exact: bool):
-        _check(self._lib.rairs_set_scan_mode(self._h, C.c_int(1 if exact else 0)))
+    def set_scan_mode(self, exact: bool, list_major: bool = False):
+        """rairs_set_scan_mode: automatic, the exact kernel, or (list_major) the list-major search for small batches too."""
+        _check(self._lib.rairs_set_scan_mode(self._h, C.c_int(1 if exact else 2 if list_major else 0)))
 
     # --- measurement ----------------------------------------------------------------------
     def set_profiling(self, level):

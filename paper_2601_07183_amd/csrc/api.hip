@@ -705,7 +705,7 @@ static FewLayout few_layout(const rairs_index *h, int64_t nq, int nprobe, int re
 static bool use_few(const rairs_index *h, int64_t nq, int nprobe, int refine_k, size_t list_major_bytes)
 {
     const IndexView &v = h->v;
-    if (h->force_exact || !rairs_mfma_supported(v) || v.nlist < 64 || v.nlist > FEW_MAX_NLIST ||
+    if (h->scan_mode != RAIRS_SCAN_AUTO || !rairs_mfma_supported(v) || v.nlist < 64 || v.nlist > FEW_MAX_NLIST ||
         nprobe > FEW_MAX_NPROBE || nq > FEW_MAX_QUERIES || v.ntotal == 0 || h->seg_blocks_max[nprobe] >= FEW_MAX_BLOCKS)
         return false;
     const int64_t blocks = (h->seg_blocks_total * nprobe + v.nlist - 1) / v.nlist;     // of a query, on average
@@ -876,7 +876,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     // query's row, and only its ranking waits for the probe lists (see search_impl).
     const IndexView &v = h->v;
     uint32_t *bitmap = (uint32_t *)(ws + w.bitmap);
-    const bool mfma = rairs_mfma_supported(v) && !h->force_exact;
+    const bool mfma = rairs_mfma_supported(v) && h->scan_mode != RAIRS_SCAN_EXACT;
     // With the sample on the matrix cores nothing on the caller's stream reads the bitmaps before
     // the scan does, so they (and the zeroed histograms) are made on the side stream ahead of the
     // grouping, whose event the scan waits for anyway.
@@ -893,6 +893,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     ea.nprobe = nprobe; ea.refine_k = refine_k; ea.dco = dco;
     ea.cand_ids = cand_ids; ea.cand_score = cand_score;
     h->last_pass_n = 0;
+    h->last_few = 0;
     if (!mfma) {
         if (ev) RAIRS_HIP(hipEventRecord(ev[0], s));
         rc = rairs_launch_scan_exact(v, ea, n, s);
@@ -1058,6 +1059,7 @@ static int search_few(rairs_index *h, char *ws, int ws_source, const float *d_qu
     h->last_dco = a.dco;
     h->last_dco_n = nq;
     h->last_pass_n = nq; h->last_flags_off = w.flags; h->last_cnt_off = w.surv_cnt; h->last_log_chunks = 0;
+    h->last_few = 1;
     const int plevel = ws_source != WS_GRAPH ? h->prof : 0;
     hipEvent_t *ev = h->ev[h->ev_count % RAIRS_EV_RING];
     FewEvents se = {nullptr, nullptr, nullptr, nullptr};
@@ -1130,7 +1132,7 @@ static int search_impl(rairs_index *h, int ws_source, const float *d_queries, in
         // stream goes straight on with the bound's sample, taken from the list with the smallest
         // key of the query's row; see scan_pass.  The chain that the scan waits for -- GEMM,
         // sample, ranking -- thus stays on one stream, with no event hop in it.
-        const bool early = overlap && !h->force_exact && rairs_mfma_supported(v) &&
+        const bool early = overlap && h->scan_mode != RAIRS_SCAN_EXACT && rairs_mfma_supported(v) &&
                            grouped_sample(v, n, refine_k) && rairs_coarse_has_scores(v, nprobe, q);
         if ((rc = rairs_launch_coarse(v, q, n, nprobe, (float *)(ws + w.dmat), ws_hmin(ws, w), probe_ids,
                                       (float *)(ws + w.probe_dists), (uint32_t *)(ws + w.cflags), s,
@@ -1222,6 +1224,7 @@ extern "C" int rairs_graph_create(rairs_index_t *h, const float *d_queries, int6
     // one eager run first: kernels whose attributes are set at launch get that done outside the capture
     h->graph_ws = g->ws;
     h->graph_ws_bytes = g->ws_bytes;
+    const int last_few = h->last_few;
     rc = search_impl(h, WS_GRAPH, d_queries, nq, k, nprobe, refine_k, d_out_ids, d_out_dists, hip_stream);
     if (rc == RAIRS_OK && hipStreamSynchronize(s) != hipSuccess) {
         rairs_set_error("the warm-up search failed: %s", hipGetErrorString(hipGetLastError()));
@@ -1247,6 +1250,7 @@ extern "C" int rairs_graph_create(rairs_index_t *h, const float *d_queries, int6
     h->last_pass_n = 0;
     h->last_dco = nullptr;
     h->last_dco_n = 0;
+    h->last_few = last_few;
     if (rc == RAIRS_OK) {
         e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);
         if (e != hipSuccess) {
@@ -1298,15 +1302,18 @@ extern "C" int rairs_set_workspace(rairs_index_t *h, void *d_ws, size_t bytes)
 extern "C" int rairs_set_scan_mode(rairs_index_t *h, int mode)
 {
     if (!h) FAIL(RAIRS_EINVAL, "handle is NULL");
-    if (mode != RAIRS_SCAN_AUTO && mode != RAIRS_SCAN_EXACT) FAIL(RAIRS_EINVAL, "unknown scan mode %d", mode);
-    h->force_exact = mode == RAIRS_SCAN_EXACT;
+    if (mode != RAIRS_SCAN_AUTO && mode != RAIRS_SCAN_EXACT && mode != RAIRS_SCAN_LIST_MAJOR)
+        FAIL(RAIRS_EINVAL, "unknown scan mode %d", mode);
+    h->scan_mode = mode;
+    h->last_few = 0;
     return RAIRS_OK;
 }
 
 extern "C" const char *rairs_scan_kernel_name(const rairs_index_t *h)
 {
     if (!h) return nullptr;
-    if (h->force_exact || !rairs_mfma_supported(h->v)) return "scan_exact_kernel";
+    if (h->last_few) return "few_scan_kernel";
+    if (h->scan_mode == RAIRS_SCAN_EXACT || !rairs_mfma_supported(h->v)) return "scan_exact_kernel";
     return rairs_mfma_reg_tables(h->v) ? "scan_mfma_kernel" : "scan_mfma_lds_kernel";
 }
 

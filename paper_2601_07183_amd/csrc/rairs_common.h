@@ -110,7 +110,8 @@ struct rairs_index {
     int64_t *last_dco;            // DCO counts of the last rairs_search, inside that workspace
     int64_t last_dco_n;
     // profiling
-    int force_exact;
+    int scan_mode;                // RAIRS_SCAN_AUTO, _EXACT or _LIST_MAJOR
+    int last_few;                 // the handle's last search took the few-query path
     int64_t last_pass_n;          // queries of the last MFMA pass (0: none)
     size_t last_flags_off, last_cnt_off, last_fill_off;
     int last_log_chunks;          // 0: the last pass kept no log (few-query search: every survivor is counted once)

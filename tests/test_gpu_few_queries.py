@@ -32,9 +32,9 @@ def _check(binding, hx, q, cases):
             # both sides sum in the defined order: equal bits
             assert (dists.cpu().numpy() == want.dists).all()
             assert (ix.dco(nq) == want.dco).all()
+            assert ix.scan_kernel_name() == "few_scan_kernel"
             st = ix.scan_stats()
-            assert st["queries"] == nq and st["redone"] == 0
-            assert st["survivors"] == st["logged"]           # kept without a log: this path
+            assert st["queries"] == nq and st["survivors"] == st["logged"] > 0       # kept without a log
     finally:
         ix.free()
 
@@ -71,7 +71,7 @@ def test_full_buffers_and_ties(binding):
 
 def test_equal_centroids_and_large_directory(binding):
     # centroids in groups of identical rows: list ids decide among equal distances, also at the
-    # nprobe-th place; a directory of several thousand lists (eight and 32 keys per thread)
+    # nprobe-th place; a directory of several thousand lists (four and sixteen keys per thread)
     g = np.random.Generator(np.random.PCG64(9))
     for nlist in (1500, 5000):
         n, d = 8000, 16

@@ -55,20 +55,26 @@ def _compare_all_stages(binding, hx, q, k, nprobe, refine_k):
         for i in range(0, len(q), max(1, len(q) // 8)):
             _, _, ob, osc = oracle.lut(ox, q[i])
             assert bias[i].item() == np.float32(ob) and scale[i].item() == np.float32(osc)
-        for exact in (False, True):                  # MFMA list-major path, then exact-only path
-            ix.set_scan_mode(exact)
+        # MFMA list-major path, exact-only path, and what a call without a mode takes (small batches
+        # over 64 lists and more: the few-query search)
+        for mode in ("list-major", "exact", "auto"):
+            ix.set_scan_mode(mode == "exact", list_major=mode == "list-major")
             # scan on the ORACLE's tables and probe lists: integer work, bit exact
             cand, score, dco = ix.scan(_dev(want.lut), _dev(want.probes), refine_k)
             torch.cuda.synchronize()
-            assert (cand.cpu().numpy() == want.cand_ids).all(), f"exact={exact}"
-            assert (score.cpu().numpy() == want.cand_acc).all(), f"exact={exact}"
-            assert (dco.cpu().numpy() == want.dco).all(), f"exact={exact}"
+            assert (cand.cpu().numpy() == want.cand_ids).all(), mode
+            assert (score.cpu().numpy() == want.cand_acc).all(), mode
+            assert (dco.cpu().numpy() == want.dco).all(), mode
             # whole path
             ids, dists = ix.search(dq, k, nprobe, refine_k)
             torch.cuda.synchronize()
-            assert (ids.cpu().numpy() == want.ids).all(), f"exact={exact}"
+            assert (ids.cpu().numpy() == want.ids).all(), mode
             _assert_dists(dists.cpu().numpy(), want.dists)
             assert (ix.dco(len(q)) == want.dco).all()
+            if mode == "list-major":
+                assert ix.scan_kernel_name() in ("scan_mfma_kernel", "scan_mfma_lds_kernel")
+            elif mode == "exact":
+                assert ix.scan_kernel_name() == "scan_exact_kernel"
         # refine on the ORACLE's candidates
         rid, rd = ix.refine(dq, _dev(want.cand_ids), k)
         torch.cuda.synchronize()
@@ -527,14 +533,19 @@ def test_inner_product_coarse_routes(binding):
             ix.free()
 
 
-@pytest.mark.parametrize("nq", [1, 7])
-def test_search_graph_replays(binding, tiny_workload, nq):
+@pytest.mark.parametrize("nq,few", [(1, True), (7, True), (1, False), (7, False)])
+def test_search_graph_replays(binding, tiny_workload, nq, few):
     # a captured search replayed several times on new queries, with eager searches and
     # synchronisations of the same handle in between: every replay must equal the eager result
     w, base, q, hx = tiny_workload
+    # (few: the search of small batches; else the list-major one)
     want = oracle.search(oracle.OracleIndex(hx), q, w.k, 16, w.refine_k)
     ix = binding.Index(hx)
     try:
+        ix.set_scan_mode(False, list_major=not few)
+        ix.search(_dev(q[:nq]), w.k, 16, w.refine_k)
+        torch.cuda.synchronize()
+        assert (ix.scan_kernel_name() == "few_scan_kernel") == few
         stream = torch.cuda.Stream()
         with torch.cuda.stream(stream):
             dq = torch.zeros((nq, hx.d), dtype=torch.float32, device="cuda")
@@ -563,7 +574,8 @@ def test_search_graph_replays(binding, tiny_workload, nq):
         ix.free()
 
 
-def test_caller_owned_workspace(binding, tiny_workload):
+@pytest.mark.parametrize("few", [True, False])
+def test_caller_owned_workspace(binding, tiny_workload, few):
     # rairs_workspace_bytes / rairs_set_workspace through the C ABI: a torch tensor serves as the
     # workspace; one byte too few is RAIRS_EWORKSPACE and enqueues nothing; the library's own
     # workspace and the caller's give the same bits
@@ -573,6 +585,7 @@ def test_caller_owned_workspace(binding, tiny_workload):
     want = oracle.search(oracle.OracleIndex(hx), q, w.k, 16, w.refine_k)
     ix = binding.Index(hx)
     try:
+        ix.set_scan_mode(False, list_major=not few)
         dq = _dev(q)
         need = ix.workspace_bytes(len(q), 16, w.refine_k)
         assert need > 0 and ix.workspace_bytes(0, 16, w.refine_k) == 0
@@ -599,6 +612,7 @@ def test_caller_owned_workspace(binding, tiny_workload):
         assert (ids.cpu().numpy() == want.ids).all()
         _assert_dists(dists.cpu().numpy(), want.dists)
         assert (ix.dco(len(q)) == want.dco).all()
+        assert (ix.scan_kernel_name() == "few_scan_kernel") == few
         # back to the handle's own workspace: same bits
         ix.use_own_workspace()
         ids2, dists2 = ix.search(dq, w.k, 16, w.refine_k)
@@ -629,11 +643,13 @@ def test_argument_errors_and_empty_batch(binding, small_index):
     ix.free()                                               # second free is a no-op
 
 
-def test_stage_timers(binding, tiny_workload):
+@pytest.mark.parametrize("few", [True, False])
+def test_stage_timers(binding, tiny_workload, few):
     # the stage timers are measurement helpers: levels, the ring of recorded searches, errors
     w, base, q, hx = tiny_workload
     ix = binding.Index(hx)
     try:
+        ix.set_scan_mode(False, list_major=not few)
         dq = _dev(q)
         with pytest.raises(binding.RairsError):
             ix.stage_ms()                                    # nothing recorded yet
@@ -646,6 +662,7 @@ def test_stage_timers(binding, tiny_workload):
         ix.set_profiling(binding.PROFILE_STAGES)
         for _ in range(3):
             ids, _ = ix.search(dq, w.k, 16, w.refine_k)
+        assert (ix.scan_kernel_name() == "few_scan_kernel") == few
         one, mean = ix.stage_ms(), ix.stage_ms_mean(3)
         assert all(v > 0 for v in one.values()) and all(v > 0 for v in mean.values())
         assert one["scan_kernel"] <= one["scan"]

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-def test_search_noalloc_matches_search_on_two_calls_in_a_row():
+@pytest.mark.parametrize("few", [True, False])           # the search of small batches; the list-major one
+def test_search_noalloc_matches_search_on_two_calls_in_a_row(few):
     from paper_2601_07183_amd import binding
     lib = binding.load()
     assert torch.cuda.is_available(), "gpu tests need a GPU"
@@ -23,6 +24,7 @@ def test_search_noalloc_matches_search_on_two_calls_in_a_row():
     hx = ib.build_index(base, w.nlist, w.M, seed=w.seed)
     ix = binding.Index(hx)
     try:
+        ix.set_scan_mode(False, list_major=not few)
         # the second call is smaller (fewer queries, fewer probes, smaller bigK) and runs in the
         # same array, which still holds the first call's contents
         for nq, k, nprobe, refine_k in ((200, 10, 16, 40), (37, 5, 4, 20)):
@@ -37,6 +39,7 @@ def test_search_noalloc_matches_search_on_two_calls_in_a_row():
                 C.c_int(refine_k), C.c_void_p(ids.data_ptr()), C.c_void_p(dists.data_ptr()),
                 C.c_void_p(torch.cuda.current_stream().cuda_stream))
             assert rc == 0, lib.rairs_last_error()
+            assert (ix.scan_kernel_name() == "few_scan_kernel") == few
             torch.cuda.synchronize()
             # bit-exact against the existing entry point (ids) and the same distance bits
             assert (ids == ref_ids).all()
