@@ -281,7 +281,11 @@ __global__ __launch_bounds__(WG) void coarse_select_kernel(uint32_t *dmat,
 // 12 KB of a 64 KB row at 98 of 16,384 lists, after 4 KB of minima.  (Whole rows / this, 10,000
 // queries: 98 of 16,384 lists 360 / 114 us, 39 of 4,096 56 / 37, 23 of 1,024 36 / 24.  Up to 3/4 of
 // the half tiles, where the entries at or below the estimate are about twice nprobe; beyond it
-// they grow fast.)
+// they grow fast.  Of nhalf half tiles, nprobe of which have their minimum at or below it, the estimate
+// lets in about nhalf ln(1 / (1 - 9/8 nprobe / nhalf)) entries: more than the 256 that are narrowed in
+// four registers from about 140 of 4,096 or 180 of 8,192 lists on.  Up to 512 are narrowed in eight,
+// more are sorted; the whole stage by the row's sample / by the minima but for more than 256 entries
+// the radix select / this: 176 of 4,096 x 128 350 / 317 / 214 us, 200 of 8,192 x 96 603 / 673 / 393.)
 // Else the nprobe-th smallest key is found in one pass over the row when a sample allows it: the
 // ksamp-th smallest key `est` of the row's first `nsamp` keys is, with ksamp chosen well above the
 // sample's share of nprobe, above the nprobe-th smallest of the row; every key <= est is gathered
@@ -290,17 +294,18 @@ __global__ __launch_bounds__(WG) void coarse_select_kernel(uint32_t *dmat,
 // to a radix select over the whole row (four passes), which always works.
 #define SHORTLIST_SAMPLE 512
 
-// A wave's shortlist cut to what the margin asks for: ng <= 256 entries (key << 32 | list), at least
+// A wave's shortlist cut to what the margin asks for: ng <= 64 U entries (key << 32 | list), at least
 // nprobe of them, in the wave's own LDS region.  They go back into registers, the nprobe-th smallest
 // key is found bit by bit, and the lists up to the widened threshold are packed: no sort.  Returns
 // their number; 0, and nothing is changed, if the threshold is above est.
+template <int U>
 static __device__ __forceinline__ uint32_t shortlist_pack(uint64_t *sel, uint32_t ng, int nprobe, float margin,
                                                           uint32_t est, int lane)
 {
     wave_lds_sync();
-    uint64_t mine[4];
+    uint64_t mine[U];
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
+    for (int u = 0; u < U; u++) {
         const uint32_t i = 64u * u + lane;
         mine[u] = i < ng ? sel[i] : ~0ull;
     }
@@ -309,7 +314,7 @@ static __device__ __forceinline__ uint32_t shortlist_pack(uint64_t *sel, uint32_
         const uint32_t cand = kth | (1u << bit);
         uint32_t below = 0;
 #pragma unroll
-        for (int u = 0; u < 4; u++)
+        for (int u = 0; u < U; u++)
             if (64u * u < ng) below += (uint32_t)__popcll(__ballot((uint32_t)(mine[u] >> 32) < cand));
         if (below < (uint32_t)nprobe) kth = cand;
     }
@@ -318,13 +323,32 @@ static __device__ __forceinline__ uint32_t shortlist_pack(uint64_t *sel, uint32_
     wave_lds_sync();                                     // every lane holds its entries
     uint32_t nc = 0;
 #pragma unroll
-    for (int u = 0; u < 4; u++) {
+    for (int u = 0; u < U; u++) {
         if (64u * u < ng) {
             const bool in = 64u * u + lane < ng && (uint32_t)(mine[u] >> 32) <= thr;
             const unsigned long long m = __ballot(in);
             if (in) sel[nc + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint64_t)(uint32_t)mine[u];
             nc += (uint32_t)__popcll(m);
         }
+    }
+    return nc;
+}
+
+// The same for more entries (up to the room there is): by a sort, the shortlist is its head.
+static __device__ __forceinline__ uint32_t shortlist_sort(uint64_t *sel, uint32_t ng, int nprobe, float margin,
+                                                          uint32_t est, int lane)
+{
+    const int n2 = next_pow2((int)ng < 2 ? 2 : (int)ng);
+    for (int e = (int)ng + lane; e < n2; e += 64) sel[e] = ~0ull;
+    wave_lds_sync();
+    wave_bitonic_sort_lds(sel, n2, lane);
+    const uint32_t kth = (uint32_t)(sel[nprobe - 1] >> 32);
+    const uint32_t thr = f32_key(key_f32(kth) + margin);
+    if (thr > est) return 0;
+    uint32_t nc = 0;
+    for (int e0 = 0; e0 < (int)ng; e0 += 64) {
+        const int e = e0 + lane;
+        nc += (uint32_t)__popcll(__ballot(e < (int)ng && (uint32_t)(sel[e] >> 32) <= thr));
     }
     return nc;
 }
@@ -425,7 +449,11 @@ __global__ __launch_bounds__(WG) void coarse_shortlist_kernel(const uint32_t *__
                 }
             }
             // (hardly more than there have to be: all of them are re-scored)
-            if (ng <= (uint32_t)cap && ng <= 256u) nc = ng <= (uint32_t)nprobe + 8u ? ng : shortlist_pack(sel, ng, nprobe, margin, 0xFFFFFFFFu, lane);
+            if (ng <= (uint32_t)cap)
+                nc = ng <= (uint32_t)nprobe + 8u ? ng
+                   : ng <= 256u ? shortlist_pack<4>(sel, ng, nprobe, margin, 0xFFFFFFFFu, lane)
+                   : ng <= 512u ? shortlist_pack<8>(sel, ng, nprobe, margin, 0xFFFFFFFFu, lane)
+                                : shortlist_sort(sel, ng, nprobe, margin, 0xFFFFFFFFu, lane);
             have = nc > 0;
         }
     } else if (nsamp > 0 && margin_ok) {
@@ -468,24 +496,9 @@ __global__ __launch_bounds__(WG) void coarse_shortlist_kernel(const uint32_t *__
                 ng += (uint32_t)__popcll(m);
             }
         }
-        if (ng >= (uint32_t)nprobe && ng <= 256u && ng <= (uint32_t)cap) {
-            nc = shortlist_pack(sel, ng, nprobe, margin, est, lane);
+        if (ng >= (uint32_t)nprobe && ng <= (uint32_t)cap) {
+            nc = ng <= 256u ? shortlist_pack<4>(sel, ng, nprobe, margin, est, lane) : shortlist_sort(sel, ng, nprobe, margin, est, lane);
             have = nc > 0;
-        } else if (ng >= (uint32_t)nprobe && ng <= (uint32_t)cap) {
-            const int n2 = next_pow2((int)ng < 2 ? 2 : (int)ng);
-            for (int e = (int)ng + lane; e < n2; e += 64) sel[e] = ~0ull;
-            wave_lds_sync();
-            wave_bitonic_sort_lds(sel, n2, lane);
-            const uint32_t kth = (uint32_t)(sel[nprobe - 1] >> 32);
-            const uint32_t thr = f32_key(key_f32(kth) + margin);
-            if (thr <= est) {
-                // the sorted entries up to thr are the shortlist
-                for (int e0 = 0; e0 < (int)ng; e0 += 64) {
-                    const int e = e0 + lane;
-                    nc += (uint32_t)__popcll(__ballot(e < (int)ng && (uint32_t)(sel[e] >> 32) <= thr));
-                }
-                have = true;
-            }
         }
     }
     bool fits = true;

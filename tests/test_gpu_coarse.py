@@ -13,11 +13,11 @@ pytestmark = pytest.mark.gpu
 
 # nlist: partial tiles, rows of 4-byte and 16-byte alignment, 64 / 256 / 1,024 half tiles and one tile
 # more; d: partial steps of 16, one chunk of 128, partial and whole further ones; nprobe: around
-# 3/4 of the half tiles and beyond the 256 entries that a wave narrows; batches of partial tiles
+# 3/4 of the half tiles and beyond the 256 entries that a wave narrows without a sort; batches of partial tiles
 @pytest.mark.parametrize("nlist,d,nprobes,metric", [
     (64, 8, (1, 3, 4, 64), "l2"), (97, 24, (1, 5, 6, 97), "l2"), (1023, 128, (1, 10, 47, 48, 49, 130), "l2"),
     (1024, 96, (10, 48, 64, 300), "ip"), (1026, 136, (23, 49, 50), "l2"), (4096, 32, (39, 191, 192, 200, 201), "l2"),
-    (4130, 64, (200, 201, 260), "ip"), (1000, 960, (45, 47), "l2"), (512, 256, (24, 25), "l2"), (16384, 16, (98, 200), "l2"),
+    (4130, 64, (200, 201, 260), "ip"), (1000, 960, (45, 47), "l2"), (512, 256, (24, 25), "l2"), (8192, 16, (150, 192, 200), "l2"), (16384, 16, (98, 200), "l2"),
     (16416, 16, (98,), "l2"),
     (500, 100, (12, 40), "l2"), (300, 4, (7, 30), "ip"), (260, 140, (9, 30), "l2"), (130, 18, (9,), "l2")])
 def test_probe_lists(nlist, d, nprobes, metric):
