@@ -939,7 +939,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     ma.work = (uint32_t *)(ws + w.work);
     ma.hist = (uint32_t *)(ws + w.hist);
     h->last_pass_n = n; h->last_flags_off = w.flags; h->last_cnt_off = w.surv_cnt;
-    h->last_fill_off = w.chunk_fill; h->last_log_chunks = w.log_chunks;
+    h->last_fill_off = w.chunk_fill; h->last_cursor_off = w.log_misc; h->last_log_chunks = w.log_chunks;
     ma.log = (uint2 *)(ws + w.log); ma.chunk_fill = (uint32_t *)(ws + w.chunk_fill);
     ma.log_cursor = (uint32_t *)(ws + w.log_misc); ma.log_overflow = ma.log_cursor + 1;
     ma.log_chunks = w.log_chunks;
@@ -1381,7 +1381,9 @@ extern "C" int rairs_get_scan_stats(rairs_index_t *h, int64_t *stats)
     if (h->last_log_chunks == 0) { stats[4] = stats[1]; return RAIRS_OK; }
     std::vector<uint32_t> fill((size_t)h->last_log_chunks);
     RAIRS_HIP(hipMemcpy(fill.data(), (char *)h->last_ws + h->last_fill_off, fill.size() * 4, hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < fill.size(); i++) stats[4] += fill[i];
+    uint32_t used = 0;                                 // chunks handed out; the words behind them count spilled survivors
+    RAIRS_HIP(hipMemcpy(&used, (char *)h->last_ws + h->last_cursor_off, 4, hipMemcpyDeviceToHost));
+    for (size_t i = 0; i < fill.size() && i < used; i++) stats[4] += fill[i];
     return RAIRS_OK;
 }
 

@@ -113,7 +113,7 @@ struct rairs_index {
     int scan_mode;                // RAIRS_SCAN_AUTO, _EXACT or _LIST_MAJOR
     int last_few;                 // the handle's last search took the few-query path
     int64_t last_pass_n;          // queries of the last MFMA pass (0: none)
-    size_t last_flags_off, last_cnt_off, last_fill_off;
+    size_t last_flags_off, last_cnt_off, last_fill_off, last_cursor_off;
     int last_log_chunks;          // 0: the last pass kept no log (few-query search: every survivor is counted once)
     int prof, prof_valid;
     float stage_ms[RAIRS_NSTAGES];
@@ -237,9 +237,9 @@ struct MfmaScanArgs {
     uint32_t *flags;              // [nq] set when the survivor buffer overflowed
     uint32_t *work;               // [2][1 + nq] {count, query ...}: queries for the workgroup-wide select; flagged queries
     uint2 *log;                   // [log_chunks][RAIRS_LOG_CHUNK] survivor log {slot, score << 16 | query of the pass}
-    uint32_t *chunk_fill;         // [log_chunks] entries written to each chunk
+    uint32_t *chunk_fill;         // [log_chunks] entries written to each chunk; behind the chunks handed out: see LogSpill
     uint32_t *log_cursor;         // [1] chunks handed out
-    uint32_t *log_overflow;       // [2] set if the log ran out of chunks; entries spilled from full survivor buffers
+    uint32_t *log_overflow;       // [2] set if the log ran out of chunks; entries of full survivor buffers when no chunk is left for them
     int log_chunks;
     unsigned long long *dco;      // [nq] items scored per query, counted as blocks are contracted; may be null
     int any_order;                // the bigK candidates may be written in any order (the whole search: refine orders them anyway)

@@ -74,7 +74,7 @@ __global__ void lm_zero_kernel(int32_t *lcount, int32_t *lcursor, int nlist, uin
     if (gid < nlist) { lcount[gid] = 0; lcursor[gid] = 0; }
     if (gid < nq) { surv_cnt[gid] = 0; if (dco) dco[gid] = 0ull; }
     if (gid < log_chunks) chunk_fill[gid] = 0;
-    if (gid == 0) { *next_task = first_task; *log_cursor = 0u; log_overflow[0] = 0; log_overflow[1] = 0; }   // (the cursor: set again with the unit count; [1]: spilled entries)
+    if (gid == 0) { *next_task = first_task; *log_cursor = 0u; log_overflow[0] = 0; log_overflow[1] = 0; }   // (the cursor: set again with the unit count)
     if (gid == 0) { work[0] = 0u; work[1 + nq] = 0u; }   // the two lists of queries for the kernels behind the scan
 }
 
@@ -772,7 +772,6 @@ __global__ __launch_bounds__(COLLECT_WG) void collect_kernel(MfmaScanArgs a)
     __shared__ uint32_t cnt[COLLECT_SLOTS], base[COLLECT_SLOTS];
     const int tid = threadIdx.x;
     const uint32_t lim = log_chunks_used(a);
-    const LogSpill spill = log_spill(a);
     for (uint32_t c = blockIdx.x; c < lim; c += gridDim.x) {
     const uint32_t n = a.chunk_fill[c];
     if (n == 0) continue;                               // uniform
@@ -821,7 +820,8 @@ __global__ __launch_bounds__(COLLECT_WG) void collect_kernel(MfmaScanArgs a)
             const uint32_t pos = slot[k] >= 0 ? base[slot[k]] + rank[k] : atomicAdd(&a.surv_cnt[qid], 1u);
             if (pos < (uint32_t)a.surv_cap)
                 a.surv_buf[(size_t)qid * a.surv_cap + pos] = ((uint64_t)(e[k].y >> 16) << 48) | e[k].x;
-            else if (pos < SURV_CAP_MAX) {              // rare: see log_spill
+            else if (pos < SURV_CAP_MAX) {              // rare: see LogSpill
+                const LogSpill spill = log_spill(a, (uint32_t)qid);
                 const uint32_t at = atomicAdd(spill.count, 1u);
                 if (at < spill.room) spill.ent[at] = e[k];
             }
@@ -865,8 +865,12 @@ __global__ __launch_bounds__(WG) void select_wave_kernel(IndexView v, MfmaScanAr
     const uint32_t n = a.surv_cnt[q];
     // (queries that this kernel leaves to the two kernels behind it go on a list each, so that those
     // kernels, which normally have nothing to do, are a few workgroups looking at a count)
-    const LogSpill spill = log_spill(a);
-    if (n > SURV_CAP_MAX || *a.log_overflow != 0u || (n > (uint32_t)a.surv_cap && *spill.count > spill.room)) {
+    bool redo_it = n > SURV_CAP_MAX || *a.log_overflow != 0u;
+    if (!redo_it && n > (uint32_t)a.surv_cap) {
+        const LogSpill spill = log_spill(a, (uint32_t)q);
+        redo_it = *spill.count > spill.room;
+    }
+    if (redo_it) {
         if (lane == 0) {
             a.flags[q] = 1;                 // redone by the exact kernel
             uint32_t *redo = a.work + 1 + a.nq;

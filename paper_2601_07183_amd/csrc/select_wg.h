@@ -2,15 +2,22 @@
 // its list (more survivors than a wave holds): resolve the survivors and keep the bigK smallest
 // (score, id).  A two-pass radix select on the 16-bit score finds the score of the bigK-th
 // survivor; only entries up to that score are sorted.  A query's survivors beyond its buffer come
-// from the spill (up to SURV_CAP_MAX in all; more than that, or a spill without room, and the wave
+// from the spill (up to SURV_CAP_MAX in all; more than that, or a full bucket of the spill, and the wave
 // kernel puts the query on the list of the exact redo instead).
 #pragma once
 #include "device_util.h"
 
 // Survivors that do not fit their query's buffer go, as log entries, to the unused chunks at the end of
-// the survivor log.  A buffer is sized so that one query in some ten thousand needs this, and the
-// alternative, the exact redo, is one workgroup's walk through all lists of the query: 19 ms on an
-// 8M x 128 index with 98 probes and 17 ms on 200,000 x 960 with 45, for batches of 5.8 and 1.2 ms.
+// the survivor log.  A buffer is sized so that one query in some ten thousand needs this where a bound
+// exists, and the alternative, the exact redo, is one workgroup's walk through all lists of the query:
+// 19 ms on an 8M x 128 index with 98 probes and 17 ms on 200,000 x 960 with 45, for batches of 5.8 and
+// 1.2 ms.  Where lists are shorter than bigK there is no bound and whole batches come here, so the chunks
+// are dealt out to the queries in buckets of SPILL_CHUNKS, counted in the fill word of their first
+// chunk: a query walks only the bucket that it shares with every so-many-th other query.  (12,800
+// queries, 32 probes of lists of some 50 items, 5,267 of them over: 3.9 ms with all of those redone, 15.7
+// with a walk over everything that was spilled for each, 2.3 with buckets.)  A bucket holds what two to four queries can spill; a
+// full one sends its queries to the redo.
+#define SPILL_CHUNKS 4
 struct LogSpill {
     uint2 *ent;                   // {slot, score << 16 | query of the pass}
     uint32_t *count;              // entries that wanted to go there, `room` of them did
@@ -21,11 +28,12 @@ static __device__ __forceinline__ uint32_t log_chunks_used(const MfmaScanArgs &a
     const uint32_t lim = *a.log_cursor;                 // chunks handed out
     return lim < (uint32_t)a.log_chunks ? lim : (uint32_t)a.log_chunks;
 }
-static __device__ __forceinline__ LogSpill log_spill(const MfmaScanArgs &a)
+static __device__ __forceinline__ LogSpill log_spill(const MfmaScanArgs &a, uint32_t q)
 {
-    const uint32_t lim = log_chunks_used(a);
-    const uint64_t room = (uint64_t)((uint32_t)a.log_chunks - lim) * RAIRS_LOG_CHUNK;
-    return {a.log + (size_t)lim * RAIRS_LOG_CHUNK, a.log_overflow + 1, room < 0x7FFFFFFFull ? (uint32_t)room : 0x7FFFFFFFu};
+    const uint32_t lim = log_chunks_used(a), left = (uint32_t)a.log_chunks - lim, buckets = left / SPILL_CHUNKS;
+    if (left == 0) return {a.log, a.log_overflow + 1, 0u};
+    const uint32_t c = buckets ? lim + q % buckets * SPILL_CHUNKS : lim;
+    return {a.log + (size_t)c * RAIRS_LOG_CHUNK, a.chunk_fill + c, (buckets ? SPILL_CHUNKS : left) * RAIRS_LOG_CHUNK};
 }
 
 struct SelectShared {
@@ -64,7 +72,7 @@ static __device__ __forceinline__ void select_query_wg(const IndexView &v, const
         keys[i] = resolve((uint32_t)e, (uint32_t)(e >> 48));
     }
     if (n > (uint32_t)a.surv_cap) {         // uniform: the rest of them is in the spill, among other queries' entries
-        const LogSpill spill = log_spill(a);
+        const LogSpill spill = log_spill(a, (uint32_t)q);
         const uint32_t ns = *spill.count;   // (at most spill.room, or the query would be on the other list)
         __syncthreads();
         for (uint32_t i = (uint32_t)tid; i < ns; i += WG) {

@@ -15,17 +15,28 @@ pytestmark = pytest.mark.gpu
 # all of them are in shared blocks and a query of the clump has exactly that many survivors.
 @pytest.mark.parametrize("counts,redone", [((1024, 1056), 0), ((1056, 2048), 0), ((4096, 64), 0), ((4128, 1056), 7)])
 def test_spilled_survivors(counts, redone):
+    _check(counts, (7, 8), (redone, redone), 8, 4)
+
+
+# whole batches over their buffers, the log's unused chunks dealt out in buckets: a few hundred entries
+# from each of 300 queries (all fit), and 3,072 from each of 220, which overfill theirs and are redone
+@pytest.mark.parametrize("counts,queries,redone", [((1504, 64), (300, 300), (0, 0)), ((4096, 64), (220, 380), (1, 220))])
+def test_many_spilled_queries(counts, queries, redone):
+    _check(counts, queries, redone, 32, 16)
+
+
+def _check(counts, queries, redone, d, M):
     from paper_2601_07183_amd import binding
-    va = datagen.random_vectors(60, 1, 8)
+    va = datagen.random_vectors(60, 1, d)
     vb = va + np.float32(40)
-    e = np.zeros((1, 8), np.float32)
+    e = np.zeros((1, d), np.float32)
     e[0, 0] = 0.5
     x = np.concatenate([np.tile(va, (counts[0], 1)), np.tile(vb, (counts[1], 1))])
     cents = np.concatenate([va + e, va - e, vb + e, vb - e]).astype(np.float32)
     asg = np.array([[0, 1]] * counts[0] + [[2, 3]] * counts[1], dtype=np.int32)
-    cb = ib.train_pq(datagen.random_vectors(61, 300, 8), 4, 5, 2)
-    noise = datagen.random_vectors(62, 15, 8) * np.float32(0.01)
-    q = (np.concatenate([np.tile(va, (7, 1)), np.tile(vb, (8, 1))]) + noise).astype(np.float32)
+    cb = ib.train_pq(datagen.random_vectors(61, 300, d), M, 5, 2)
+    noise = datagen.random_vectors(62, sum(queries), d) * np.float32(0.01)
+    q = (np.concatenate([np.tile(va, (queries[0], 1)), np.tile(vb, (queries[1], 1))]) + noise).astype(np.float32)
     hx = ib.add_vectors(x, cents, cb, assign=asg)
     want = oracle.search(oracle.OracleIndex(hx), q, 10, 2, 64)
     ix = binding.Index(hx)
@@ -38,6 +49,9 @@ def test_spilled_survivors(counts, redone):
             assert (ids.cpu().numpy() == want.ids).all()
             assert (dists.cpu().numpy() == want.dists).all()
             assert (ix.dco(len(q)) == want.dco).all()
-            assert ix.scan_stats()["redone"] == redone
+            st = ix.scan_stats()
+            print("   ", st, flush=True)
+            assert redone[0] <= st["redone"] <= redone[1]
+            assert st["max_survivors"] == max(counts) and st["logged"] == st["survivors"]
     finally:
         ix.free()
