@@ -401,6 +401,9 @@ static int upload_impl(const rairs_host_index_t *x, void *hip_stream, rairs_inde
                 nb[(size_t)l] += hs[(size_t)sidx].nblk;
             h->seg_blocks_total += nb[(size_t)l];
         }
+        double sq = 0.0;
+        for (int l = 0; l < x->nlist; l++) sq += (double)nb[(size_t)l] * (double)nb[(size_t)l];
+        h->seg_blocks_seen = h->seg_blocks_total ? (int64_t)(sq / (double)h->seg_blocks_total + 0.5) : 0;
         const int most = x->nlist < FEW_MAX_NPROBE ? x->nlist : FEW_MAX_NPROBE;
         std::partial_sort(nb.begin(), nb.begin() + most, nb.end(), std::greater<int64_t>());
         int64_t sum = 0;
@@ -645,16 +648,41 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
 
 // ---- the few-query search -----------------------------------------------------------------------
 
-// Batches up to this much work take the few-query search: code dwords per lane over the blocks of
-// all (query, probed list) pairs, plus the fixed cost of a query (its probe and finish workgroups)
-// in the same unit, at about 0.11 ns each.  The list-major search of a small batch takes 200 to 350 us
-// whatever its size.  Measured, few-query / list-major, 1M x 128 index, nprobe 23: 100 queries 94 /
-// 358 us, 400: 284 / 345, 800: 585 / 355; 2M x 96, nprobe 39: 400 queries 164 / 321, 1,000: 353 /
-// 313; 20,000 x 32, nprobe 4: 200 queries 31 / 211.
-#ifndef FEW_MAX_WORK
+// The rule that sends a batch to the few-query search: its work against what the list-major search of the
+// same batch is known to cost.  Work per query in units of a code dword of all 64 lanes looked up, about
+// 0.05 ns on the full chip: those of the blocks of its probed lists, its workgroups of the probe and the
+// finish kernel (350), the direct-form distances (a unit for seven lists and for 550 of their
+// dimensions), the candidates and the tables (5 per candidate and per sub-quantizer).  A query meets
+// large lists more often than small ones: the blocks of a probed list are taken as the list's that an
+// average block is in, which is within a third of what was counted on all indexes below (the plain mean
+// is ten times too low on the 200,000 x 960 one).  The list-major search of a small batch costs
+// its dozen dependent kernels: some 80 us, more with bigK, with more than four dwords of codes, with
+// eight probed lists and more and with a large directory; and several times that where most lists
+// are too short to give the scan a bound (fewer than two thirds of bigK items).  FEW_MAX_WORK, in which a query counts 512 and
+// a block the mean, keeps the batches out that were never measured to gain.
+// Measured (few-query / list-major, us; the line lies between the last two figures of each list):
+//   1M x 128, 1,024 lists    nprobe 23: 100 queries 104 / 362, 400: 350 / 335, 800: 633 / 342
+//                            nprobe 1: 1,600 queries 195 / 279, 3,200: 364 / 329
+//   2M x 96, 4,096 lists     nprobe 39: 400 queries 170 / 314, 800: 347 / 301
+//   1M x 128, 16,384 lists   nprobe 1, bigK 10: 400 queries 180 / 240, 3,200: 1,161 / 382 (800: 334 / 265)
+//   200,000 x 960, M = 240   nprobe 45: 100 queries 452 / 873, 200: 843 / 732; nprobe 1: 800: 319 / 396,
+//                            1,600: 565 / 470
+//   20,000 x 32, M = 16      nprobe 4: 1,600 queries 134 / 245, 6,400: 368 / 302
 #define FEW_MAX_WORK 2500000ll
-#endif
 #define FEW_QUERY_WORK 512ll
+static bool few_pays(const rairs_index *h, int64_t nq, int nprobe, int refine_k)
+{
+    const IndexView &v = h->v;
+    const int64_t mean_blocks = (h->seg_blocks_total * nprobe + v.nlist - 1) / v.nlist;
+    if (nq * (mean_blocks * v.nd + FEW_QUERY_WORK) > FEW_MAX_WORK) return false;
+    const int64_t blocks = std::min(std::min(h->seg_blocks_seen * nprobe, h->seg_blocks_total), (int64_t)h->seg_blocks_max[nprobe]);
+    const int64_t work = blocks * v.nd + 350 + v.nlist / 7 + (int64_t)v.nlist * v.d / 550 + 5ll * refine_k + 5ll * v.M;
+    int64_t limit = 1500000 + 20000ll * refine_k + 75ll * v.nlist;
+    if (v.nd > 4) limit += 2000000;
+    if (nprobe >= 8) limit += v.nd > 4 ? 4000000 : 1200000;
+    if (nprobe > 1 && 48 * h->seg_blocks_total < (int64_t)refine_k * v.nlist) limit *= 4;
+    return nq * work <= limit;
+}
 #define FEW_TARGET_WGS 2048         // scan workgroups that a batch is spread over
 #define FEW_MAX_QUERIES 65535
 #ifndef FEW_SAMPLE_TIMES
@@ -708,8 +736,7 @@ static bool use_few(const rairs_index *h, int64_t nq, int nprobe, int refine_k, 
     if (h->scan_mode != RAIRS_SCAN_AUTO || !rairs_mfma_supported(v) || v.nlist < 64 || v.nlist > FEW_MAX_NLIST ||
         nprobe > FEW_MAX_NPROBE || nq > FEW_MAX_QUERIES || v.ntotal == 0 || h->seg_blocks_max[nprobe] >= FEW_MAX_BLOCKS)
         return false;
-    const int64_t blocks = (h->seg_blocks_total * nprobe + v.nlist - 1) / v.nlist;     // of a query, on average
-    if (nq * (blocks * v.nd + FEW_QUERY_WORK) > FEW_MAX_WORK) return false;
+    if (!few_pays(h, nq, nprobe, refine_k)) return false;
     return few_layout(h, nq, nprobe, refine_k).total <= list_major_bytes;
 }
 

@@ -95,6 +95,7 @@ struct rairs_index {
     void *dev_alloc[24];
     int64_t nsegs, nparts;
     int64_t seg_blocks_total;     // blocks of all segments of all lists (a shared block counts in both of its lists)
+    int64_t seg_blocks_seen;      // blocks of the list that a block is in, on average over the blocks
     int32_t seg_blocks_max[FEW_MAX_NPROBE + 1];  // [p]: most of them that any p lists hold together
     int max_parts;                // most parts in any list (bounds the work-unit table)
     int ndev_alloc;

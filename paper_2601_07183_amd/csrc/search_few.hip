@@ -2,7 +2,7 @@
 // list-major path of scan_mfma.hip fills the 32 columns of a matrix tile with queries that probe
 // the same list and needs some fifteen kernels to set that up; with a few queries per list most
 // columns are empty and the set-up is the cost.  Here every query keeps its own workgroups and
-// the whole search is four kernels (the rule that chooses is FEW_MAX_WORK in api.hip):
+// the whole search is four kernels (the rule that chooses is few_pays in api.hip):
 //
 //   front:  distances of all (query, list) pairs in the direct form, and the lookup tables;
 //   probe:  per query the nprobe smallest, the probe bitmap, the blocks of its lists (reference cells
@@ -21,7 +21,7 @@
 // What bounds it: for one query the chain of launches, barriers and memory round trips (1M x 128
 // index, nprobe 23: 3.4 + 10 + 6 + 8 us of kernels, 30 us a search; 147 us list-major), for a
 // hundred the scan's lookups -- 1.9 vector instructions and one two-cycle LDS read each, 7 to 8 *
-// 10^12 lookups/s on the chip (100 queries at nprobe 32: 482 -> 124 us).
+// 10^12 lookups/s on the chip (100 queries at nprobe 32: 386 -> 115 us).
 #include "device_util.h"
 #include "lut_build.h"
 

@@ -90,3 +90,31 @@ def test_deleted_items(binding):
     hx = ib.build_index(base, 64, 16, seed=3, coarse_iters=4, pq_iters=4)
     hx = ib.delete_ids(hx, g.permutation(5000)[:2500])
     _check(binding, hx, base[:20], [(1, 10, 8, 40), (20, 10, 12, 100), (3, 10, 64, 1024)])
+
+
+# which search a batch takes: thousands of queries that only meet many distances (16,384 lists), or lists
+# that are large where the average one is small, are list-major batches; both ways agree
+@pytest.mark.parametrize("nlist,d,big,nprobe,few_nq,lm_nq", [(16384, 16, 0, 1, 200, 3000), (64, 32, 40000, 4, 100, 1500)])
+def test_route(binding, nlist, d, big, nprobe, few_nq, lm_nq):
+    g = np.random.Generator(np.random.PCG64(nlist))
+    n = 2000 + big
+    cents = g.standard_normal((nlist, d)).astype(np.float32)
+    asg = np.sort(g.integers(0, nlist, size=(n, 2)), axis=1).astype(np.int32)
+    asg[2000:] = (0, 1)
+    base = g.standard_normal((n, d)).astype(np.float32)
+    hx = ib.add_vectors(base, cents, ib.train_pq(base[:2000], 16, 3, 2), assign=asg)
+    q = g.standard_normal((lm_nq, d)).astype(np.float32)
+    ix = binding.Index(hx)
+    try:
+        dq = torch.from_numpy(q).cuda()
+        for nq, few in ((1, True), (few_nq, True), (lm_nq, False)):
+            print("case: route", nlist, d, nprobe, nq, flush=True)
+            ix.set_scan_mode(False, list_major=True)
+            want = ix.search(dq[:nq], 10, nprobe, 40)
+            ix.set_scan_mode(False)
+            ids, dists = ix.search(dq[:nq], 10, nprobe, 40)
+            torch.cuda.synchronize()
+            assert (ix.scan_kernel_name() == "few_scan_kernel") == few
+            assert (ids == want[0]).all() and (dists == want[1]).all()
+    finally:
+        ix.free()
