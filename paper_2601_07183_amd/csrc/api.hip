@@ -654,8 +654,8 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
 // finish kernel (350), the direct-form distances (a unit for seven lists and for 550 of their
 // dimensions), the candidates and the tables (5 per candidate and per sub-quantizer).  A query meets
 // large lists more often than small ones: the blocks of a probed list are taken as the list's that an
-// average block is in, which is within a third of what was counted on all indexes below (the plain mean
-// is ten times too low on the 200,000 x 960 one).  The list-major search of a small batch costs
+// average block is in, which is within a factor of two of what was counted (the plain mean is ten times too
+// low on the 200,000 x 960 index below).  The list-major search of a small batch costs
 // its dozen dependent kernels: some 80 us, more with bigK, with more than four dwords of codes, with
 // eight probed lists and more and with a large directory; and several times that where most lists
 // are too short to give the scan a bound (fewer than two thirds of bigK items).  FEW_MAX_WORK, in which a query counts 512 and

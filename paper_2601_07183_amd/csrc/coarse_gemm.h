@@ -11,9 +11,10 @@
 // of 32 cycles instead of 64 of 64 for a 32 x 32 tile at d = 128.  Measured (fp32 instruction / this):
 // 10,000 queries against 16,384 x 128 centroids 530 / 358 us, 4,096 x 96 113 / 86, 1,000 against
 // 1,024 x 960 90 / 38, 65,536 against 1,024 x 128 189 / 127; bound now by the operand fetch and the
-// store of the keys next to the products.  Root mean square error of the scores against 64 bits, 700
-// queries (fp32 instruction / this): d = 128 1.2e-3 / 8.5e-4 at scores of 2e4, d = 96 2.5e-8 / 1.5e-8
-// at 0.4, d = 960 4.6e-9 / 2.8e-9 at 0.07, d = 32 5.8e-7 / 4.4e-7 at 12; no shape is further off.
+// store of the keys next to the products.  Error of the scores against 64 bits over 700 queries and all
+// lists (root mean square and largest, fp32 instruction / this): d = 128 1.2e-3, 2.6e-2 / 8.5e-4, 9.2e-3 at
+// scores of 2e4; d = 96 2.5e-8, 3.8e-7 / 1.5e-8, 1.1e-7 at 0.4; d = 960 4.7e-9, 1.5e-7 / 2.8e-9, 3.7e-8 at
+// 0.07; d = 32 5.8e-7, 6.3e-6 / 4.4e-7, 3.0e-6 at 12; of nine shapes and both metrics none is further off.
 //
 // A workgroup takes 128 queries, 32 per wave, whose pieces stay in registers; the lists' pieces are
 // laid out at upload in operand order ([tile][step of 16 dimensions][piece][lane] 16-byte operands,

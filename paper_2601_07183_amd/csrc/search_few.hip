@@ -19,7 +19,7 @@
 // queries, so there are no global atomics and nothing has to be cleared beforehand.
 //
 // What bounds it: for one query the chain of launches, barriers and memory round trips (1M x 128
-// index, nprobe 23: 3.4 + 10 + 6 + 8 us of kernels, 30 us a search; 147 us list-major), for a
+// index, nprobe 23: 4 + 12 + 5 + 9 us of kernels, 30 to 35 us a search; 147 us list-major), for a
 // hundred the scan's lookups -- 1.9 vector instructions and one two-cycle LDS read each, 7 to 8 *
 // 10^12 lookups/s on the chip (100 queries at nprobe 32: 386 -> 115 us).
 #include "device_util.h"
