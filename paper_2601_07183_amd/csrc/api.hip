@@ -658,8 +658,9 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
 // low on the 200,000 x 960 index below).  The list-major search of a small batch costs
 // its dozen dependent kernels: some 80 us, more with bigK, with more than four dwords of codes, with
 // eight probed lists and more and with a large directory; and several times that where most lists
-// are too short to give the scan a bound (fewer than two thirds of bigK items).  FEW_MAX_WORK, in which a query counts 512 and
-// a block the mean, keeps the batches out that were never measured to gain.
+// are too short to give the scan a bound (fewer than two thirds of bigK items).  FEW_MAX_WORK, in which a
+// query counts 512 and a block the mean, is a limit on top (beyond it some batches over short lists with
+// many probes would gain as well).
 // Measured (few-query / list-major, us; the line lies between the last two figures of each list):
 //   1M x 128, 1,024 lists    nprobe 23: 100 queries 104 / 362, 400: 350 / 335, 800: 633 / 342
 //                            nprobe 1: 1,600 queries 195 / 279, 3,200: 364 / 329
