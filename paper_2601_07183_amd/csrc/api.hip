@@ -656,7 +656,7 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
 // large lists more often than small ones: the blocks of a probed list are taken as the list's that an
 // average block is in, which is within a factor of two of what was counted (the plain mean is ten times too
 // low on the 200,000 x 960 index below).  The list-major search of a small batch costs
-// its dozen dependent kernels: some 80 us, more with bigK, with more than four dwords of codes, with
+// its dozen dependent kernels: some 90 us, more with bigK, with more than four dwords of codes, with
 // eight probed lists and more and with a large directory; and several times that where most lists
 // are too short to give the scan a bound (fewer than two thirds of bigK items).  FEW_MAX_WORK, in which a
 // query counts 512 and a block the mean, is a limit on top (beyond it some batches over short lists with
@@ -678,9 +678,9 @@ static bool few_pays(const rairs_index *h, int64_t nq, int nprobe, int refine_k)
     if (nq * (mean_blocks * v.nd + FEW_QUERY_WORK) > FEW_MAX_WORK) return false;
     const int64_t blocks = std::min(std::min(h->seg_blocks_seen * nprobe, h->seg_blocks_total), (int64_t)h->seg_blocks_max[nprobe]);
     const int64_t work = blocks * v.nd + 350 + v.nlist / 7 + (int64_t)v.nlist * v.d / 550 + 5ll * refine_k + 5ll * v.M;
-    int64_t limit = 1500000 + 20000ll * refine_k + 75ll * v.nlist;
-    if (v.nd > 4) limit += 2000000;
-    if (nprobe >= 8) limit += v.nd > 4 ? 4000000 : 1200000;
+    int64_t limit = 1800000 + 24000ll * refine_k + 90ll * v.nlist;
+    if (v.nd > 4) limit += 2400000;
+    if (nprobe >= 8) limit += v.nd > 4 ? 4800000 : 1450000;
     if (nprobe > 1 && 48 * h->seg_blocks_total < (int64_t)refine_k * v.nlist) limit *= 4;
     return nq * work <= limit;
 }
