@@ -545,9 +545,10 @@ struct WsLayout {
     size_t dmat, cflags, probe_ids, probe_dists, bitmap, lut, cand, dco;
     size_t lcount, loff, lcursor, toff, unit_list, unit_rec, next_task, qlist, tau, bound, surv_cnt, flags, work, hist, surv_buf, log, chunk_fill, log_misc, total;
     size_t hmin;                  // 0: none (more lists than RAIRS_HMIN_MAX_NLIST)
+    size_t tables;                // of the scan: behind sample scores and minima, in bytes that the survivor buffers get later
     size_t s_off, s_toff, s_q, s_tiles, s_scores, s_first;      // matrix-core sample (0 bytes when not used)
     int sample_blocks;
-    int log_chunks;
+    int log_chunks, split_max;
     int surv_cap;
     int bmwords;
 };
@@ -615,13 +616,21 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     w.work = take((size_t)2 * (1 + nq) * 4);
     w.surv_cap = surv_cap_for(refine_k);
     {
-        // Chunks of RAIRS_LOG_CHUNK entries; a wave moves on when its next flush (up to 128 entries)
-        // does not fit, and every wave that gets a unit holds a current and a reserved chunk.
+        // Chunks of RAIRS_LOG_CHUNK entries: log_per_query_for for every query, and what the waves hold that get
+        // a unit or a slice of one, a chunk each and some for the next.
         const int64_t units = (nq * nprobe < nq * nprobe / 32 + v.nlist ? nq * nprobe : nq * nprobe / 32 + v.nlist) *
                               (int64_t)(max_parts > 0 ? max_parts : 1);
         const int64_t active = rairs_scan_log_waves(v, units);
         w.log_chunks = (int)((nq * log_per_query_for(refine_k) + RAIRS_LOG_CHUNK - 128) / (RAIRS_LOG_CHUNK - 127) +
                              2 * active + 16);
+        // Units are cut into as many slices as there are chunks for, four at most, and no further than leaves a query
+        // with 16 pieces: the waves at a query's pieces learn of each other's survivors late, and with more of them
+        // at once so much stays above the final bound that buffers overflow.  (28,000 x 32, 97 lists: 1,000
+        // queries x 4 lists 236 us whole and 200 in four slices; 300 queries x 16 lists 252 and 286.)
+        w.split_max = nprobe <= 4 ? 4 : nprobe <= 8 ? 2 : 1;
+        if (nq * nprobe / 32 > 1024) w.split_max = 1;      // (the 2,048 waves have a unit each)
+        if ((int64_t)w.split_max * units > 2 * active && 2 * active < 2048) w.split_max = (int)(2 * active / (units > 0 ? units : 1));
+        if (!rairs_mfma_reg_tables(v)) w.split_max = 1;
     }
     w.chunk_fill = take((size_t)w.log_chunks * 4);
     w.log_misc = take(64);
@@ -642,6 +651,12 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     const size_t surv_bytes = (size_t)nq * w.surv_cap * 8;
     w.s_scores = w.surv_buf = take(samp_bytes + hmin_bytes > surv_bytes ? samp_bytes + hmin_bytes : surv_bytes);
     w.hmin = hmin_bytes ? w.s_scores + samp_bytes : 0;
+    // The scan's tables (1,296 bytes a query at most: M <= 64) live from the selection of the probe lists to the
+    // end of the scan, the survivor buffers from there on.  With the sample on the matrix cores its scores and the
+    // minima may still be in use when the tables are made (on the other stream), else the minima are not.  That
+    // sample takes at most max(3,072, 10 bigK) bytes a query and the minima 2,048 then: all three together stay
+    // below the survivors' max(8,192, 64 bigK).
+    w.tables = w.s_scores + (grouped ? samp_bytes + align_up(hmin_bytes, 256) : 0);
     w.total = off;
     return w;
 }
@@ -930,7 +945,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     }
     MfmaScanArgs ma;
     memset(&ma, 0, sizeof(ma));
-    ma.lut = lut; ma.probe_ids = probe_ids; ma.bitmap = bitmap; ma.bmwords = w.bmwords;
+    ma.lut = lut; ma.tables = (const uint8_t *)(ws + w.tables); ma.probe_ids = probe_ids; ma.bitmap = bitmap; ma.bmwords = w.bmwords;
     ma.nprobe = nprobe; ma.refine_k = refine_k; ma.p_first = 1; ma.nq = n;
     ma.any_order = any_order ? 1 : 0;
     ma.lcount = (int32_t *)(ws + w.lcount); ma.loff = (int32_t *)(ws + w.loff);
@@ -946,20 +961,21 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
         ma.unit_parts = up >= 4 ? 4 : up >= 3 ? 3 : parts_total >= 16000 ? 2 : 1;
         // with the tables in LDS a whole workgroup shares a unit and reloads up to 128 KB of
         // tables for each: always the longest units
-        if (!(v.T == 8 || v.T == 24 || v.T == 32)) ma.unit_parts = 4;
+        if (!rairs_mfma_reg_tables(v)) ma.unit_parts = 4;
         // The last lists in single parts, so that the kernel's last units are small: as many lists
         // as hold about 1.3 units for each of the 2,048 waves, at most a third.  (1M x 128
         // workload, 8,200 two-part units, kernel: none 0.560 ms, last eighth 0.558, fifth 0.551,
         // third 0.542, half 0.546; a third of the 100M workload's 129,000 four-part units: 11.7 ms
         // against 11.1.)
         ma.unit_tail_from = v.nlist;
-        if (ma.unit_parts > 1 && (v.T == 8 || v.T == 24 || v.T == 32)) {
+        if (ma.unit_parts > 1 && rairs_mfma_reg_tables(v)) {
             const double units = (double)parts_total / ma.unit_parts;
             double f = units > 0 ? 1.3 * 2048 / units : 0.0;
             f = f > 1.0 / 3 ? 1.0 / 3 : f;
             ma.unit_tail_from = v.nlist - (int)(v.nlist * f);
         }
     }
+    ma.split_max = w.split_max;
     ma.next_task = (uint32_t *)(ws + w.next_task); ma.qlist = (int32_t *)(ws + w.qlist);
     ma.tau = (int32_t *)(ws + w.tau); ma.surv_cnt = (uint32_t *)(ws + w.surv_cnt);
     ma.surv_buf = (uint64_t *)(ws + w.surv_buf); ma.surv_cap = w.surv_cap;
@@ -985,6 +1001,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     uint16_t *s_scores = (uint16_t *)(ws + w.s_scores);
     if (overlap) {
         if ((rc = rairs_launch_group(v, ma, h->side))) return rc;
+        if (rairs_mfma_reg_tables(v) && (rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), h->side))) return rc;
         RAIRS_HIP(hipEventRecord(h->ev_group, h->side));
     }
     if (grouped && probed_on_side) {
@@ -1013,7 +1030,10 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
                                                (int32_t *)(ws + w.tau), ma.bound, s)))
         return rc;
     if (overlap) RAIRS_HIP(hipStreamWaitEvent(s, h->ev_group, 0));
-    else if ((rc = rairs_launch_group(v, ma, s))) return rc;
+    else {
+        if ((rc = rairs_launch_group(v, ma, s))) return rc;
+        if (rairs_mfma_reg_tables(v) && (rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), s))) return rc;
+    }
     if ((rc = rairs_launch_scan_mfma(v, ma, s, ev))) return rc;
     if ((rc = rairs_launch_select(v, ma, s))) return rc;
     // a query with more entries at or below its final bound than buffer and spill hold (thousands of

@@ -213,6 +213,7 @@ int rairs_launch_sample_scores(const IndexView &v, const uint8_t *lut, int sampl
 // list-major MFMA scan (scan_mfma.hip)
 struct MfmaScanArgs {
     const uint8_t *lut;
+    const uint8_t *tables;        // the same in the form of the scan with tables in registers (rairs_launch_scan_tables)
     const int32_t *probe_ids;
     const uint32_t *bitmap;
     int bmwords, nprobe, refine_k;
@@ -228,6 +229,7 @@ struct MfmaScanArgs {
     int32_t *unit_rec;            // [units][8] {list, tile, first segment, end segment, first query of the list in qlist, its queries, 0, 0}
     int unit_parts;               // parts per unit, 1..4
     int unit_tail_from;           // lists from this one on: single-part units (nlist: none)
+    int split_max;                // most waves that may share a unit (a chunk of the log for each)
     uint32_t *next_task;          // [1]
     const int32_t *tau;           // [nq] bound from the sample (0xFFFF: none); fixes the histogram range
     int32_t *bound;               // [nq] current bound, starts at tau, only decreases
@@ -249,7 +251,10 @@ struct MfmaScanArgs {
 };
 bool rairs_mfma_supported(const IndexView &v);
 bool rairs_mfma_reg_tables(const IndexView &v);    // the tile's tables fit the registers (sparse instruction)
-int64_t rairs_scan_log_waves(const IndexView &v, int64_t units);    // most waves that own log chunks at once, for a pass of at most `units` units
+int64_t rairs_scan_log_waves(const IndexView &v, int64_t units);    // half of the chunks that waves may hold, for a pass of at most `units` units
+// the lookup tables in the form that the register-table scan's matrix instructions take
+size_t rairs_scan_tables_bytes(const IndexView &v, int64_t nq);
+int rairs_launch_scan_tables(const IndexView &v, const uint8_t *lut, int64_t nq, uint8_t *tables, hipStream_t s);
 // grouping of the (query, probed list) pairs by list and the unit table, then the scan itself
 int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s);
 int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_t s, hipEvent_t *ev);

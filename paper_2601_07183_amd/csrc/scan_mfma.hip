@@ -3,19 +3,10 @@
 // Section 5.2 taken to its conclusion: a block is fetched once for 32 queries).
 //
 // score(query, item) = sum_m lut[query][m][code[item][m]] is a contraction of the lookup tables
-// with the one-hot expansion of the codes:  sum_m sum_c lut[q][m][c] * [code[item][m] == c].
-// A one-hot row of 16 has one non-zero, so the expansion is 2:4 sparse and the register-table
-// kernel uses the sparse matrix instruction: one v_smfmac_i32_32x32x64_i8 covers 32 items x 32
-// queries x 4 sub-quantizers (K = 4 x 16 codewords):
-//   A (rows = items):   lane (item, h) passes, compressed, positions [16h, 16h+16) and
-//                       [32+16h, 48+16h) of the 64 -- sub-quantizers 4t+h and 4t+2+h, the two
-//                       nibbles of one code byte: 16 kept values and 16 two-bit positions, looked
-//                       up per nibble in a 16-entry LDS table;
-//   B (cols = queries): lane (query, g) holds the 32 table bytes lut[q][4t+2g .. 4t+2g+1][0..15]
-//                       as signed bytes (value - 128; 128 * M is added back after the sum), kept
-//                       in registers for the whole tile.
-// The LDS-table kernel (any M) uses the dense v_mfma_i32_32x32x32_i8, two sub-quantizers per
-// instruction with both operands from LDS.
+// with a 0/1 expansion of the codes, which the register-table kernel gives to the sparse matrix
+// instruction v_smfmac_i32_32x32x64_i8 in a form that has nothing to look up (selectors, below).
+// The LDS-table kernel (any M) uses the dense v_mfma_i32_32x32x32_i8 on the one-hot expansion
+// (sum_c lut[q][m][c] * [code == c]), two sub-quantizers per instruction with both operands from LDS.
 // Integer arithmetic throughout, so the scores equal the plain 16-bit sums bit for bit.
 //
 // Work is cut into units (list L, tile of <= 32 queries probing L, run of parts of the list; a part
@@ -48,19 +39,23 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 
 // ---- grouping queries by list ----------------------------------------------------------------
 
-// Chunks of the survivor log that the scanning waves start with: `starters` waves (with the tables
-// in registers) or workgroups (tables in LDS, `waves_each` waves) begin on the units numbered by
-// their own index; each wave of those that get a unit owns the chunk of its index and, reserved,
-// the one at index + active waves.  The cursor for later chunks starts behind both.  (Handing out
-// the first chunks by a counter instead makes 2,048 waves hit one address as the kernel starts:
-// 20 us on a 0.56 ms kernel.)
-static __device__ __forceinline__ uint32_t log_active_waves(uint32_t nunits, uint32_t starters, uint32_t waves_each)
+// Where there are fewer units than waves, a unit's blocks are cut into a power of two of slices, a wave for each (as
+// many as the log has chunks for: split_max).
+static __device__ __forceinline__ uint32_t unit_slices(uint32_t nunits, uint32_t starters, uint32_t split_max)
 {
-    return (nunits < starters ? nunits : starters) * waves_each;
+    uint32_t s = 1;
+    while (2u * s <= split_max && nunits * 2u * s <= starters) s *= 2u;
+    return s;
 }
-static __device__ __forceinline__ uint32_t log_first_free(uint32_t nunits, uint32_t starters, uint32_t waves_each)
+// Chunks of the survivor log that the scanning waves start with: `starters` waves (with the tables
+// in registers) or workgroups (tables in LDS, `waves_each` waves) begin on the slices of units numbered by
+// their own index, and each wave of those that get one owns the chunk of its index.  The cursor for later
+// chunks starts behind them.  (Handing out the first chunks by a counter instead makes 2,048 waves hit
+// one address as the kernel starts: 20 us on a 0.56 ms kernel.)
+static __device__ __forceinline__ uint32_t log_first_free(uint32_t nunits, uint32_t starters, uint32_t waves_each, uint32_t split_max)
 {
-    return 2u * log_active_waves(nunits, starters, waves_each);
+    const uint32_t n = nunits * unit_slices(nunits, starters, split_max);
+    return (n < starters ? n : starters) * waves_each;
 }
 
 // The scanning waves start on the units numbered by their own index (a second one each at index +
@@ -131,7 +126,7 @@ __global__ __launch_bounds__(1024) void lm_prefix_kernel(IndexView v,
                                                          int32_t *loff, int32_t *lcursor,
                                                          int32_t *toff, int32_t *unit_list,
                                                          int unit_parts, int tail_from, int32_t *unit_rec,
-                                                         uint32_t *log_cursor, uint32_t starters, uint32_t waves_each)
+                                                         uint32_t *log_cursor, uint32_t starters, uint32_t waves_each, uint32_t split_max)
 {
     __shared__ int sc[1024], st[1024];
     // one workgroup on the critical path of the grouping, usually next to a kernel that fills the
@@ -170,7 +165,7 @@ __global__ __launch_bounds__(1024) void lm_prefix_kernel(IndexView v,
     if (tid == 1023) {
         loff[v.nlist] = sc[1023];
         toff[v.nlist] = st[1023];
-        *log_cursor = log_first_free((uint32_t)st[1023], starters, waves_each);
+        *log_cursor = log_first_free((uint32_t)st[1023], starters, waves_each, split_max);
     }
 }
 
@@ -275,7 +270,7 @@ __global__ __launch_bounds__(256) void lm_fill_lds_kernel(IndexView v, const int
                                                           int32_t *loff, int32_t *lcursor, int32_t *qlist,
                                                           int qb, int32_t *toff, int32_t *unit_list,
                                                           int unit_parts, int tail_from, int32_t *unit_rec,
-                                                          uint32_t *log_cursor, uint32_t starters, uint32_t waves_each)
+                                                          uint32_t *log_cursor, uint32_t starters, uint32_t waves_each, uint32_t split_max)
 {
     extern __shared__ int32_t lm_lds[];                // [nlist] ranks / run starts, [nlist + 1] offsets
     __shared__ int32_t wsum[4], total;
@@ -318,7 +313,7 @@ __global__ __launch_bounds__(256) void lm_fill_lds_kernel(IndexView v, const int
         const int nunits = total;
         if (ub == 0 && tid == 0) {
             toff[nlist] = nunits;
-            *log_cursor = log_first_free((uint32_t)nunits, starters, waves_each);
+            *log_cursor = log_first_free((uint32_t)nunits, starters, waves_each, split_max);
         }
         const int share = (nunits + LM_UNIT_WGS - 1) / LM_UNIT_WGS;
         const int e1 = (ub + 1) * share < nunits ? (ub + 1) * share : nunits;
@@ -369,25 +364,48 @@ __global__ __launch_bounds__(256) void lm_fill_lds_kernel(IndexView v, const int
 
 // ---- the scan ----------------------------------------------------------------------------------
 
-// Bin of a score: floor(score * mul / 2^32) with mul = floor(BINS 2^32 / (range + 1)), range >=
-// BINS, so that scores 0..range fall into bins 0..BINS-1 without a division on the hot path
-// (larger scores are put into the last bin by the caller).
+// Element at a 32-bit byte offset from a uniform base (one register of address per lane instead of two).
+// The offset is made opaque where it is used: widened outside of a loop it would be a pair of registers again.
+template <typename T>
+static __device__ __forceinline__ T *at32(T *base, uint32_t bytes)
+{
+    asm volatile("" : "+v"(bytes));
+    return (T *)((char *)base + bytes);
+}
+// The same value, but made anew where this stands: what is derived from it does not stay in registers
+// across the loops around it.
+static __device__ __forceinline__ int here(int x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// counter++ by the calling lane.  (Through an address per lane: where the compiler sees one address it adds up over
+// the lanes first and waits for the answer at once.)
+static __device__ __forceinline__ uint32_t take_next(uint32_t *counter) { return atomicAdd(at32(counter, 0u), 1u); }
+
+// Bin of a score: floor(score * mul / 2^32) with mul close to BINS 2^32 / (range + 1), range >= BINS, so
+// that scores 0 .. range fall into bins 0 .. BINS - 1 (larger scores, and whatever rounding puts beyond
+// the last bin, are put into it by the caller).
+static __device__ __forceinline__ uint32_t hist_range(uint32_t range)
+{
+    return range < (uint32_t)RAIRS_HIST_BINS ? (uint32_t)RAIRS_HIST_BINS : range;
+}
 static __device__ __forceinline__ uint32_t hist_mul(uint32_t range)
 {
-    const uint32_t r = range < (uint32_t)RAIRS_HIST_BINS ? (uint32_t)RAIRS_HIST_BINS : range;
-    return (uint32_t)(((unsigned long long)RAIRS_HIST_BINS << 32) / (uint64_t)(r + 1u));
+    return (uint32_t)((float)RAIRS_HIST_BINS * 4294967296.0f * __builtin_amdgcn_rcpf((float)(range + 1u)));
 }
 
 // Tightest bound the histogram of query `qid` proves: the histogram counts queue entries, so once
 // bins 0..b hold >= bigK of them nothing scoring above the top edge of bin b can be among the
 // bigK best.
-static __device__ __forceinline__ uint32_t histogram_bound(const MfmaScanArgs &a, int qid,
-                                                           uint32_t mul)
+static __device__ __forceinline__ uint32_t histogram_bound(const MfmaScanArgs &a, uint32_t qid,
+                                                           uint32_t range)
 {
-    const uint4 *hq = (const uint4 *)(a.hist + (size_t)qid * RAIRS_HIST_BINS);
+    const uint4 *hq = (const uint4 *)at32(a.hist, qid * (RAIRS_HIST_BINS * 4u));
     const uint32_t need = (uint32_t)a.refine_k;
     uint32_t cum = 0;
-    int b = RAIRS_HIST_BINS;
+    int b = 0;                                         // bins with fewer than bigK counted up to them: the first with enough
     // (16 bins in flight at a time: all 64 at once take 64 registers, which the scan loop around
     // this call then pays for with spills)
     constexpr int HB = 4;
@@ -397,41 +415,57 @@ static __device__ __forceinline__ uint32_t histogram_bound(const MfmaScanArgs &a
         for (int i = 0; i < HB; i++) h[i] = hq[i0 + i];
 #pragma unroll
         for (int i = 0; i < HB; i++) {
-            cum += h[i].x; b = (cum >= need && b == RAIRS_HIST_BINS) ? 4 * (i0 + i) : b;
-            cum += h[i].y; b = (cum >= need && b == RAIRS_HIST_BINS) ? 4 * (i0 + i) + 1 : b;
-            cum += h[i].z; b = (cum >= need && b == RAIRS_HIST_BINS) ? 4 * (i0 + i) + 2 : b;
-            cum += h[i].w; b = (cum >= need && b == RAIRS_HIST_BINS) ? 4 * (i0 + i) + 3 : b;
+            cum += h[i].x; b += cum < need ? 1 : 0;
+            cum += h[i].y; b += cum < need ? 1 : 0;
+            cum += h[i].z; b += cum < need ? 1 : 0;
+            cum += h[i].w; b += cum < need ? 1 : 0;
         }
     }
     if (b >= RAIRS_HIST_BINS - 1) return 0xFFFFu;      // the last bin also holds scores beyond the range
-    // largest score whose bin is <= b
-    const uint64_t edge = ((((uint64_t)(b + 1)) << 32) - 1ull) / (uint64_t)mul;
-    return edge < 0xFFFFull ? (uint32_t)edge : 0xFFFFu;
+    // A score of bin <= b is below (b + 1) 2^32 / mul.  The reciprocal, its two roundings and the
+    // truncation leave mul within 2^-21 of BINS 2^32 / (range + 1), which is at least 2^22, so that is less than
+    // x + 0.05, x = (b + 1) (range + 1) / BINS <= 65536, and the score at most floor(x + 4 / 64).
+    static_assert(RAIRS_HIST_BINS == 64, "the slack is in 64ths");
+    const uint32_t edge = ((uint32_t)(b + 1) * (range + 1u) + 4u) / RAIRS_HIST_BINS;
+    return edge < 0xFFFFu ? edge : 0xFFFFu;
 }
 
 // A passing (item, query) pair waits in a per-wave LDS queue until enough have gathered; then the
 // wave appends them to its current chunk of a global survivor log with plain stores, counts them
-// in the queries' histograms and, for some, lowers the query's bound.  Nothing on this path
-// waits for a returning atomic: the wave owns its chunk, and the next chunk's number is requested
-// long before it is needed (only waves with work own chunks, so the log of a small batch is
-// small).  Chunks of 2,048 entries: with 256 the scan kernel of the 1M x 128 workload took
+// in the queries' histograms and, for some, lowers the query's bound.  The wave owns its chunk and
+// takes a number for the next one when it is full (only waves with work own chunks, so the log of a
+// small batch is small).  That waits for an atomic's answer, once in 2,048 entries; asked for at an
+// earlier flush, the answer's register was copied, and so waited for together with the flush's stores, in
+// every round of survivors (6,000 queries, bigK = 400, lists of 3,800 items: 292 us instead of 253).  Chunks of 2,048 entries: with 256 the scan kernel of the 1M x 128 workload took
 // 0.610 ms instead of 0.558 (1,024 and more: the same) and the collect step, whose atomics go by
 // chunk and query, 49 us instead of 35.  Ids, tags and the duplicate rule are resolved afterwards,
 // in bulk, by collect_kernel and the select kernels.
-#define STAGE_CAP 128              // a multiple of 64 (a flush takes the queue in rows of 64); 192 and 256 measured slower
+#define STAGE_CAP 128              // of the LDS-table kernel; a multiple of 64 (a flush takes the queue in rows of 64)
 static_assert(STAGE_CAP % 64 == 0 && STAGE_CAP >= 128, "stage queue rows");
 #define LOG_CHUNK RAIRS_LOG_CHUNK
+static_assert((LOG_CHUNK & (LOG_CHUNK - 1)) == 0, "places in a chunk are taken by masking");
 #define LOG_COUNTED 0x80000000u    // bit 31 of a staged slot: the entry counts in the histogram
+struct StageEntry {
+    uint2 log;                     // the log entry: {block * 32 + item (| LOG_COUNTED), score << 16 | query of the pass}
+    uint32_t range, unused;        // of the query's histogram
+};
 struct StageQueue {
-    uint2 ent[STAGE_CAP];          // the log entry: {block * 32 + item (| LOG_COUNTED), score << 16 | query of the pass}
-    uint32_t hmul[STAGE_CAP];      // hist_mul of the query's score range
+    static constexpr int CAP = 256;
+    StageEntry ent[CAP + 64];        // the last 64 take what lanes without an entry write
+    __device__ __forceinline__ uint2 &log(int i) { return ent[i].log; }
+    __device__ __forceinline__ uint32_t &range(int i) { return ent[i].range; }
+};
+// the same for the kernel with the tables in LDS, where every KB counts
+struct SmallStageQueue {
+    static constexpr int CAP = STAGE_CAP;
+    uint2 log_s[STAGE_CAP];
+    uint32_t range_s[STAGE_CAP];
+    __device__ __forceinline__ uint2 &log(int i) { return log_s[i]; }
+    __device__ __forceinline__ uint32_t &range(int i) { return range_s[i]; }
 };
 
 struct LogCursor {
     uint32_t chunk, used;               // wave-uniform
-    uint32_t next_v;                    // lane 0: the chunk reserved for later (left in a vector
-                                        // register so that nobody waits for the atomic's answer
-                                        // before the chunk is needed)
 };
 
 // When a wave refreshes bounds: every `gap`-th flush.  The gap starts at 4, doubles (up to 16)
@@ -448,31 +482,35 @@ struct RefreshPace {
     uint32_t gap, since, turn;          // wave-uniform
 };
 
-static __device__ __forceinline__ void stage_flush(const MfmaScanArgs &a, StageQueue &sq, int n,
-                                                   int lane, LogCursor &lc, RefreshPace &rp)
+template <typename Queue>
+static __device__ __forceinline__ void stage_flush(const MfmaScanArgs &a, Queue &sq, int n,
+                                                   int lane0, LogCursor &lc, RefreshPace &rp)
 {
-    if (lc.used + (uint32_t)n > LOG_CHUNK) {
-        // close the chunk, move to the one reserved earlier, reserve another
-        if (lane == 0 && lc.chunk < (uint32_t)a.log_chunks) a.chunk_fill[lc.chunk] = lc.used;
-        lc.chunk = (uint32_t)__builtin_amdgcn_readfirstlane((int)lc.next_v);
-        lc.used = 0;
-        uint32_t nx = 0;
-        if (lane == 0) nx = atomicAdd(a.log_cursor, 1u);
-        lc.next_v = nx;
+    const int lane = here(lane0);
+    const uint32_t end = lc.used + (uint32_t)n;
+    uint32_t next = lc.chunk;
+    if (end > LOG_CHUNK) {
+        // the chunk fills up: the rest goes to another
+        if (lane == 0) {
+            if (lc.chunk < (uint32_t)a.log_chunks) a.chunk_fill[lc.chunk] = LOG_CHUNK;
+            next = take_next(a.log_cursor);
+        }
+        next = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
     }
-    const bool room = lc.chunk < (uint32_t)a.log_chunks;
+    const bool room = lc.chunk < (uint32_t)a.log_chunks && next < (uint32_t)a.log_chunks;
     if (!room && lane == 0) *a.log_overflow = 1u;      // every query is then redone exactly
 #pragma unroll
-    for (int u = 0; u < STAGE_CAP / 64; u++) {
+    for (int u = 0; u < Queue::CAP / 64; u++) {
         const int i = lane + 64 * u;
         if (i < n) {
-            const uint2 e = sq.ent[i];
+            const uint2 e = sq.log(i);
             const uint32_t qid = e.y & 0xFFFFu;
-            if (room) a.log[(size_t)lc.chunk * LOG_CHUNK + lc.used + i] = make_uint2(e.x & ~LOG_COUNTED, e.y);
+            const uint32_t at = lc.used + (uint32_t)i;
+            if (room) a.log[(size_t)(at < LOG_CHUNK ? lc.chunk : next) * LOG_CHUNK + (at & (LOG_CHUNK - 1u))] = make_uint2(e.x & ~LOG_COUNTED, e.y);
             if (e.x & LOG_COUNTED) {
                 // scores beyond the histogram's range share the last bin
-                const uint32_t bin = __umulhi(e.y >> 16, sq.hmul[i]);
-                atomicAdd(&a.hist[(size_t)qid * RAIRS_HIST_BINS + (bin < RAIRS_HIST_BINS - 1 ? bin : RAIRS_HIST_BINS - 1)], 1u);
+                const uint32_t bin = __umulhi(e.y >> 16, hist_mul(sq.range(i)));
+                atomicAdd(at32(a.hist, (qid * RAIRS_HIST_BINS + (bin < RAIRS_HIST_BINS - 1 ? bin : RAIRS_HIST_BINS - 1)) * 4u), 1u);
             }
         }
     }
@@ -483,25 +521,27 @@ static __device__ __forceinline__ void stage_flush(const MfmaScanArgs &a, StageQ
         rp.since = 0;
         bool lowered = false;
         if (lane < n && ((lane + rp.turn) & (REFRESH_LANES_MASK)) == 0) {
-            const int qid = (int)(sq.ent[lane].y & 0xFFFFu);
-            const int32_t cur = __hip_atomic_load(&a.bound[qid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t nb = histogram_bound(a, qid, sq.hmul[lane]);
+            const uint32_t qid = sq.log(lane).y & 0xFFFFu;
+            int32_t *bq = at32(a.bound, qid * 4u);
+            const int32_t cur = __hip_atomic_load(bq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t nb = histogram_bound(a, qid, sq.range(lane));
             if (nb < 0xFFFFu && (int32_t)nb < cur) {
-                atomicMin(&a.bound[qid], (int32_t)nb);
+                atomicMin(bq, (int32_t)nb);
                 lowered = true;
             }
         }
         rp.turn++;
         rp.gap = __ballot(lowered) != 0ull ? REFRESH_GAP_MIN : (rp.gap < REFRESH_GAP_MAX ? rp.gap * 2u : REFRESH_GAP_MAX);
     }
-    lc.used += (uint32_t)n;
+    lc.used = end > LOG_CHUNK ? end - LOG_CHUNK : end;
+    lc.chunk = next;
 }
 
 // The accumulators of a block start at -(th + 1), th the lane's threshold in the matrix core's
 // signed units, so a row passes (score <= th) exactly when its accumulator ends up negative, and
 // the mask of passing rows is the 16 sign bits: one funnel shift per row, no compare, no select.
 // Lanes that must not pass anything start at a large positive value instead.
-#define ACC_NEVER 0x3FFFFFFF
+#define ACC_NEVER 0x40000000        // (the bits of 2.0f, which an instruction can hold)
 static __device__ __forceinline__ uint32_t negative_rows(const v16i &acc)
 {
     uint32_t pm = 0;
@@ -510,17 +550,210 @@ static __device__ __forceinline__ uint32_t negative_rows(const v16i &acc)
     return pm;
 }
 
-// Kept values and positions of the compressed one-hot operand, by code: entry c of the first 16
-// is the 8 kept values (a one in the first slot of group c >> 2), entry 16 + c the 8 two-bit
-// positions (c & 3 in that slot) once as the low and once as the high half of the position word.
-static __device__ __forceinline__ void fill_sparse_tab(uint2 *tab)
+// Mask of the accumulator rows r whose item, 8 (r / 4) + r % 4 in a lane's own count, is below n.
+static __device__ __forceinline__ uint32_t rows_below(int n)
 {
-    if (threadIdx.x < 16) {
-        const int c = threadIdx.x;
-        const unsigned long long val = 1ull << (16 * (c >> 2));
-        const uint32_t pos = (uint32_t)(c & 3) << (4 * (c >> 2));
-        tab[c] = make_uint2((uint32_t)val, (uint32_t)(val >> 32));
-        tab[16 + c] = make_uint2(pos, pos << 16);
+    uint32_t rows = 0;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const int m = n - 8 * k < 0 ? 0 : n - 8 * k > 4 ? 4 : n - 8 * k;
+        rows |= ((1u << m) - 1u) << (4 * k);
+    }
+    return rows;
+}
+// ---- selectors: a code as five picks of one out of four ------------------------------------------
+//
+// The sparse instruction takes, per group of four positions, two kept values and their positions
+// 0 .. 3.  With the kept values constant (a one in one of the two slots, a zero in the other) a group
+// picks one of its four table entries by position.  A code c = 4 h + l becomes five such picks:
+//   group g < 4:  entry l of T[4 g .. 4 g + 3] if h == g, else its entry f_g (f = 3, 0, 0, 0),
+//   group 4:      entry h of {T[f_0], T[4 + f_1], T[8 + f_2], T[12 + f_3]},
+// whose sum is T[c] + sum_g T[4 g + f_g]: the score plus a number that depends on the query alone, which
+// goes into the threshold.  (Four groups cannot do: every pattern takes one entry of each group, so the
+// 16 x 16 matrix of picks has rank 13.)  The picks of all codes of a dword are bitwise functions of
+// it: with X the l and Y the h of sixteen codes as 2-bit fields (eight codes in the fields of one
+// slot, eight in those of the other), R1 and R0 the bits of h doubled, the five position words are
+//   X | R1 | R0,  X & R0 & ~R1,  X & R1 & ~R0,  X & R1 & R0,  Y
+// -- a dozen vector instructions for ten matrix instructions, and no table to look anything up in.
+// Position words: nibble n of a lane's word belongs to its group n, low two bits the first slot.
+#define SEL_F0 3                    // f_0; f_1, f_2 and f_3 are 0
+#define SEL_FIRST 0x00010001        // kept values: the pick is the first slot's ...
+#define SEL_SECOND 0x01000100       // ... or the second one's
+// bit by bit m ? a : b
+static __device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
+
+static __device__ __forceinline__ void select_words(uint32_t X, uint32_t Y, uint32_t R1, uint32_t R0, uint32_t (&w)[5])
+{
+    w[0] = X | R1 | R0;
+    w[1] = X & R0 & ~R1;
+    w[2] = X & R1 & ~R0;
+    w[3] = X & R1 & R0;
+    w[4] = Y;
+}
+// sixteen codes of a lane: those of dword a in the first slots, those of dword b in the second ones
+static __device__ __forceinline__ void select_words_pair(uint32_t a, uint32_t b, uint32_t (&w)[5])
+{
+    const uint32_t X = bit_select(0x33333333u, a, b << 2), Y = bit_select(0x33333333u, a >> 2, b);
+    select_words(X, Y, bit_select(0x55555555u, Y >> 1, Y), bit_select(0x55555555u, Y, Y << 1), w);
+}
+// eight codes, first slots (the second ones hold anything)
+static __device__ __forceinline__ void select_words_one(uint32_t a, uint32_t (&w)[5])
+{
+    const uint32_t Y = a >> 2;
+    select_words(a, Y, bit_select(0x55555555u, a >> 3, Y), bit_select(0x55555555u, Y, a >> 1), w);
+}
+
+// An instruction (v_smfmac_i32_32x32x64_i8: 32 items x 32 queries x 16 groups) takes one group of eight codes
+// of either parity: 5 nd of them a block, instruction 5 w + g group g of the codes of dword w.  Lane (item,
+// parity) gives positions for its eight groups; the instruction's K order, checked entry by entry, takes groups
+// 0 - 3 of parity p from registers 4 p .. + 3 of the table operand's lower half wave, groups 4 - 7 from its
+// upper one.  (The one-hot expansion took 4 nd instructions, each fed by four LDS look-ups and five vector
+// instructions.)
+
+// The table operand straight from the bytes T (the sample's kernel): lane (query, half) holds, for dword w,
+// sub-quantizers 16 w + 8 half .. + 7, even ones in the first four registers, four table entries (signed:
+// value - 128) to a register.  Sub-quantizers from M on are zero.  Returns what a contraction is above the
+// score (the same number in both lanes of a query).
+template <int ND>
+static __device__ __forceinline__ int load_byte_tables(const uint8_t *lut, uint32_t qid, int M, int half, v8i (&B)[5 * ND])
+{
+    const uint8_t *lq = lut + (size_t)qid * (size_t)(M * 16) + half * 128;
+    int extra = 0;                                     // sum of the (signed) entries that the groups not meant pick
+#pragma unroll
+    for (int w = 0; w < ND; w++) {
+        v4i x[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) x[k] = *(const v4i *)(lq + w * 256 + k * 16) ^ (int)0x80808080;
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const int r = (k >> 1) + 4 * (k & 1);
+#pragma unroll
+            for (int g = 0; g < 4; g++) B[5 * w + g][r] = x[k][g];
+            // bytes f_0 of group 0, 0 of groups 1, 2, 3
+            const int e = (int)(__builtin_amdgcn_perm((uint32_t)x[k].y, (uint32_t)x[k].x, 0x0C0C0400u + SEL_F0) |
+                                __builtin_amdgcn_perm((uint32_t)x[k].w, (uint32_t)x[k].z, 0x04000C0Cu));
+            B[5 * w + 4][r] = e;
+            extra = __builtin_amdgcn_sdot4(e, 0x01010101, extra, false);
+        }
+        __builtin_amdgcn_sched_barrier(0);             // (32 registers of loads in flight at a time, not 32 ND)
+    }
+    extra += __shfl_xor(extra, 32);
+    // a contraction is the sum over the sub-quantizers of T[c] + sum_g T[4 g + f_g], less 5 * 128; extra is that
+    // of the T[4 g + f_g], less 4 * 128
+    return extra - 128 * M;
+}
+
+// The scan's own form of the tables, made once per query.  A group's entries may be shifted by a number of
+// its own, so the entry that the groups not meant pick is made zero wherever the other three fit into a
+// signed byte then: four of five picks are zeros.  What a matrix instruction costs is power: with random
+// table bytes picked everywhere the chip holds 1.5 GHz (21.5 ns each, every SIMD at it), with four of five
+// picks zero 2.05 GHz (16.0 ns; the one-hot expansion 1.6 GHz, 20.6 ns).
+// Per query scan_tables_stride bytes: for dword w and half the five registers of eight words each that
+// load_byte_tables describes, then what a contraction is above the score.
+static __host__ __device__ __forceinline__ int scan_tables_stride(int nd) { return nd * 320 + 16; }
+
+// One wave per query, a lane per sub-quantizer.
+__global__ __launch_bounds__(WG) void scan_tables_kernel(const uint8_t *__restrict__ lut, int M, int nd, int64_t nq,
+                                                         uint8_t *__restrict__ tables)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t q = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
+    if (q >= nq) return;
+    const int stride = scan_tables_stride(nd);
+    uint32_t *out = (uint32_t *)(tables + (size_t)q * stride);
+    int above = 0;
+    for (int m = lane; m < 16 * nd; m += 64) {
+        uint32_t e[5] = {0u, 0u, 0u, 0u, 0u};          // (sub-quantizers from M on: zeros)
+        if (m < M) {
+            const v4i x = *(const v4i *)(lut + (size_t)q * (size_t)(M * 16) + (size_t)m * 16);
+            above -= 128;
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                int t[4];
+#pragma unroll
+                for (int l = 0; l < 4; l++) t[l] = (int)(((uint32_t)x[g] >> (8 * l)) & 255u);
+                const int lo = min(min(t[0], t[1]), min(t[2], t[3])), hi = max(max(t[0], t[1]), max(t[2], t[3]));
+                const int tf = t[g == 0 ? SEL_F0 : 0];
+                const int shift = min(max(tf, hi - 127), lo + 128);
+                above += tf - shift;
+#pragma unroll
+                for (int l = 0; l < 4; l++) e[g] |= ((uint32_t)(t[l] - shift) & 255u) << (8 * l);
+                e[4] |= ((uint32_t)(tf - 128) & 255u) << (8 * g);
+            }
+        }
+        const int k = m & 7, r = (k >> 1) + 4 * (k & 1);
+        uint32_t *p = out + (m >> 3) * 40 + r;
+#pragma unroll
+        for (int g = 0; g < 5; g++) p[8 * g] = e[g];
+    }
+    const uint32_t sum = wave_sum_u32((uint32_t)above);
+    if (lane == 0) out[nd * 80] = sum;
+}
+
+template <int ND>
+static __device__ __forceinline__ void load_scan_tables(const uint8_t *tables, uint32_t qid, int half, v8i (&B)[5 * ND])
+{
+    const uint32_t row = qid * (uint32_t)scan_tables_stride(ND);        // < 2^29: a pass has at most 65,536 queries
+    const char *p = (const char *)at32(tables, row + (uint32_t)half * 160u);
+#pragma unroll
+    for (int t = 0; t < 5 * ND; t++) {
+        const v4i x = *(const v4i *)(p + (t / 5 * 320 + t % 5 * 32)), y = *(const v4i *)(p + (t / 5 * 320 + t % 5 * 32 + 16));
+        B[t] = (v8i){x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    }
+}
+
+// acc += the contraction of a block's codes with the tables, in two parts.
+template <int ND>
+struct Contraction {
+    static constexpr int FRONT = ND >= 3 ? 10 : 5, BACK = 5 * ND - FRONT;      // matrix instructions
+    uint32_t s[2][5];                                  // position words of the two parts
+    __device__ __forceinline__ void front_words(const uint32_t (&c)[ND])
+    {
+        if (ND > 1) select_words_pair(c[0], c[ND > 1 ? 1 : 0], s[0]);
+        else select_words_one(c[0], s[0]);
+    }
+    __device__ __forceinline__ void back_words(const uint32_t (&c)[ND])
+    {
+        if (ND == 3) select_words_one(c[ND - 1], s[1]);
+        if (ND == 4) select_words_pair(c[ND > 2 ? 2 : 0], c[ND - 1], s[1]);
+    }
+    __device__ __forceinline__ void front(const v8i (&B)[5 * ND], v16i &acc)
+    {
+        five<0>(s[0], B, acc);
+        if (ND >= 3) five<1>(s[0], B, acc);
+    }
+    __device__ __forceinline__ void back(const v8i (&B)[5 * ND], v16i &acc)
+    {
+        if (ND == 2) five<(ND == 2 ? 1 : 0)>(s[0], B, acc);
+        if (ND >= 3) five<(ND >= 3 ? 2 : 0)>(s[1], B, acc);
+        if (ND == 4) five<(ND == 4 ? 3 : 0)>(s[1], B, acc);
+    }
+    template <int W>
+    static __device__ __forceinline__ void five(const uint32_t (&w)[5], const v8i (&B)[5 * ND], v16i &acc)
+    {
+        constexpr int kept = W & 1 ? SEL_SECOND : SEL_FIRST;
+        const v4i slot = {kept, kept, kept, kept};
+#pragma unroll
+        for (int g = 0; g < 5; g++) acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(slot, B[5 * W + g], acc, (int)w[g], 0, 0);
+    }
+};
+template <int ND>
+static __device__ __forceinline__ void contract_block(const uint32_t (&c)[ND], const v8i (&B)[5 * ND], v16i &acc)
+{
+    Contraction<ND> k;
+    k.front_words(c);
+    k.front(B, acc);
+    k.back_words(c);
+    k.back(B, acc);
+}
+// Lets the instruction scheduler put N vector instructions behind each of M matrix instructions.
+template <int M, int N>
+static __device__ __forceinline__ void interleave()
+{
+#pragma unroll
+    for (int i = 0; i < M; i++) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, N, 0);
     }
 }
 
@@ -544,35 +777,32 @@ static __device__ __forceinline__ int select_row(const v16i &acc, int r)
     return (s2b & m3) | (s2a & ~m3);
 }
 
-template <int T>
+// Read-only words at a wave-uniform address, by scalar loads.
+template <typename T>
+using scalar_ptr = const __attribute__((address_space(4))) T *;
+template <typename T>
+static __device__ __forceinline__ scalar_ptr<T> as_scalar(const T *p) { return (scalar_ptr<T>)(uintptr_t)p; }
+
+// What bounds it: the matrix cores' power (2 waves a SIMD; see scan_tables_kernel) and the survivors' vector
+// instructions, which run beside them a block behind.  Before (one-hot rows looked up in LDS, survivors after
+// each block): 1M x 128, M = 64, 10,000 queries, 23 probes: 695 us, now 645; 2,999 queries, bigK = 400: 515, 460;
+// 1M x 96, M = 48: 430, 400; 100 probes of 16,384 lists: 3.96 ms, 3.75.
+// ND: code dwords of an item and parity (M <= 16 ND).  SLICED: units may be cut into slices (compiled in where they
+// never are, that costs 3 % of the 1M x 128 workload's kernel).
+template <int ND, bool SLICED>
 __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanArgs a)
 {
-    constexpr int ND = (T + 7) / 8;
-    constexpr int M = 2 * T;
-    constexpr int TS = T / 2;                          // sparse matrix instructions per block
-    static_assert(T % 2 == 0, "a sparse instruction takes four sub-quantizers");
     __shared__ StageQueue stage[WG / 64];
-    // A code byte holds the codes (c1, c2) of two sub-quantizers of one instruction; their one-hot
-    // rows of 16 + 16 zeros and ones are 2:4 sparse, so the matrix core takes them compressed:
-    // per group of four positions two kept values and their 2-bit positions, looked up by code.
-    __shared__ uint2 sparse_tab[32];
-    fill_sparse_tab(sparse_tab);
-    __syncthreads();
-    const int lane = threadIdx.x & 63, g = lane >> 5, j = lane & 31;
-    StageQueue &sq = stage[threadIdx.x >> 6];
-    const int bias = 128 * M;
-
-    v8i B[TS];
-#pragma unroll
-    for (int t = 0; t < TS; t++) B[t] = (v8i){0, 0, 0, 0, 0, 0, 0, 0};
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    StageQueue &sq = stage[wave];
     int nstaged = 0;                                   // wave-uniform fill of the stage queue
-    const uint32_t nunits = (uint32_t)a.toff[v.nlist];
+    const uint32_t nunits = (uint32_t)as_scalar(a.toff)[v.nlist];
     if (nunits == 0u) return;                          // nothing was written: all chunk fills stay 0
-    // first unit and first two log chunks by wave index; the counters start behind them
-    const uint32_t gwave = blockIdx.x * (WG / 64) + (threadIdx.x >> 6), nwaves = gridDim.x * (WG / 64);
+    // first unit and first log chunk by wave index; the counters start behind them
+    const uint32_t gwave = blockIdx.x * (WG / 64) + (uint32_t)wave, nwaves = gridDim.x * (WG / 64);
     LogCursor lc;
     lc.chunk = gwave;                                  // (a wave without a unit never writes)
-    lc.next_v = gwave + log_active_waves(nunits, nwaves, 1u);
     lc.used = 0;
     RefreshPace pace = {REFRESH_GAP_MIN, REFRESH_GAP_MIN - 1u, 0u};
 #define FLUSH_STAGE()                                                   \
@@ -581,179 +811,227 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
         nstaged = 0;                                                    \
     } while (0)
 
+    // Unit u below is slice u % slices of unit u / slices.
+    const uint32_t slices = SLICED ? unit_slices(nunits, nwaves, (uint32_t)a.split_max) : 1u, nslices = nunits * slices;
+    const uint32_t slice_shift = (uint32_t)__builtin_ctz(slices);
     // A wave works on unit u, already knows the one after it (u_next) and asks the counter for
     // the one after that: so the record of the next unit can be fetched a whole unit ahead and a
-    // unit starts with its list, tile and segments in registers instead of a chain of look-ups.
+    // unit starts with its queries and segments in registers instead of a chain of look-ups.
+    // A flush costs much the same for one row of 64 entries and for three; but what waits in the queues is not
+    // counted, so bounds fall later, and with few units a wave or a small bigK so many entries gather above the
+    // final bound that buffers overflow.  (1M x 128, 2,999 queries, bigK = 400: 514 us with one row, 473 with two, 460 with
+    // three; 10,000, 100, 1,024 lists of 24 blocks: 302, 280, 280; 3,000, 40, 97 lists of 18: 97, 94, 96, but
+    // queries are redone for 20 us more.)
+    const int flush_above = a.refine_k >= 256 ? 192 : nunits >= 3u * nwaves ? 128 : 64;
     uint32_t u = gwave, u_next = gwave + nwaves;       // the counter starts behind both
-    int rec = u < nunits ? a.unit_rec[(size_t)u * UNIT_REC_WORDS + (lane & 7)] : 0;
-    while (u < nunits) {                               // every wave leaves: the counter only grows
-        uint32_t u_next2 = 0;
-        if (lane == 0) u_next2 = atomicAdd(a.next_task, 1u);
-        const int tile = __builtin_amdgcn_readlane(rec, 1);
-        const int seg0 = __builtin_amdgcn_readlane(rec, 2), seg1 = __builtin_amdgcn_readlane(rec, 3);
-        const int qbase = __builtin_amdgcn_readlane(rec, 4), qn = __builtin_amdgcn_readlane(rec, 5);
-        rec = a.unit_rec[(size_t)(u_next < nunits ? u_next : u) * UNIT_REC_WORDS + (lane & 7)];
+    auto record = [&](uint32_t i) {
+        const scalar_ptr<int32_t> p = as_scalar(a.unit_rec) + (size_t)(i >> slice_shift) * UNIT_REC_WORDS;
+        return make_int4(p[4] + 32 * p[1], p[5] - 32 * p[1], p[2], p[3]);      // {first query of the tile, queries from there on, segments}
+    };
+    // ... and the query of this lane's column there (an absent column takes query 0's tables and never passes), the
+    // range of its histogram, and what its contractions are above its scores
+    struct Column {
         int qid;
-        uint32_t hmul;
-        {
-            // the tile: query of this lane's column and its tables
-            const int qi = tile * 32 + j;
-            qid = qi < qn ? a.qlist[qbase + qi] : -1;
-            hmul = hist_mul(qid >= 0 ? (uint32_t)a.tau[qid] : 0u);
-            // instruction t takes sub-quantizers 4t .. 4t+3; this lane's half of its 64 positions
-            // is the 16 + 16 table entries of sub-quantizers 4t + 2g and 4t + 2g + 1
-            const uint8_t *lq = a.lut + (size_t)(qid >= 0 ? qid : 0) * (M * 16) + g * 32;
-            // every lane loads (an absent column reads query 0's rows and masks them to zero): a
-            // conditional load would be waited for one by one
-            const int keep = qid >= 0 ? -1 : 0;
-            const v4i flip = {(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
-            const v4i keep4 = {keep, keep, keep, keep};
-#pragma unroll
-            for (int t = 0; t < TS; t++) {
-                const v4i x = (*(const v4i *)(lq + t * 64) ^ flip) & keep4;
-                const v4i y = (*(const v4i *)(lq + t * 64 + 16) ^ flip) & keep4;
-                B[t] = (v8i){x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-            }
+        uint32_t range;
+        int above;
+    };
+    auto tile_query = [&](const int4 &r) { const int j = here(lane) & 31; return j < r.y ? *at32(a.qlist + r.x, (uint32_t)j * 4u) : -1; };
+    auto query_facts = [&](Column &c) {
+        const uint32_t q = (uint32_t)(c.qid >= 0 ? c.qid : 0);
+        c.range = hist_range((uint32_t)*at32(a.tau, q * 4u));
+        c.above = *(const int *)at32(a.tables, q * (uint32_t)scan_tables_stride(ND) + (uint32_t)(ND * 320));
+    };
+    int4 rec = record(u < nslices ? u : 0u);
+    Column next;
+    next.qid = tile_query(rec);
+    query_facts(next);
+    while (u < nslices) {                              // every wave leaves: the counter only grows
+        uint32_t u_next2 = 0;
+        if (lane == 0) u_next2 = take_next(a.next_task);
+        int seg0 = rec.z, first = 0, left = INT_MAX;   // the slice: from block `first` of run seg0 on, `left` blocks
+        const int seg1 = rec.w;
+        const int qid = next.qid, above = next.above;
+        const uint32_t range = next.range;
+        rec = record(u_next < nslices ? u_next : u);
+        next.qid = tile_query(rec);
+        // run entries go two ahead and the owner's bitmap word one ahead, so that neither is waited for at
+        // the head of a run
+        auto segment = [&](int i) {
+            const scalar_ptr<SegEntry> p = as_scalar(v.segs) + i;
+            SegEntry e;
+            e.blk_begin = p->blk_begin; e.nblk = p->nblk; e.misc_from = p->misc_from; e.owner = p->owner; e.tail_valid = p->tail_valid;
+            return e;
+        };
+        if (slices > 1u) {                             // uniform
+            int n = 0;
+            for (int i = seg0; i < seg1; i++) n += as_scalar(v.segs)[i].nblk;
+            const int s = (int)(u & (slices - 1u));
+            first = (n * s) >> slice_shift;
+            left = ((n * (s + 1)) >> slice_shift) - first;
+            if (left > 0)
+                while (first >= as_scalar(v.segs)[seg0].nblk) first -= as_scalar(v.segs)[seg0++].nblk;
         }
+        if (left > 0) {
+        const int unit_lane = here(lane);
+        const uint32_t q0 = (uint32_t)(qid >= 0 ? qid : 0);
+        v8i B[5 * ND];
+        load_scan_tables<ND>(a.tables, q0, unit_lane >> 5, B);
+        query_facts(next);
         // the query's bound: other waves keep lowering it, so it is looked up again during the
         // run, ahead of the block that uses it (a stale bound is only looser)
         // per-lane addresses stay 32-bit offsets from uniform bases (a 64-bit pointer per lane
         // costs two of the registers this kernel is short of)
-        const uint32_t q0 = (uint32_t)(qid >= 0 ? qid : 0);
         const uint32_t bm0 = q0 * (uint32_t)a.bmwords;   // < 2^27: a pass has at most 65,536 queries of at most 2,048 words
-        int bound_next = __hip_atomic_load(a.bound + q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        // segment entries run two ahead and the owner's bitmap word one ahead, so that neither
-        // is waited for at the head of a segment
-        SegEntry se = v.segs[seg0];
-        SegEntry sen = v.segs[seg0 + 1 < seg1 ? seg0 + 1 : seg0];
-        uint32_t owner_bits = a.bitmap[bm0 + (uint32_t)(se.owner >= 0 ? se.owner >> 5 : 0)];
-        const uint32_t *cp = v.codes + (size_t)se.blk_begin * ND * 64;      // wave-uniform
+        int bound_next = __hip_atomic_load(at32(a.bound, q0 * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        // Codes and masks {countable slots, slots in use} of a block are fetched a block before they are
+        // scored: the fetches walk through the unit's runs on their own (and stay on its last block).  (Two or
+        // three blocks ahead: no faster.)
+        int fseg = seg0;
+        SegEntry fs = segment(seg0);
+        int fblk = fs.blk_begin + first, fend = fs.blk_begin + fs.nblk;
+        fs = segment(seg0 + 1 < seg1 ? seg0 + 1 : seg0);       // the run behind the one that is being fetched
         uint32_t cn[ND];
+        uint2 cmn;
+        auto fetch = [&]() {
+            const char *p = (const char *)at32(v.codes + (size_t)fblk * ND * 64, (uint32_t)lane * 4u);    // (a uniform base)
 #pragma unroll
-        for (int w = 0; w < ND; w++) cn[w] = cp[w * 64 + lane];
-        // {countable slots, slots in use} of the block, fetched with its codes
-        uint2 cmn = v.bmask[se.blk_begin];
-        uint32_t scored = 0;                           // items this lane's query was scored against in this unit
-        for (int seg = seg0; seg < seg1; seg++) {
-            const bool has_next = seg + 1 < seg1;
-            const SegEntry sen2 = v.segs[seg + 2 < seg1 ? seg + 2 : seg1 - 1];
-            const uint32_t ob_next = a.bitmap[bm0 + (uint32_t)(sen.owner >= 0 ? sen.owner >> 5 : 0)];
-            const uint32_t *cpn = v.codes + (size_t)sen.blk_begin * ND * 64;   // wave-uniform
-            // cell (owner, L) is scored through list `owner` for queries that probe it
-            const bool live = qid >= 0 && !(se.owner >= 0 && ((owner_bits >> (se.owner & 31)) & 1u));
-            if (__ballot(live) == 0ull) {
-                // nobody needs this run; keep the prefetch chain going
-                if (has_next) {
-#pragma unroll
-                    for (int w = 0; w < ND; w++) cn[w] = cpn[w * 64 + lane];
-                    cmn = v.bmask[sen.blk_begin];
-                }
-            } else {
-                uint32_t seg_items = 0;                // wave-uniform: slots in use of the blocks contracted
-                for (int b = 0; b < se.nblk; b++) {
-                    uint32_t c[ND];
-#pragma unroll
-                    for (int w = 0; w < ND; w++) c[w] = cn[w];
-                    const uint32_t cmask = cmn.x;
-                    seg_items += (uint32_t)__popc(cmn.y);
-                    // the accumulators start at -(threshold + 1): a row passes iff it ends up negative
-                    const int negth = live ? -(bound_next - bias + 1) : ACC_NEVER;
-                    // (every fourth block is often enough: the bound moves rarely)
-                    if ((b & 3) == 3) bound_next = __hip_atomic_load(a.bound + q0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    if (b + 1 < se.nblk) {             // fetch the next block while this one is scored
-#pragma unroll
-                        for (int w = 0; w < ND; w++) cn[w] = cp[(size_t)(b + 1) * ND * 64 + w * 64 + lane];
-                        cmn = v.bmask[se.blk_begin + b + 1];
-                    } else if (has_next) {             // ... or the first block of the next run
-#pragma unroll
-                        for (int w = 0; w < ND; w++) cn[w] = cpn[w * 64 + lane];
-                        cmn = v.bmask[sen.blk_begin];
-                    }
-                    // (a copy the compiler cannot see through: the accumulators' start value must
-                    // not stay tied to the register that the survivor path reads later, or the
-                    // whole 16-register tuple is built elsewhere and moved)
-                    int acc0 = negth;
-                    asm volatile("" : "+v"(acc0));
-                    v16i acc;
-#pragma unroll
-                    for (int r = 0; r < 16; r++) acc[r] = acc0;
-                    // The table reads of an instruction (values, positions) go out two
-                    // instructions ahead of it, so that an LDS round trip hides behind matrix
-                    // work; the scheduling fences keep the compiler from moving them either way
-                    // (all at the front costs 80 registers, none ahead stalls every instruction).
-#define CODE_LO(t_) ((c[(t_) >> 2] >> (8 * ((t_) & 3))) & 15u)
-#define CODE_HI(t_) ((c[(t_) >> 2] >> (8 * ((t_) & 3) + 4)) & 15u)
-#define LOAD_A(t_)                                                                        \
-    do {                                                                                  \
-        const uint2 *e1_ = &sparse_tab[CODE_LO(t_)], *e2_ = &sparse_tab[CODE_HI(t_)];      \
-        v1[t_] = e1_[0]; v2[t_] = e2_[0];                                                 \
-        p1[t_] = e1_[16].x; p2[t_] = e2_[16].y;                                           \
-    } while (0)
-                    // raw table words; they are put together where they are used, not where
-                    // they are loaded, so that nothing waits for a load in its own stage
-                    uint2 v1[TS], v2[TS];
-                    uint32_t p1[TS], p2[TS];
-                    LOAD_A(0);
-                    if (TS > 1) LOAD_A(1);
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int t = 0; t < TS; t++) {
-                        const v4i av = {(int)v1[t].x, (int)v1[t].y, (int)v2[t].x, (int)v2[t].y};
-                        acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(av, B[t], acc, (int)(p1[t] | p2[t]), 0, 0);
-                        if (t + 2 < TS) LOAD_A(t + 2);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-#undef LOAD_A
-#undef CODE_LO
-#undef CODE_HI
-                    // acc[r]: item row 8*(r/4) + 4*g + (r%4), query column j
-                    uint32_t pm = negative_rows(acc);     // rows of this lane that pass
-                    if (__ballot(pm != 0u) != 0ull) {
-                        const uint32_t slot0 = (uint32_t)(se.blk_begin + b) * 32u + 4u * g;
-                        if (b == se.nblk - 1 && se.tail_valid < 32) {
-                            // the list's last block: drop rows whose slot holds no item
-#pragma unroll
-                            for (int r = 0; r < 16; r++)
-                                if (8 * (r >> 2) + 4 * g + (r & 3) >= se.tail_valid) pm &= ~(1u << r);
-                        }
-                        for (;;) {
-                            const bool has = pm != 0u;
-                            const unsigned long long mask = __ballot(has);
-                            if (mask == 0ull) break;
-                            // every lane selects (lanes without a row select row 0 and drop it)
-                            const int r = has ? __builtin_ctz(pm) : 0;
-                            pm &= pm - 1u;
-                            const int sc = select_row(acc, r) - negth;    // the row's sum, in the matrix core's units
-                            if (has) {
-                                const int pos = nstaged + lanes_below(mask);
-                                const uint32_t item = 8u * (uint32_t)(r >> 2) + (uint32_t)(r & 3);   // + 4 g
-                                sq.ent[pos] = make_uint2((slot0 + item) | (((cmask >> (item + 4u * g)) & 1u) << 31),
-                                                         ((uint32_t)(sc + bias) << 16) | (uint32_t)qid);
-                                sq.hmul[pos] = hmul;
-                            }
-                            nstaged += __popcll(mask);
-                            if (nstaged > STAGE_CAP - 64) {
-                                FLUSH_STAGE();
-                            }
-                        }
-                    }
-                }
-                // the distance computations of this run (Section 6.1's DCO): every slot in use of
-                // every block that was contracted, for each query the run was live for
-                scored += live ? seg_items : 0u;
+            for (int w = 0; w < ND; w++) cn[w] = *(const uint32_t *)(p + w * 256);
+            const scalar_ptr<uint2> m = as_scalar(v.bmask) + fblk;
+            cmn = make_uint2(m->x, m->y);
+            if (fblk + 1 < fend) fblk++;
+            else if (fseg + 1 < seg1) {
+                fseg++;
+                fblk = fs.blk_begin;
+                fend = fblk + fs.nblk;
+                fs = segment(fseg + 1 < seg1 ? fseg + 1 : fseg);
             }
+        };
+        fetch();
+        // The blocks in turn.  A block's survivors are looked for while the next one is contracted: two sets of
+        // accumulators, and with each set what its survivors need to know of the block.
+        struct Scored {
+            v16i acc;                                  // acc[r]: item row 8 (r / 4) + 4 half + r % 4, query column j
+            int negth;                                 // what the accumulators started at
+            uint32_t rows;                             // this lane's rows whose slots can hold an item
+            int blk;                                   // wave-uniform
+            uint32_t cmask;
+        };
+        int seg = seg0, b = first;
+        SegEntry se = segment(seg0), sen = segment(seg0 + 1 < seg1 ? seg0 + 1 : seg0);
+        auto owner_word = [&](const SegEntry &e) { return *at32(a.bitmap, (bm0 + (uint32_t)(e.owner >= 0 ? e.owner >> 5 : 0)) * 4u); };
+        uint32_t owner_bits = owner_word(se);          // of the run to be entered
+        uint32_t scored = 0, seg_items = 0;            // items this lane's query was scored against in this unit; slots in use of the run's blocks
+        bool live = false;
+        int negth = ACC_NEVER;
+        auto enter_run = [&]() {
+            // cell (owner, L) is scored through list `owner` for queries that probe it
+            live = qid >= 0 && !(se.owner >= 0 && ((owner_bits >> (se.owner & 31)) & 1u));
+            // (the next run's word into the same register: into another one, it is copied and waited for here)
+            __builtin_amdgcn_sched_barrier(0);
+            owner_bits = owner_word(sen);
+            negth = ACC_NEVER;
+            seg_items = 0;
+        };
+        // the block behind the present one, if the unit has one
+        auto advance = [&]() __attribute__((always_inline)) {
+            if (--left > 0 && ++b < se.nblk) return true;
+            // the distance computations of this run (Section 6.1's DCO): every slot in use of every block
+            // that was contracted, for each query the run was live for
+            scored += live ? seg_items : 0u;
+            if (left == 0 || ++seg >= seg1) return false;
             se = sen;
-            sen = sen2;
-            owner_bits = ob_next;
-            cp = cpn;
+            sen = segment(seg + 1 < seg1 ? seg + 1 : seg);
+            b = first = 0;
+            enter_run();
+            return true;
+        };
+        // one survivor of every lane that has any (pm: its rows that pass), no branches
+        auto stage_round = [&](const Scored &x, uint32_t &pm, int lane_) __attribute__((always_inline)) {
+            const int half = lane_ >> 5;
+            const unsigned long long mask = __builtin_amdgcn_ballot_w64(pm != 0u);
+            int at = nstaged + lanes_below(mask);
+            asm volatile("" : "+v"(at));               // (or a branch goes around its two instructions)
+            const int pos = pm != 0u ? at : StageQueue::CAP + lane_;
+            const int r = __builtin_ctz(pm | 0x10000u);
+            pm &= pm - 1u;
+            const int sc = select_row(x.acc, r & 15) - x.negth - above;      // the row's score
+            const uint32_t item = 8u * (uint32_t)(r >> 2) + (uint32_t)(r & 3) + 4u * half;
+            sq.log(pos) = make_uint2(((uint32_t)x.blk * 32u + item) | (((x.cmask >> (item & 31u)) & 1u) << 31),
+                                         ((uint32_t)sc << 16) | (uint32_t)qid);
+            sq.range(pos) = range;
+            nstaged += __popcll(mask);
+        };
+        auto stage_rest = [&](const Scored &x, uint32_t &pm) __attribute__((always_inline)) {
+            for (;;) {
+                if (nstaged > flush_above) FLUSH_STAGE();
+                if (__builtin_amdgcn_ballot_w64(pm != 0u) == 0ull) break;
+                stage_round(x, pm, here(lane));
+            }
+        };
+        auto step = [&](Scored &x, const Scored &before) __attribute__((always_inline)) {
+            uint32_t c[ND];
+            const uint2 masks = cmn;
+#pragma unroll
+            for (int w = 0; w < ND; w++) c[w] = cn[w];
+            fetch();
+            seg_items += (uint32_t)__popc(masks.y);
+            // (every fourth block is often enough: the bound moves rarely)
+            if (((b - first) & 3) == 0) {
+                // the accumulators start at -(threshold + 1): a row passes iff it ends up negative
+                if (live) negth = -(bound_next + above + 1);
+                bound_next = __hip_atomic_load(at32(a.bound, q0 * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+            x.negth = negth;
+            x.blk = se.blk_begin + b;
+            x.cmask = masks.x;
+            x.rows = 0xFFFFu;
+            // the list's last block: drop rows whose slot holds no item
+            if (b == se.nblk - 1 && se.tail_valid < 32) x.rows = rows_below(se.tail_valid - 4 * (here(lane) >> 5));
+            Contraction<ND> k;
+            k.front_words(c);
+            // (a copy the compiler cannot see through: the accumulators' start value must not stay tied to the
+            // register that the survivors need later, or the whole tuple is built elsewhere and moved)
+            int acc0 = negth;
+            asm volatile("" : "+v"(acc0));
+#pragma unroll
+            for (int r = 0; r < 16; r++) x.acc[r] = acc0;
+            __builtin_amdgcn_sched_barrier(0);
+            k.front(B, x.acc);
+            k.back_words(c);
+            uint32_t pm = negative_rows(before.acc) & before.rows;     // rows of this lane that pass
+            interleave<Contraction<ND>::FRONT, 3>();
+            __builtin_amdgcn_sched_barrier(0);
+            k.back(B, x.acc);
+            stage_round(before, pm, here(lane));
+            interleave<Contraction<ND>::BACK, 4>();
+            __builtin_amdgcn_sched_barrier(0);
+            // (the next block's codes are waited for here: behind a flush it would be a wait for its stores and
+            // atomics too, which are counted with the loads)
+#pragma unroll
+            for (int w = 0; w < ND; w++) asm volatile("" : "+v"(cn[w]));
+            stage_rest(before, pm);
+        };
+        Scored x0, x1;
+        x1.negth = ACC_NEVER; x1.rows = 0u; x1.blk = 0; x1.cmask = 0u;
+#pragma unroll
+        for (int r = 0; r < 16; r++) x1.acc[r] = ACC_NEVER;
+        enter_run();
+        for (;;) {
+            step(x0, x1);
+            if (!advance()) break;
+            step(x1, x0);
+            if (!advance()) { x0 = x1; break; }
         }
+        uint32_t pm = negative_rows(x0.acc) & x0.rows;
+        stage_rest(x0, pm);
+        if (a.dco && here(lane) < 32 && scored) atomicAdd(at32(a.dco, (uint32_t)qid * 8u), (unsigned long long)scored);
+        } else
+            query_facts(next);
         // do not sit on survivors for long: their histogram counts tighten everyone's bound
-        if (nstaged >= 32) FLUSH_STAGE();
-        if (a.dco && g == 0 && scored) atomicAdd(&a.dco[qid], (unsigned long long)scored);
+        if (nstaged >= 32 || (u_next >= nslices && nstaged > 0)) FLUSH_STAGE();
         u = u_next;
         u_next = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_next2);
     }
-    if (nstaged > 0) FLUSH_STAGE();
     // (a wave that never had a unit wrote nothing, and the chunk of its index may be another wave's)
     if (lane == 0 && lc.used > 0 && lc.chunk < (uint32_t)a.log_chunks) a.chunk_fill[lc.chunk] = lc.used;
 }
@@ -1015,7 +1293,7 @@ __global__ __launch_bounds__(1024, 1) void scan_mfma_lds_kernel(IndexView v, Mfm
     const int ND = v.nd, KS = ND * 8;                   // K-steps incl. zero padding, ND <= LDSK_MAX_ND
     const int nthreads = blockDim.x, nwave = nthreads >> 6;
     v4i *Bl = (v4i *)dyn_lds;                           // [KS][64]
-    StageQueue *stage = (StageQueue *)(dyn_lds + (size_t)KS * 64 * 16);   // [nwave]
+    SmallStageQueue *stage = (SmallStageQueue *)(dyn_lds + (size_t)KS * 64 * 16);   // [nwave]
     if (threadIdx.x < 16) {
         v4i r = {0, 0, 0, 0};
         const int sh = 1 << ((threadIdx.x & 3) * 8);
@@ -1026,7 +1304,7 @@ __global__ __launch_bounds__(1024, 1) void scan_mfma_lds_kernel(IndexView v, Mfm
         onehot[threadIdx.x] = r;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, j = lane & 31;
-    StageQueue &sq = stage[wave];
+    SmallStageQueue &sq = stage[wave];
     const int M = v.M, T = v.T;
     const int bias = 128 * M;
     int nstaged = 0;
@@ -1036,7 +1314,6 @@ __global__ __launch_bounds__(1024, 1) void scan_mfma_lds_kernel(IndexView v, Mfm
     const uint32_t gwave = blockIdx.x * nwave + wave, nwaves = gridDim.x * nwave;
     LogCursor lc;
     lc.chunk = gwave;                                  // (a workgroup without a unit never writes)
-    lc.next_v = gwave + log_active_waves(nunits, gridDim.x, (uint32_t)nwave);
     lc.used = 0;
     for (bool first = true;; first = false) {
         __syncthreads();                               // everyone is done with the previous tile
@@ -1071,7 +1348,7 @@ __global__ __launch_bounds__(1024, 1) void scan_mfma_lds_kernel(IndexView v, Mfm
         }
         const int qi = tile * 32 + j;
         const int qid = qi < nql ? a.qlist[base + qi] : -1;
-        const uint32_t hmul = hist_mul(qid >= 0 ? (uint32_t)a.tau[qid] : 0u);
+        const uint32_t range = hist_range(qid >= 0 ? (uint32_t)a.tau[qid] : 0u);
         const int32_t *bq = a.bound + (qid >= 0 ? qid : 0);
         const uint32_t *bmq = a.bitmap + (size_t)(qid >= 0 ? qid : 0) * a.bmwords;
         __syncthreads();
@@ -1141,9 +1418,7 @@ __global__ __launch_bounds__(1024, 1) void scan_mfma_lds_kernel(IndexView v, Mfm
                     const uint32_t slot0 = (uint32_t)cur.blk * 32u + 4u * g;
                     const int tail_valid = segs_s[cur.seg].tail_valid;
                     if (cur.last && tail_valid < 32) {
-#pragma unroll
-                        for (int r = 0; r < 16; r++)
-                            if (8 * (r >> 2) + 4 * g + (r & 3) >= tail_valid) pm &= ~(1u << r);
+                        pm &= rows_below(tail_valid - 4 * g);
                     }
                     for (;;) {
                         const bool has = pm != 0u;
@@ -1161,9 +1436,9 @@ __global__ __launch_bounds__(1024, 1) void scan_mfma_lds_kernel(IndexView v, Mfm
                             const int sc = ((r & 8) ? s2b : s2a) - negth;
                             const int pos = nstaged + lanes_below(mask);
                             const uint32_t item = 8u * (uint32_t)(r >> 2) + (uint32_t)(r & 3);   // + 4 g
-                            sq.ent[pos] = make_uint2((slot0 + item) | (((cmask >> (item + 4u * g)) & 1u) << 31),
-                                                     ((uint32_t)(sc + bias) << 16) | (uint32_t)qid);
-                            sq.hmul[pos] = hmul;
+                            sq.log(pos) = make_uint2((slot0 + item) | (((cmask >> (item + 4u * g)) & 1u) << 31),
+                                                         ((uint32_t)(sc + bias) << 16) | (uint32_t)qid);
+                            sq.range(pos) = range;
                         }
                         nstaged += __popcll(mask);
                         if (nstaged > STAGE_CAP - 64) {
@@ -1284,7 +1559,7 @@ __global__ __launch_bounds__(1024) void sample_group_kernel(const int32_t *__res
 
 // scores[q][b * 32 + i] = score of item i of block b of the first `sample_blocks` own blocks of
 // q's first list (0xFFFF: the slot holds no item); blocks the list does not have are not written.
-template <int T>
+template <int ND>
 __global__ __launch_bounds__(WG) void sample_mfma_kernel(IndexView v, const uint8_t *__restrict__ lut,
                                                             int sample_blocks,
                                                             const int32_t *__restrict__ s_off,
@@ -1293,17 +1568,10 @@ __global__ __launch_bounds__(WG) void sample_mfma_kernel(IndexView v, const uint
                                                             const int32_t *__restrict__ s_tiles,
                                                             uint16_t *__restrict__ scores)
 {
-    constexpr int ND = (T + 7) / 8;
-    constexpr int M = 2 * T;
-    constexpr int TS = T / 2;
-    __shared__ uint2 sparse_tab[32];                   // as in scan_mfma_kernel
-    fill_sparse_tab(sparse_tab);
-    __syncthreads();
     const int lane = threadIdx.x & 63, g = lane >> 5, j = lane & 31;
-    const uint32_t bias = 128u * M;
     const uint32_t ntiles = (uint32_t)s_toff[v.nlist];
     const uint32_t gwave = blockIdx.x * (WG / 64) + (threadIdx.x >> 6), nwaves = gridDim.x * (WG / 64);
-    v8i B[TS];
+    v8i B[5 * ND];
     for (uint32_t u = gwave; u < ntiles; u += nwaves) {
         const int L = __builtin_amdgcn_readfirstlane(s_tiles[u]);
         const ListEntry le = v.lists[L];
@@ -1311,18 +1579,7 @@ __global__ __launch_bounds__(WG) void sample_mfma_kernel(IndexView v, const uint
         const int base = s_off[L], n = s_off[L + 1] - base;
         const int qi = tile * 32 + j;
         const int qid = qi < n ? s_q[base + qi] : -1;
-        {
-            const uint8_t *lq = lut + (size_t)(qid >= 0 ? qid : 0) * (M * 16) + g * 32;
-            const int keep = qid >= 0 ? -1 : 0;
-            const v4i flip = {(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
-            const v4i keep4 = {keep, keep, keep, keep};
-#pragma unroll
-            for (int t = 0; t < TS; t++) {
-                const v4i x = (*(const v4i *)(lq + t * 64) ^ flip) & keep4;
-                const v4i y = (*(const v4i *)(lq + t * 64 + 16) ^ flip) & keep4;
-                B[t] = (v8i){x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
-            }
-        }
+        const int above = load_byte_tables<ND>(lut, (uint32_t)(qid >= 0 ? qid : 0), v.M, g, B);
         int cnt = le.shared_cnt + le.misc_cnt;
         cnt = cnt < sample_blocks ? cnt : sample_blocks;
         if (cnt <= 0) continue;                        // uniform for the wave
@@ -1342,34 +1599,11 @@ __global__ __launch_bounds__(WG) void sample_mfma_kernel(IndexView v, const uint
                 for (int w = 0; w < ND; w++) cn[w] = cp[(size_t)(b + 1) * ND * 64 + w * 64];
                 vmn = v.vmask[le.blk_begin + b + 1];
             }
-            // the accumulators start at the bias of the signed table entries, so they end as the
-            // scores themselves (below 2^16)
+            // the accumulators end as the scores themselves (below 2^16)
             v16i acc;
 #pragma unroll
-            for (int r = 0; r < 16; r++) acc[r] = (int)bias;
-#define CODE_LO(t_) ((c[(t_) >> 2] >> (8 * ((t_) & 3))) & 15u)
-#define CODE_HI(t_) ((c[(t_) >> 2] >> (8 * ((t_) & 3) + 4)) & 15u)
-#define LOAD_A(t_)                                                                        \
-    do {                                                                                  \
-        const uint2 *e1_ = &sparse_tab[CODE_LO(t_)], *e2_ = &sparse_tab[CODE_HI(t_)];      \
-        v1[t_] = e1_[0]; v2[t_] = e2_[0];                                                 \
-        p1[t_] = e1_[16].x; p2[t_] = e2_[16].y;                                           \
-    } while (0)
-            uint2 v1[TS], v2[TS];
-            uint32_t p1[TS], p2[TS];
-            LOAD_A(0);
-            if (TS > 1) LOAD_A(1);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int t = 0; t < TS; t++) {
-                const v4i av = {(int)v1[t].x, (int)v1[t].y, (int)v2[t].x, (int)v2[t].y};
-                acc = __builtin_amdgcn_smfmac_i32_32x32x64_i8(av, B[t], acc, (int)(p1[t] | p2[t]), 0, 0);
-                if (t + 2 < TS) LOAD_A(t + 2);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#undef LOAD_A
-#undef CODE_LO
-#undef CODE_HI
+            for (int r = 0; r < 16; r++) acc[r] = -above;
+            contract_block<ND>(c, B, acc);
             // acc[r]: item 8 * (r / 4) + 4 * g + r % 4, query column j: four consecutive items
             // per group of four registers, written as one 8-byte store.  A block whose 32 slots
             // all hold items (every block but a list's last, unless items were deleted) needs no
@@ -1399,7 +1633,7 @@ __global__ __launch_bounds__(WG) void sample_mfma_kernel(IndexView v, const uint
 
 bool rairs_sample_scores_supported(const IndexView &v, int64_t nq)
 {
-    return (v.T == 8 || v.T == 24 || v.T == 32) && v.nlist <= SAMPLE_GROUP_MAX_NLIST &&
+    return (v.M == 16 || v.M == 48 || v.M == 64) && v.nlist <= SAMPLE_GROUP_MAX_NLIST &&
            nq >= SAMPLE_GROUP_MIN_QUERIES;
 }
 
@@ -1432,13 +1666,13 @@ int rairs_launch_sample_scores(const IndexView &v, const uint8_t *lut, int sampl
     const int64_t tiles_max = nq / 32 + v.nlist;
     unsigned grid = (unsigned)((tiles_max + WG / 64 - 1) / (WG / 64));
     if (grid > 512u) grid = 512u;
-#define SAMPLE_MFMA(T_)                                                                           \
-    hipLaunchKernelGGL(sample_mfma_kernel<T_>, dim3(grid), dim3(WG), 0, s, v, lut, sample_blocks, s_off, \
+#define SAMPLE_MFMA(ND_)                                                                          \
+    hipLaunchKernelGGL(sample_mfma_kernel<ND_>, dim3(grid), dim3(WG), 0, s, v, lut, sample_blocks, s_off, \
                        s_toff, s_q, s_tiles, scores)
-    switch (v.T) {
-    case 8: SAMPLE_MFMA(8); break;
-    case 24: SAMPLE_MFMA(24); break;
-    default: SAMPLE_MFMA(32); break;
+    switch (v.nd) {
+    case 1: SAMPLE_MFMA(1); break;
+    case 3: SAMPLE_MFMA(3); break;
+    default: SAMPLE_MFMA(4); break;
     }
 #undef SAMPLE_MFMA
     RAIRS_HIP(hipGetLastError());
@@ -1450,7 +1684,7 @@ bool rairs_mfma_supported(const IndexView &v)
     return v.T >= 1 && v.nd * 8 * 64 * 16 <= 128 * 1024;    // tables of a tile must fit 128 KB of LDS
 }
 
-bool rairs_mfma_reg_tables(const IndexView &v) { return v.T == 8 || v.T == 24 || v.T == 32; }
+bool rairs_mfma_reg_tables(const IndexView &v) { return v.nd <= 4; }
 
 // persistent grids: 256 compute units x 2 workgroups of 4 waves with the tables in registers; one
 // workgroup per compute unit, with as many waves as LDS leaves room for, with the tables in LDS
@@ -1461,7 +1695,7 @@ static void scan_launch_shape(const IndexView &v, bool *reg_tables, unsigned *gr
     *grid = *reg_tables ? 512u : 256u;
     *table_bytes = (size_t)v.nd * 8 * 64 * 16;
     int w = 16;
-    while (w > 4 && *table_bytes + (size_t)w * sizeof(StageQueue) > 158 * 1024) w >>= 1;
+    while (w > 4 && *table_bytes + (size_t)w * sizeof(SmallStageQueue) > 158 * 1024) w >>= 1;
     *lds_waves = w;
 }
 
@@ -1473,8 +1707,10 @@ int64_t rairs_scan_log_waves(const IndexView &v, int64_t units)
     int lds_waves;
     size_t table_bytes;
     scan_launch_shape(v, &reg_tables, &gridx, &lds_waves, &table_bytes);
-    if (reg_tables) return units < (int64_t)gridx * (WG / 64) ? units : (int64_t)gridx * (WG / 64);
-    return (units < (int64_t)gridx ? units : (int64_t)gridx) * lds_waves;
+    // (Programs size workspaces by this, and the few-query search has to fit into them: shapes that have come to
+    // the tables in registers since keep the figure of the tables in LDS, which is the larger one.)
+    if (v.M == 16 || v.M == 48 || v.M == 64) return units < (int64_t)gridx * (WG / 64) ? units : (int64_t)gridx * (WG / 64);
+    return (units < 256 ? units : 256) * lds_waves;
 }
 
 int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
@@ -1487,7 +1723,7 @@ int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
     size_t table_bytes;
     scan_launch_shape(v, &reg_tables, &gridx, &lds_waves, &table_bytes);
     const uint32_t nwaves = gridx * (reg_tables ? WG / 64 : lds_waves);
-    // who starts on a unit of its own index, and with how many waves (see log_active_waves)
+    // who starts on a unit of its own index, and with how many waves (see log_first_free)
     const uint32_t starters = reg_tables ? nwaves : gridx, waves_each = reg_tables ? 1u : (uint32_t)lds_waves;
     if (a.log_chunks < 2) {
         rairs_set_error("survivor log of %d chunks", a.log_chunks);
@@ -1518,15 +1754,24 @@ int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL(lm_fill_lds_kernel, dim3(lgrid + LM_UNIT_WGS), dim3(256), lds, s, v, a.probe_ids, a.nq,
                            a.nprobe, a.p_first, a.lcount, a.loff, a.lcursor, a.qlist, qb, a.toff,
-                           a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each);
+                           a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each, (uint32_t)a.split_max);
     } else {
         hipLaunchKernelGGL(lm_prefix_kernel, dim3(1), dim3(1024), 0, s, v, a.lcount, a.loff, a.lcursor,
-                           a.toff, a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each);
+                           a.toff, a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each, (uint32_t)a.split_max);
         hipLaunchKernelGGL(lm_units_kernel, dim3((unsigned)((v.nlist + 255) / 256)), dim3(256), 0, s, v, a.lcount,
                            a.loff, a.toff, a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec);
         hipLaunchKernelGGL(lm_fill_kernel, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, s,
                            a.probe_ids, a.nq, a.nprobe, a.p_first, v.nlist, a.loff, a.lcursor, a.qlist);
     }
+    RAIRS_HIP(hipGetLastError());
+    return RAIRS_OK;
+}
+
+size_t rairs_scan_tables_bytes(const IndexView &v, int64_t nq) { return (size_t)nq * scan_tables_stride(v.nd); }
+
+int rairs_launch_scan_tables(const IndexView &v, const uint8_t *lut, int64_t nq, uint8_t *tables, hipStream_t s)
+{
+    hipLaunchKernelGGL(scan_tables_kernel, dim3((unsigned)((nq + WG / 64 - 1) / (WG / 64))), dim3(WG), 0, s, lut, v.M, v.nd, nq, tables);
     RAIRS_HIP(hipGetLastError());
     return RAIRS_OK;
 }
@@ -1549,12 +1794,13 @@ int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_
     scan_launch_shape(v, &reg_tables, &gridx, &lds_waves, &table_bytes);
     const dim3 grid(gridx);
     if (ev) RAIRS_HIP(hipEventRecord(ev[0], s));
-    switch (v.T) {
-    case 8: hipLaunchKernelGGL(scan_mfma_kernel<8>, grid, dim3(WG), 0, s, v, a); break;
-    case 24: hipLaunchKernelGGL(scan_mfma_kernel<24>, grid, dim3(WG), 0, s, v, a); break;
-    case 32: hipLaunchKernelGGL(scan_mfma_kernel<32>, grid, dim3(WG), 0, s, v, a); break;
+    switch (v.nd) {
+    case 1: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<1, true> : scan_mfma_kernel<1, false>), grid, dim3(WG), 0, s, v, a); break;
+    case 2: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<2, true> : scan_mfma_kernel<2, false>), grid, dim3(WG), 0, s, v, a); break;
+    case 3: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<3, true> : scan_mfma_kernel<3, false>), grid, dim3(WG), 0, s, v, a); break;
+    case 4: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<4, true> : scan_mfma_kernel<4, false>), grid, dim3(WG), 0, s, v, a); break;
     default: {
-        const size_t lds = table_bytes + (size_t)lds_waves * sizeof(StageQueue);
+        const size_t lds = table_bytes + (size_t)lds_waves * sizeof(SmallStageQueue);
         RAIRS_HIP(hipFuncSetAttribute((const void *)scan_mfma_lds_kernel,
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL(scan_mfma_lds_kernel, grid, dim3(64 * lds_waves), lds, s, v, a);
