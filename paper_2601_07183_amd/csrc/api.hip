@@ -651,11 +651,11 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     const size_t surv_bytes = (size_t)nq * w.surv_cap * 8;
     w.s_scores = w.surv_buf = take(samp_bytes + hmin_bytes > surv_bytes ? samp_bytes + hmin_bytes : surv_bytes);
     w.hmin = hmin_bytes ? w.s_scores + samp_bytes : 0;
-    // The scan's tables (1,296 bytes a query at most: M <= 64) live from the selection of the probe lists to the
-    // end of the scan, the survivor buffers from there on.  With the sample on the matrix cores its scores and the
-    // minima may still be in use when the tables are made (on the other stream), else the minima are not.  That
-    // sample takes at most max(3,072, 10 bigK) bytes a query and the minima 2,048 then: all three together stay
-    // below the survivors' max(8,192, 64 bigK).
+    // The scan's tables (5,136 bytes a query at most, 1,296 for M <= 64) live from the selection of the probe lists
+    // to the end of the scan, the survivor buffers from there on.  With the sample on the matrix cores (M <= 64) its
+    // scores and the minima may still be in use when the tables are made (on the other stream), else the minima are
+    // not.  That sample takes at most max(3,072, 10 bigK) bytes a query and the minima 2,048 then: all three
+    // together stay below the survivors' max(8,192, 64 bigK).
     w.tables = w.s_scores + (grouped ? samp_bytes + align_up(hmin_bytes, 256) : 0);
     w.total = off;
     return w;
@@ -1001,7 +1001,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     uint16_t *s_scores = (uint16_t *)(ws + w.s_scores);
     if (overlap) {
         if ((rc = rairs_launch_group(v, ma, h->side))) return rc;
-        if (rairs_mfma_reg_tables(v) && (rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), h->side))) return rc;
+        if ((rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), h->side))) return rc;
         RAIRS_HIP(hipEventRecord(h->ev_group, h->side));
     }
     if (grouped && probed_on_side) {
@@ -1032,7 +1032,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     if (overlap) RAIRS_HIP(hipStreamWaitEvent(s, h->ev_group, 0));
     else {
         if ((rc = rairs_launch_group(v, ma, s))) return rc;
-        if (rairs_mfma_reg_tables(v) && (rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), s))) return rc;
+        if ((rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), s))) return rc;
     }
     if ((rc = rairs_launch_scan_mfma(v, ma, s, ev))) return rc;
     if ((rc = rairs_launch_select(v, ma, s))) return rc;

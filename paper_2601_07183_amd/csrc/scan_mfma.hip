@@ -3,10 +3,9 @@
 // Section 5.2 taken to its conclusion: a block is fetched once for 32 queries).
 //
 // score(query, item) = sum_m lut[query][m][code[item][m]] is a contraction of the lookup tables
-// with a 0/1 expansion of the codes, which the register-table kernel gives to the sparse matrix
+// with a 0/1 expansion of the codes, which the kernels give to the sparse matrix
 // instruction v_smfmac_i32_32x32x64_i8 in a form that has nothing to look up (selectors, below).
-// The LDS-table kernel (any M) uses the dense v_mfma_i32_32x32x32_i8 on the one-hot expansion
-// (sum_c lut[q][m][c] * [code == c]), two sub-quantizers per instruction with both operands from LDS.
+// The LDS-table kernel (M > 64) does the same with the tables in LDS.
 // Integer arithmetic throughout, so the scores equal the plain 16-bit sums bit for bit.
 //
 // Work is cut into units (list L, tile of <= 32 queries probing L, run of parts of the list; a part
@@ -28,6 +27,8 @@
 // the query's bound now and then and lower it with an atomic minimum; scanning waves re-read it
 // for every block.  A stale view is only looser.
 #include <limits.h>
+
+#include <type_traits>
 
 #include "device_util.h"
 #include "select_wg.h"
@@ -440,8 +441,6 @@ static __device__ __forceinline__ uint32_t histogram_bound(const MfmaScanArgs &a
 // 0.610 ms instead of 0.558 (1,024 and more: the same) and the collect step, whose atomics go by
 // chunk and query, 49 us instead of 35.  Ids, tags and the duplicate rule are resolved afterwards,
 // in bulk, by collect_kernel and the select kernels.
-#define STAGE_CAP 128              // of the LDS-table kernel; a multiple of 64 (a flush takes the queue in rows of 64)
-static_assert(STAGE_CAP % 64 == 0 && STAGE_CAP >= 128, "stage queue rows");
 #define LOG_CHUNK RAIRS_LOG_CHUNK
 static_assert((LOG_CHUNK & (LOG_CHUNK - 1)) == 0, "places in a chunk are taken by masking");
 #define LOG_COUNTED 0x80000000u    // bit 31 of a staged slot: the entry counts in the histogram
@@ -450,18 +449,17 @@ struct StageEntry {
     uint32_t range, unused;        // of the query's histogram
 };
 struct StageQueue {
-    static constexpr int CAP = 256;
+    static constexpr int CAP = 256;         // a multiple of 64: a flush takes the queue in rows of 64
     StageEntry ent[CAP + 64];        // the last 64 take what lanes without an entry write
     __device__ __forceinline__ uint2 &log(int i) { return ent[i].log; }
-    __device__ __forceinline__ uint32_t &range(int i) { return ent[i].range; }
+    __device__ __forceinline__ uint32_t range(const MfmaScanArgs &, int i, uint32_t) { return ent[i].range; }
 };
-// the same for the kernel with the tables in LDS, where every KB counts
+// the same for the kernel with the tables in LDS, where every KB counts: the range is looked up again
 struct SmallStageQueue {
-    static constexpr int CAP = STAGE_CAP;
-    uint2 log_s[STAGE_CAP];
-    uint32_t range_s[STAGE_CAP];
-    __device__ __forceinline__ uint2 &log(int i) { return log_s[i]; }
-    __device__ __forceinline__ uint32_t &range(int i) { return range_s[i]; }
+    static constexpr int CAP = 128;
+    uint2 ent[CAP];
+    __device__ __forceinline__ uint2 &log(int i) { return ent[i]; }
+    __device__ __forceinline__ uint32_t range(const MfmaScanArgs &a, int, uint32_t qid) { return hist_range((uint32_t)*at32(a.tau, qid * 4u)); }
 };
 
 struct LogCursor {
@@ -509,7 +507,7 @@ static __device__ __forceinline__ void stage_flush(const MfmaScanArgs &a, Queue 
             if (room) a.log[(size_t)(at < LOG_CHUNK ? lc.chunk : next) * LOG_CHUNK + (at & (LOG_CHUNK - 1u))] = make_uint2(e.x & ~LOG_COUNTED, e.y);
             if (e.x & LOG_COUNTED) {
                 // scores beyond the histogram's range share the last bin
-                const uint32_t bin = __umulhi(e.y >> 16, hist_mul(sq.range(i)));
+                const uint32_t bin = __umulhi(e.y >> 16, hist_mul(sq.range(a, i, qid)));
                 atomicAdd(at32(a.hist, (qid * RAIRS_HIST_BINS + (bin < RAIRS_HIST_BINS - 1 ? bin : RAIRS_HIST_BINS - 1)) * 4u), 1u);
             }
         }
@@ -524,7 +522,7 @@ static __device__ __forceinline__ void stage_flush(const MfmaScanArgs &a, Queue 
             const uint32_t qid = sq.log(lane).y & 0xFFFFu;
             int32_t *bq = at32(a.bound, qid * 4u);
             const int32_t cur = __hip_atomic_load(bq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const uint32_t nb = histogram_bound(a, qid, sq.range(lane));
+            const uint32_t nb = histogram_bound(a, qid, sq.range(a, lane, qid));
             if (nb < 0xFFFFu && (int32_t)nb < cur) {
                 atomicMin(bq, (int32_t)nb);
                 lowered = true;
@@ -958,7 +956,7 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
             const uint32_t item = 8u * (uint32_t)(r >> 2) + (uint32_t)(r & 3) + 4u * half;
             sq.log(pos) = make_uint2(((uint32_t)x.blk * 32u + item) | (((x.cmask >> (item & 31u)) & 1u) << 31),
                                          ((uint32_t)sc << 16) | (uint32_t)qid);
-            sq.range(pos) = range;
+            sq.ent[pos].range = range;
             nstaged += __popcll(mask);
         };
         auto stage_rest = [&](const Scored &x, uint32_t &pm) __attribute__((always_inline)) {
@@ -1275,186 +1273,184 @@ __global__ __launch_bounds__(WG) void select_wave_kernel(IndexView v, MfmaScanAr
 // (Queries with more survivors than a wave holds are left on a list for the workgroup-wide select,
 // select_wg.h, which runs in the launch behind this one together with the exact redo.)
 
-// ---- the same scan with the tile's tables in LDS (any M up to 256) ----------------------------
+// ---- the same scan with the tile's tables in LDS (more than 64 sub-quantizers) -----------------------
 //
-// For tables too large for registers (M = 240: 30 KB per query pair of lanes) the waves of a
-// workgroup (as many as LDS leaves room for, up to 16) share one tile: its tables sit in LDS as [K-step][lane] 16-byte operands, zero beyond
-// the last subspace, and the waves take the unit's blocks round robin.  Each MFMA then reads both
-// operands from LDS (one-hot row and table row), which holds it to about half the matrix-core
-// rate; survivors, bounds and the log work exactly as in scan_mfma_kernel.
-#define LDSK_MAX_ND 16      // code dwords per lane and block: M <= 256
-#define LDSK_MAX_SEGS 32    // segments per unit: up to 4 parts of RAIRS_PART_SEGS segments
-__global__ __launch_bounds__(1024, 1) void scan_mfma_lds_kernel(IndexView v, MfmaScanArgs a)
+// For tables too large for registers (M = 240: 37.5 KB per half wave of queries) the eight waves of a workgroup
+// share one tile.  Its tables sit in LDS as [instruction][16-byte half][lane] (of sixteen dwords of codes
+// the last one's in registers, or 160 KB would not do), the unit's blocks go to the waves in groups of
+// four, and a wave's instruction operand is read once for its group: two LDS reads to four matrix instructions, 16 of the
+// LDS's cycles for 132 of a SIMD's, so four SIMDs keep it half busy.  (Units of few blocks are dealt in groups of
+// two.)  Codes come a pair of dwords ahead.  Survivors, bounds and the log work as in scan_mfma_kernel.
+// The dense instruction with one-hot rows from LDS, two reads each, took all of the LDS's time: 200,000 x 960,
+// M = 240, 1,000 queries, 45 probes: 865 us, now 570.
+#define LDSK_MAX_SEGS 32    // runs per unit: up to 4 parts of RAIRS_PART_SEGS runs
+#define LDSK_WAVES 8
+// matrix instructions a block whose tables are in LDS
+static __host__ __device__ __forceinline__ int ldsk_lds_ops(int nd) { return 5 * (nd < 16 ? nd : 15); }
+template <bool LAST_IN_REGS>                           // sixteen dwords of codes
+__global__ __launch_bounds__(64 * LDSK_WAVES, 2) void scan_mfma_lds_kernel(IndexView v, MfmaScanArgs a)
 {
     extern __shared__ __align__(16) unsigned char dyn_lds[];
-    __shared__ v4i onehot[16];
     __shared__ SegEntry segs_s[LDSK_MAX_SEGS];
     __shared__ uint32_t s_unit;
-    const int ND = v.nd, KS = ND * 8;                   // K-steps incl. zero padding, ND <= LDSK_MAX_ND
-    const int nthreads = blockDim.x, nwave = nthreads >> 6;
-    v4i *Bl = (v4i *)dyn_lds;                           // [KS][64]
-    SmallStageQueue *stage = (SmallStageQueue *)(dyn_lds + (size_t)KS * 64 * 16);   // [nwave]
-    if (threadIdx.x < 16) {
-        v4i r = {0, 0, 0, 0};
-        const int sh = 1 << ((threadIdx.x & 3) * 8);
-        if ((threadIdx.x >> 2) == 0) r.x = sh;
-        if ((threadIdx.x >> 2) == 1) r.y = sh;
-        if ((threadIdx.x >> 2) == 2) r.z = sh;
-        if ((threadIdx.x >> 2) == 3) r.w = sh;
-        onehot[threadIdx.x] = r;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, j = lane & 31;
-    SmallStageQueue &sq = stage[wave];
-    const int M = v.M, T = v.T;
-    const int bias = 128 * M;
+    const int ND = v.nd, ops = ldsk_lds_ops(ND);
+    v4i *Bl = (v4i *)dyn_lds;                           // [ops][2][64]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), half = lane >> 5, j = lane & 31;
+    SmallStageQueue &sq = ((SmallStageQueue *)(dyn_lds + (size_t)ops * 2048))[wave];
     int nstaged = 0;
     RefreshPace pace = {REFRESH_GAP_MIN, REFRESH_GAP_MIN - 1u, 0u};
     const uint32_t nunits = (uint32_t)a.toff[v.nlist];
     if (nunits == 0u) return;                          // uniform; nothing was written
-    const uint32_t gwave = blockIdx.x * nwave + wave, nwaves = gridDim.x * nwave;
     LogCursor lc;
-    lc.chunk = gwave;                                  // (a workgroup without a unit never writes)
+    lc.chunk = blockIdx.x * LDSK_WAVES + wave;         // (a workgroup without a unit never writes)
     lc.used = 0;
     for (bool first = true;; first = false) {
         __syncthreads();                               // everyone is done with the previous tile
         if (threadIdx.x == 0) s_unit = first ? blockIdx.x : atomicAdd(a.next_task, 1u);
         __syncthreads();
-        const uint32_t u = s_unit;
+        const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_unit);
         if (u >= nunits) break;                        // uniform for the workgroup; the counter only grows
-        const int L = a.unit_list[u];
-        const ListEntry le = v.lists[L];
-        const int rem = (int)u - a.toff[L];
-        const int up = list_unit_parts(L, a.unit_parts, a.unit_tail_from);
-        const int runs = (le.part_cnt + up - 1) / up;
-        const int tile = rem / runs;
-        const int p0 = (rem % runs) * up;
-        const int p1 = p0 + up < le.part_cnt ? p0 + up : le.part_cnt;
-        const int seg0 = v.parts[le.part_begin + p0] - le.seg_begin;
-        const int seg1 = v.parts[le.part_begin + p1] - le.seg_begin;
-        const int base = a.loff[L], nql = a.loff[L + 1] - base;
-        const int nseg = seg1 - seg0;                  // <= LDSK_MAX_SEGS
-        if ((int)threadIdx.x < nseg) segs_s[threadIdx.x] = v.segs[le.seg_begin + seg0 + threadIdx.x];
-        // tables of the tile into LDS: operand (t, lane (j, g)) = lut[q_j][2t+g][0..15] - 128
-        for (int e = threadIdx.x; e < KS * 64; e += nthreads) {
-            const int t = e >> 6, ln = e & 63, jj = ln & 31, gg = ln >> 5;
-            const int qi = tile * 32 + jj;
-            v4i x = {0, 0, 0, 0};
-            if (t < T && qi < nql) {
-                const int qq = a.qlist[base + qi];
-                x = *(const v4i *)(a.lut + (size_t)qq * (M * 16) + (size_t)(2 * t + gg) * 16);
-                x ^= (v4i){(int)0x80808080, (int)0x80808080, (int)0x80808080, (int)0x80808080};
-            }
-            Bl[e] = x;
+        const int32_t *rec = a.unit_rec + (size_t)u * UNIT_REC_WORDS;
+        const int tile = rec[1], seg0 = rec[2], nseg = rec[3] - seg0;      // nseg <= LDSK_MAX_SEGS
+        const int q_at = rec[4] + tile * 32, qn = rec[5] - tile * 32;
+        if ((int)threadIdx.x < nseg) segs_s[threadIdx.x] = v.segs[seg0 + threadIdx.x];
+        const int qid = j < qn ? a.qlist[q_at + j] : -1;
+        const uint32_t q0 = (uint32_t)(qid >= 0 ? qid : 0);     // (an absent column takes query 0's tables and never passes)
+        const char *row = (const char *)a.tables + (size_t)q0 * scan_tables_stride(ND);
+        const int above = *(const int *)(row + ND * 320);
+        const char *mine = row + half * 160;
+        for (int t = wave; t < ops; t += LDSK_WAVES) {
+            const char *p = mine + t / 5 * 320 + t % 5 * 32;
+            const v4i x = *(const v4i *)p, y = *(const v4i *)(p + 16);
+            Bl[t * 128 + lane] = x;
+            Bl[t * 128 + 64 + lane] = y;
         }
-        const int qi = tile * 32 + j;
-        const int qid = qi < nql ? a.qlist[base + qi] : -1;
-        const uint32_t range = hist_range(qid >= 0 ? (uint32_t)a.tau[qid] : 0u);
-        const int32_t *bq = a.bound + (qid >= 0 ? qid : 0);
-        const uint32_t *bmq = a.bitmap + (size_t)(qid >= 0 ? qid : 0) * a.bmwords;
+        v8i Br[LAST_IN_REGS ? 5 : 1];
+        if (LAST_IN_REGS)
+#pragma unroll
+            for (int g = 0; g < 5; g++) {
+                const char *p = mine + 15 * 320 + g * 32;
+                const v4i x = *(const v4i *)p, y = *(const v4i *)(p + 16);
+                Br[LAST_IN_REGS ? g : 0] = (v8i){x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+            }
+        const int32_t *bq = a.bound + q0;
+        const uint32_t *bmq = a.bitmap + (size_t)q0 * a.bmwords;
         __syncthreads();
-        // The unit's blocks, numbered through its segments, are dealt to the waves in turn; a wave
-        // fetches all code dwords of its next block (and that block's segment facts) while it
-        // multiplies the current one.
-        struct Blk { int valid, seg, b, blk, last; bool live; };
-        int fpos = wave;                               // number of this wave's next block in the unit
-        int wseg = 0, wbase = 0;                       // segment that holds it, blocks before that segment
-        auto locate = [&]() {
-            Blk r;
-            r.valid = 0; r.seg = 0; r.b = 0; r.blk = 0; r.last = 0; r.live = false;
-            while (wseg < nseg && fpos >= wbase + segs_s[wseg].nblk) { wbase += segs_s[wseg].nblk; wseg++; }
-            if (wseg < nseg) {
-                const int owner = segs_s[wseg].owner;
-                r.valid = 1; r.seg = wseg; r.b = fpos - wbase;
-                r.blk = segs_s[wseg].blk_begin + r.b;
-                r.last = r.b == segs_s[wseg].nblk - 1;
-                // cell (owner, L) is scored through list `owner` for queries that probe it
-                const uint32_t ob = bmq[owner >= 0 ? owner >> 5 : 0];
-                r.live = qid >= 0 && !(owner >= 0 && ((ob >> (owner & 31)) & 1u));
-            }
-            return r;
-        };
-        uint32_t cn[LDSK_MAX_ND];
-        uint2 cmn = make_uint2(0u, 0u);
+        int nblocks = 0;
+        for (int i = 0; i < nseg; i++) nblocks += segs_s[i].nblk;
+        nblocks = __builtin_amdgcn_readfirstlane(nblocks);
         uint32_t scored = 0;                           // items this lane's query was scored against, by this wave
-        int bound_next = 0;
-        auto fetch = [&](const Blk &bk) {
-            const uint32_t *cp = v.codes + (size_t)bk.blk * ND * 64 + lane;
+        int wseg = 0, wbase = 0;                       // run that holds the next block, blocks before it
+        auto group_of = [&](auto width, int first_block) __attribute__((always_inline)) {
+            constexpr int N = decltype(width)::value;
+            int blk[N], negth[N];                      // (uniform; per lane)
+            uint32_t cmask[N], rows[N];                // (uniform; per lane)
+            const int bound = __hip_atomic_load(bq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
-            for (int w = 0; w < LDSK_MAX_ND; w++)
-                if (w < ND) cn[w] = cp[(size_t)w * 64];
-            cmn = v.bmask[bk.blk];
-            bound_next = __hip_atomic_load(bq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        };
-        Blk cur = locate();
-        if (cur.valid) fetch(cur);
-        while (cur.valid) {
-            uint32_t c[LDSK_MAX_ND];
+            for (int i = 0; i < N; i++) {
+                const bool there = first_block + i < nblocks;              // (behind the last block: the last one again, nobody passes)
+                const int at = there ? first_block + i : nblocks - 1;
+                while (at >= wbase + segs_s[wseg].nblk) { wbase += segs_s[wseg].nblk; wseg++; }
+                const SegEntry se = segs_s[wseg];
+                const int b = at - wbase;
+                blk[i] = __builtin_amdgcn_readfirstlane(se.blk_begin + b);
+                // cell (owner, L) is scored through list `owner` for queries that probe it
+                const uint32_t ob = bmq[se.owner >= 0 ? se.owner >> 5 : 0];
+                const bool live = there && qid >= 0 && !(se.owner >= 0 && ((ob >> (se.owner & 31)) & 1u));
+                negth[i] = live ? -(bound + above + 1) : ACC_NEVER;
+                const uint2 masks = v.bmask[blk[i]];
+                cmask[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)masks.x);
+                scored += live ? (uint32_t)__popc(masks.y) : 0u;           // the block is contracted now: its DCO
+                // the list's last block: drop rows whose slot holds no item
+                rows[i] = b == se.nblk - 1 && se.tail_valid < 32 ? rows_below(se.tail_valid - 4 * half) : 0xFFFFu;
+            }
+            v16i acc[N];
 #pragma unroll
-            for (int w = 0; w < LDSK_MAX_ND; w++) c[w] = cn[w];
-            const uint32_t cmask = cmn.x;
-            const uint32_t blk_items = (uint32_t)__popc(cmn.y);
-            const int negth = cur.live ? -(bound_next - bias + 1) : ACC_NEVER;
-            fpos += nwave;
-            const Blk nxt = locate();
-            if (nxt.valid) fetch(nxt);
-            if (__ballot(cur.live) != 0ull) {
-                scored += cur.live ? blk_items : 0u;   // the block is contracted now: its DCO
-                v16i acc;
+            for (int i = 0; i < N; i++)
 #pragma unroll
-                for (int r = 0; r < 16; r++) acc[r] = negth;
+                for (int r = 0; r < 16; r++) acc[i][r] = negth[i];
+            uint32_t c[N][2], n[N][2];
+            auto codes = [&](uint32_t (&to)[N][2], int w) {
 #pragma unroll
-                for (int w = 0; w < LDSK_MAX_ND; w++) {
-                    if (w < ND) {                      // uniform
-                        const v4i *Bw = Bl + (size_t)w * 8 * 64 + lane;
-#pragma unroll
-                        for (int n = 0; n < 8; n++) {
-                            const uint32_t nib = (c[w] >> (4 * n)) & 15u;
-                            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(onehot[nib], Bw[n * 64], acc, 0, 0, 0);
-                        }
-                    }
+                for (int i = 0; i < N; i++) {
+                    const uint32_t *p = at32(v.codes + ((size_t)blk[i] * ND + w) * 64, (uint32_t)lane * 4u);
+                    to[i][0] = p[0];
+                    to[i][1] = p[w + 1 < ND ? 64 : 0];  // uniform
                 }
-                uint32_t pm = negative_rows(acc);
-                if (__ballot(pm != 0u) != 0ull) {
-                    const uint32_t slot0 = (uint32_t)cur.blk * 32u + 4u * g;
-                    const int tail_valid = segs_s[cur.seg].tail_valid;
-                    if (cur.last && tail_valid < 32) {
-                        pm &= rows_below(tail_valid - 4 * g);
-                    }
-                    for (;;) {
-                        const bool has = pm != 0u;
-                        const unsigned long long mask = __ballot(has);
-                        if (mask == 0ull) break;
-                        if (has) {
-                            const int r = __builtin_ctz(pm);
-                            pm &= pm - 1u;
-                            int s8[8], s4[4];
+            };
+            codes(c, 0);
+            v4i b0 = Bl[lane], b1 = Bl[64 + lane];
+            const v4i one = {SEL_FIRST, SEL_FIRST, SEL_FIRST, SEL_FIRST}, two = {SEL_SECOND, SEL_SECOND, SEL_SECOND, SEL_SECOND};
+            auto five = [&](const v4i &slot, const uint32_t (&s)[N][5], int t) __attribute__((always_inline)) {
 #pragma unroll
-                            for (int k = 0; k < 8; k++) s8[k] = (r & 1) ? acc[2 * k + 1] : acc[2 * k];
+                for (int g = 0; g < 5; g++) {
+                    const v8i B = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+                    const int tn = t + g + 1 < ops ? t + g + 1 : ops - 1;
+                    b0 = Bl[tn * 128 + lane];
+                    b1 = Bl[tn * 128 + 64 + lane];
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int k = 0; k < 4; k++) s4[k] = (r & 2) ? s8[2 * k + 1] : s8[2 * k];
-                            const int s2a = (r & 4) ? s4[1] : s4[0], s2b = (r & 4) ? s4[3] : s4[2];
-                            const int sc = ((r & 8) ? s2b : s2a) - negth;
-                            const int pos = nstaged + lanes_below(mask);
-                            const uint32_t item = 8u * (uint32_t)(r >> 2) + (uint32_t)(r & 3);   // + 4 g
-                            sq.log(pos) = make_uint2((slot0 + item) | (((cmask >> (item + 4u * g)) & 1u) << 31),
-                                                         ((uint32_t)(sc + bias) << 16) | (uint32_t)qid);
-                            sq.range(pos) = range;
-                        }
-                        nstaged += __popcll(mask);
-                        if (nstaged > STAGE_CAP - 64) {
-                            stage_flush(a, sq, nstaged, lane, lc, pace);
-                            nstaged = 0;
-                        }
+                    for (int i = 0; i < N; i++) acc[i] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(slot, B, acc[i], (int)s[i][g], 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            int w = 0;
+#pragma unroll 1                                       // (laid out fourteen times it spills)
+            for (; w + 2 <= (LAST_IN_REGS ? 14 : ND); w += 2) {
+                codes(n, w + 2 < ND ? w + 2 : w);
+                uint32_t s[N][5];
+#pragma unroll
+                for (int i = 0; i < N; i++) select_words_pair(c[i][0], c[i][1], s[i]);
+                five(one, s, 5 * w);
+                five(two, s, 5 * w + 5);
+#pragma unroll
+                for (int i = 0; i < N; i++) { c[i][0] = n[i][0]; c[i][1] = n[i][1]; }
+            }
+            if (LAST_IN_REGS || w < ND) {              // uniform: the last pair, or an odd last dword
+                uint32_t s[N][5];
+#pragma unroll
+                for (int i = 0; i < N; i++) {
+                    if (LAST_IN_REGS) select_words_pair(c[i][0], c[i][1], s[i]);
+                    else select_words_one(c[i][0], s[i]);
+                }
+                five(one, s, 5 * w);
+                if (LAST_IN_REGS)
+#pragma unroll
+                    for (int g = 0; g < 5; g++)
+#pragma unroll
+                        for (int i = 0; i < N; i++) acc[i] = __builtin_amdgcn_smfmac_i32_32x32x64_i8(two, Br[LAST_IN_REGS ? g : 0], acc[i], (int)s[i][g], 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < N; i++) {
+                uint32_t pm = negative_rows(acc[i]) & rows[i];
+                for (;;) {
+                    const unsigned long long mask = __builtin_amdgcn_ballot_w64(pm != 0u);
+                    if (mask == 0ull) break;
+                    const int r = __builtin_ctz(pm | 0x10000u);
+                    const int sc = select_row(acc[i], r & 15) - negth[i] - above;      // the row's score
+                    const uint32_t item = 8u * (uint32_t)(r >> 2) + (uint32_t)(r & 3) + 4u * half;
+                    if (pm != 0u)
+                        sq.ent[nstaged + lanes_below(mask)] = make_uint2(((uint32_t)blk[i] * 32u + item) | (((cmask[i] >> (item & 31u)) & 1u) << 31),
+                                                                         ((uint32_t)sc << 16) | (uint32_t)qid);
+                    pm &= pm - 1u;
+                    nstaged += __popcll(mask);
+                    if (nstaged > SmallStageQueue::CAP - 64) {
+                        stage_flush(a, sq, nstaged, lane, lc, pace);
+                        nstaged = 0;
                     }
                 }
             }
-            cur = nxt;
-        }
+        };
+        // groups of four where that gives all waves something, else of two
+        if (nblocks >= 3 * LDSK_WAVES)
+            for (int b = 4 * wave; b < nblocks; b += 4 * LDSK_WAVES) group_of(std::integral_constant<int, 4>(), b);
+        else
+            for (int b = 2 * wave; b < nblocks; b += 2 * LDSK_WAVES) group_of(std::integral_constant<int, 2>(), b);
         if (nstaged >= 32) {
             stage_flush(a, sq, nstaged, lane, lc, pace);
             nstaged = 0;
         }
-        if (a.dco && g == 0 && scored) atomicAdd(&a.dco[qid], (unsigned long long)scored);
+        if (a.dco && half == 0 && scored) atomicAdd(&a.dco[q0], (unsigned long long)scored);
     }
     if (nstaged > 0) stage_flush(a, sq, nstaged, lane, lc, pace);
     // (a wave that never had a unit wrote nothing, and the chunk of its index may be another wave's)
@@ -1679,38 +1675,26 @@ int rairs_launch_sample_scores(const IndexView &v, const uint8_t *lut, int sampl
     return RAIRS_OK;
 }
 
-bool rairs_mfma_supported(const IndexView &v)
-{
-    return v.T >= 1 && v.nd * 8 * 64 * 16 <= 128 * 1024;    // tables of a tile must fit 128 KB of LDS
-}
+bool rairs_mfma_supported(const IndexView &v) { return v.T >= 1 && v.nd <= 16; }
 
 bool rairs_mfma_reg_tables(const IndexView &v) { return v.nd <= 4; }
 
 // persistent grids: 256 compute units x 2 workgroups of 4 waves with the tables in registers; one
-// workgroup per compute unit, with as many waves as LDS leaves room for, with the tables in LDS
-static void scan_launch_shape(const IndexView &v, bool *reg_tables, unsigned *grid, int *lds_waves,
-                              size_t *table_bytes)
+// workgroup of LDSK_WAVES waves per compute unit with the tables in LDS
+static void scan_launch_shape(const IndexView &v, bool *reg_tables, unsigned *grid)
 {
     *reg_tables = rairs_mfma_reg_tables(v);
     *grid = *reg_tables ? 512u : 256u;
-    *table_bytes = (size_t)v.nd * 8 * 64 * 16;
-    int w = 16;
-    while (w > 4 && *table_bytes + (size_t)w * sizeof(SmallStageQueue) > 158 * 1024) w >>= 1;
-    *lds_waves = w;
 }
 
 // Most waves that can own chunks of the survivor log at once when the pass has at most `units` units.
 int64_t rairs_scan_log_waves(const IndexView &v, int64_t units)
 {
-    bool reg_tables;
-    unsigned gridx;
-    int lds_waves;
-    size_t table_bytes;
-    scan_launch_shape(v, &reg_tables, &gridx, &lds_waves, &table_bytes);
-    // (Programs size workspaces by this, and the few-query search has to fit into them: shapes that have come to
-    // the tables in registers since keep the figure of the tables in LDS, which is the larger one.)
-    if (v.M == 16 || v.M == 48 || v.M == 64) return units < (int64_t)gridx * (WG / 64) ? units : (int64_t)gridx * (WG / 64);
-    return (units < 256 ? units : 256) * lds_waves;
+    // 2,048 with the tables in registers, eight for each of 256 workgroups with the tables in LDS.  (Programs size
+    // workspaces by this, and the few-query search has to fit into them: but for three shapes the figure stays that
+    // of sixteen waves a workgroup.)
+    if (v.M == 16 || v.M == 48 || v.M == 64) return units < 2048 ? units : 2048;
+    return (units < 256 ? units : 256) * 16;
 }
 
 int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
@@ -1719,12 +1703,10 @@ int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
     if (np <= 0) return RAIRS_OK;
     bool reg_tables;
     unsigned gridx;
-    int lds_waves;
-    size_t table_bytes;
-    scan_launch_shape(v, &reg_tables, &gridx, &lds_waves, &table_bytes);
-    const uint32_t nwaves = gridx * (reg_tables ? WG / 64 : lds_waves);
+    scan_launch_shape(v, &reg_tables, &gridx);
+    const uint32_t nwaves = gridx * (reg_tables ? WG / 64 : LDSK_WAVES);
     // who starts on a unit of its own index, and with how many waves (see log_first_free)
-    const uint32_t starters = reg_tables ? nwaves : gridx, waves_each = reg_tables ? 1u : (uint32_t)lds_waves;
+    const uint32_t starters = reg_tables ? nwaves : gridx, waves_each = reg_tables ? 1u : (uint32_t)LDSK_WAVES;
     if (a.log_chunks < 2) {
         rairs_set_error("survivor log of %d chunks", a.log_chunks);
         return RAIRS_EINVAL;
@@ -1789,9 +1771,7 @@ int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_
     }
     bool reg_tables;
     unsigned gridx;
-    int lds_waves;
-    size_t table_bytes;
-    scan_launch_shape(v, &reg_tables, &gridx, &lds_waves, &table_bytes);
+    scan_launch_shape(v, &reg_tables, &gridx);
     const dim3 grid(gridx);
     if (ev) RAIRS_HIP(hipEventRecord(ev[0], s));
     switch (v.nd) {
@@ -1800,10 +1780,10 @@ int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_
     case 3: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<3, true> : scan_mfma_kernel<3, false>), grid, dim3(WG), 0, s, v, a); break;
     case 4: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<4, true> : scan_mfma_kernel<4, false>), grid, dim3(WG), 0, s, v, a); break;
     default: {
-        const size_t lds = table_bytes + (size_t)lds_waves * sizeof(SmallStageQueue);
-        RAIRS_HIP(hipFuncSetAttribute((const void *)scan_mfma_lds_kernel,
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(scan_mfma_lds_kernel, grid, dim3(64 * lds_waves), lds, s, v, a);
+        const size_t lds = (size_t)ldsk_lds_ops(v.nd) * 2048 + LDSK_WAVES * sizeof(SmallStageQueue);
+        const auto kernel = v.nd < 16 ? scan_mfma_lds_kernel<false> : scan_mfma_lds_kernel<true>;
+        RAIRS_HIP(hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * LDSK_WAVES), lds, s, v, a);
     }
     }
     if (ev) RAIRS_HIP(hipEventRecord(ev[1], s));
