@@ -22,10 +22,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-# MI355X matrix peaks for int8: dense 5.0 POP/s; the 2:4-sparse instruction v_smfmac_i32_32x32x64_i8
-# retires twice the K extent of the dense v_mfma_i32_32x32x32_i8 per pass (131,072 ops in 32 cycles
-# per SIMD x 1,024 SIMDs x 2.4 GHz), i.e. twice that for the ops it stands for.
-MFMA_I8_DENSE_POPS = 5.0
+# MI355X matrix peak for int8: the 2:4-sparse instruction v_smfmac_i32_32x32x64_i8 stands for 131,072
+# operations in 32 cycles per SIMD x 1,024 SIMDs x 2.4 GHz.
 MFMA_I8_SPARSE_POPS = 10.1
 # 128 lanes per compute unit and cycle at 2.4 GHz (the 157 TFLOP/s of the vector units at two per lane).
 # Measured on independent values: 58 to 61 T/s for sums and products, 36 to 39 for comparisons and fused
@@ -555,9 +553,8 @@ def main():
 
     # What bounds the dominant kernel.  One table lookup is 16 int8 multiply-adds of the one-hot
     # contraction = 32 ops, so the ops the kernel stands for are items x M x 32 (partly filled
-    # query tiles and list tails count as lost).  The register-table kernel issues the 2:4-sparse
-    # int8 matrix instruction, the LDS-table kernel the dense one: each is priced against the
-    # peak of ITS instruction.  The exact kernel and that of small batches do their lookups on the vector units.
+    # query tiles and list tails count as lost).  Both matrix kernels issue the 2:4-sparse int8
+    # instruction and are priced against its peak.  The exact kernel and that of small batches do their lookups on the vector units.
     kernel = ix.scan_kernel_name()
     kms = stage["scan_kernel"]
     lookups = float(dco.sum()) * w.M
@@ -567,7 +564,7 @@ def main():
     else:
         bound, unit = "mfma", "POP/s"
         achieved = lookups * 32 / (kms * 1e-3) / 1e15
-        peak = MFMA_I8_SPARSE_POPS if kernel == "scan_mfma_kernel" else MFMA_I8_DENSE_POPS
+        peak = MFMA_I8_SPARSE_POPS
     kernel_gbs = scan_bytes / (kms * 1e-3) / 1e9
     traffic = measured_traffic(w.name, chosen, kernel)
     hbm_gbs = None if traffic is None else traffic / (kms * 1e-3) / 1e9
