@@ -293,7 +293,7 @@ int rairs_get_scan_stats(rairs_index_t *h, int64_t *stats);
 
 /*
  * Name of the dominant kernel that SeilSearch launches for this index: "scan_mfma_kernel" (2:4-sparse
- * int8 matrix instruction, tables in registers: M <= 64), "scan_mfma_lds_kernel" (the same, tables
+ * int8 matrix instruction, tables in registers: M = 16, 33 to 64), "scan_mfma_lds_kernel" (the same, tables
  * in LDS) or "scan_exact_kernel" (table lookups on the vector units), by index and
  * scan mode; "few_scan_kernel" (table lookups, several workgroups per query) if the handle's last
  * search took the path of small batches (rairs_scan, rairs_set_scan_mode: the first three again).  A

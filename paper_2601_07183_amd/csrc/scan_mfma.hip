@@ -5,7 +5,7 @@
 // score(query, item) = sum_m lut[query][m][code[item][m]] is a contraction of the lookup tables
 // with a 0/1 expansion of the codes, which the kernels give to the sparse matrix
 // instruction v_smfmac_i32_32x32x64_i8 in a form that has nothing to look up (selectors, below).
-// The LDS-table kernel (M > 64) does the same with the tables in LDS.
+// The LDS-table kernel (other M) does the same with the tables in LDS.
 // Integer arithmetic throughout, so the scores equal the plain 16-bit sums bit for bit.
 //
 // Work is cut into units (list L, tile of <= 32 queries probing L, run of parts of the list; a part
@@ -1273,7 +1273,7 @@ __global__ __launch_bounds__(WG) void select_wave_kernel(IndexView v, MfmaScanAr
 // (Queries with more survivors than a wave holds are left on a list for the workgroup-wide select,
 // select_wg.h, which runs in the launch behind this one together with the exact redo.)
 
-// ---- the same scan with the tile's tables in LDS (more than 64 sub-quantizers) -----------------------
+// ---- the same scan with the tile's tables in LDS -----------------------
 //
 // For tables too large for registers (M = 240: 37.5 KB per half wave of queries) the eight waves of a workgroup
 // share one tile.  Its tables sit in LDS as [instruction][16-byte half][lane] (of sixteen dwords of codes
@@ -1677,7 +1677,11 @@ int rairs_launch_sample_scores(const IndexView &v, const uint8_t *lut, int sampl
 
 bool rairs_mfma_supported(const IndexView &v) { return v.T >= 1 && v.nd <= 16; }
 
-bool rairs_mfma_reg_tables(const IndexView &v) { return v.nd <= 4; }
+// Up to 64 sub-quantizers the tables fit into registers.  At two dwords of codes (and below 16 sub-quantizers) the
+// eight waves that share a tile in LDS are faster all the same where a few units hold most survivors, which a wave
+// alone works off one after the other: 26,578 x 48, M = 24, 1,370 queries, 69 probes 326 us in registers, 192 in LDS;
+// 28,000 x 64, M = 32, 1,000 queries, 16 probes 97 and 62; 10,000 queries 228 and 248.
+bool rairs_mfma_reg_tables(const IndexView &v) { return v.nd <= 4 && (v.nd >= 3 || v.M == 16); }
 
 // persistent grids: 256 compute units x 2 workgroups of 4 waves with the tables in registers; one
 // workgroup of LDSK_WAVES waves per compute unit with the tables in LDS
@@ -1774,9 +1778,8 @@ int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_
     scan_launch_shape(v, &reg_tables, &gridx);
     const dim3 grid(gridx);
     if (ev) RAIRS_HIP(hipEventRecord(ev[0], s));
-    switch (v.nd) {
+    switch (reg_tables ? v.nd : 0) {
     case 1: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<1, true> : scan_mfma_kernel<1, false>), grid, dim3(WG), 0, s, v, a); break;
-    case 2: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<2, true> : scan_mfma_kernel<2, false>), grid, dim3(WG), 0, s, v, a); break;
     case 3: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<3, true> : scan_mfma_kernel<3, false>), grid, dim3(WG), 0, s, v, a); break;
     case 4: hipLaunchKernelGGL((a.split_max > 1 ? scan_mfma_kernel<4, true> : scan_mfma_kernel<4, false>), grid, dim3(WG), 0, s, v, a); break;
     default: {
