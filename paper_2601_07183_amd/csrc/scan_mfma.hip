@@ -488,10 +488,11 @@ static __device__ __forceinline__ void stage_flush(const MfmaScanArgs &a, Queue 
     const uint32_t end = lc.used + (uint32_t)n;
     uint32_t next = lc.chunk;
     if (end > LOG_CHUNK) {
-        // the chunk fills up: the rest goes to another
+        // the chunk fills up: the rest goes to another (with no other left this flush is not stored at all, and the
+        // chunk ends where it stood: what reads the log takes a fill's word for it that its entries were written)
         if (lane == 0) {
-            if (lc.chunk < (uint32_t)a.log_chunks) a.chunk_fill[lc.chunk] = LOG_CHUNK;
             next = take_next(a.log_cursor);
+            if (lc.chunk < (uint32_t)a.log_chunks) a.chunk_fill[lc.chunk] = next < (uint32_t)a.log_chunks ? LOG_CHUNK : lc.used;
         }
         next = (uint32_t)__builtin_amdgcn_readfirstlane((int)next);
     }

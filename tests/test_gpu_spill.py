@@ -55,3 +55,39 @@ def _check(counts, queries, redone, d, M):
             assert st["max_survivors"] == max(counts) and st["logged"] == st["survivors"]
     finally:
         ix.free()
+
+
+# A log that runs out of chunks, both scan kernels: every query is redone exactly, no entry is counted that was
+# not written, and nothing is touched outside of the caller's workspace.  One vector 30,016 times in one pair of
+# lists: 21 million entries of 700 queries for a log of at most 17.6 million.  What stands in the workspace
+# beforehand are entries of the first query with a score that no bound lets pass (a table's sums stay below it), so an
+# entry that was read but never written shows as one logged and not among the survivors.
+@pytest.mark.parametrize("M", [4, 34, 48, 64, 240])
+def test_log_runs_out_of_chunks(M):
+    from paper_2601_07183_amd import binding
+    n, nq, bigk, guard = 30_016, 700, 64, 1 << 20
+    rng = np.random.default_rng(M)
+    cents = datagen.random_vectors(63, 2, M)
+    hx = ib.add_vectors(np.tile(datagen.random_vectors(64, 1, M), (n, 1)), cents,
+                        ib.train_pq(datagen.random_vectors(65, 64, M), M, 3, 2), assign=np.tile(np.int32([[0, 1]]), (n, 1)))
+    lut = rng.integers(0, 256, (nq, M, 16), dtype=np.uint8)
+    code = np.empty(M, np.int64)
+    code[0::2], code[1::2] = hx.vec_codes[0] & 15, hx.vec_codes[0] >> 4
+    want = lut[:, np.arange(M), code].astype(np.int64).sum(axis=1)
+    probes = np.tile(np.int32([0, 1]), (nq, 1))
+    ix = binding.Index(hx)
+    try:
+        ix.set_scan_mode(False, list_major=True)
+        size = ix.workspace_bytes(nq, 2, bigk) + 255 & ~255
+        room = torch.full(((size + 2 * guard) // 4,), -65536, dtype=torch.int32, device="cuda")     # {slot, 0xFFFF << 16 | query 0}
+        ix.set_workspace(room.view(torch.uint8)[guard:guard + size])
+        print("case:", M, flush=True)
+        cand, score, dco = (t.cpu().numpy() for t in ix.scan(torch.from_numpy(lut).cuda(), torch.from_numpy(probes).cuda(), bigk))
+        assert (room[:guard // 4] == -65536).all() and (room[(guard + size) // 4:] == -65536).all()
+        assert (cand == np.arange(bigk)).all() and (score == want[:, None]).all() and (dco == n).all()
+        st = ix.scan_stats()
+        print("   ", st, flush=True)
+        assert st["redone"] == nq and st["logged"] < nq * n
+        assert st["logged"] == st["survivors"]
+    finally:
+        ix.free()
