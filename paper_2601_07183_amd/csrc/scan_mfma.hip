@@ -819,9 +819,11 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
     // A flush costs much the same for one row of 64 entries and for three; but what waits in the queues is not
     // counted, so bounds fall later, and with few units a wave or a small bigK so many entries gather above the
     // final bound that buffers overflow.  (1M x 128, 2,999 queries, bigK = 400: 514 us with one row, 473 with two, 460 with
-    // three; 10,000, 100, 1,024 lists of 24 blocks: 302, 280, 280; 3,000, 40, 97 lists of 18: 97, 94, 96, but
-    // queries are redone for 20 us more.)
-    const int flush_above = a.refine_k >= 256 ? 192 : nunits >= 3u * nwaves ? 128 : 64;
+    // three; 300,000 x 96, 2,048 lists, 10,000 queries, 16 probes, bigK = 100, 5,500 units: 235, 204; 200,000 x 128, 400 lists,
+    // 3,000 queries, bigK = 40, 2,000 units: 146, 142, but then the selection takes 20 us more.  At M = 16 a survivor
+    // costs more than the contraction of a block, so bounds come first: 200,000 x 32, 10,000 queries, 32 probes, bigK = 10: 603
+    // with one row, 640 with two.)
+    const int flush_above = ND == 1 ? 64 : a.refine_k >= 256 ? 192 : nunits >= (a.refine_k >= 64 ? 1u : 3u) * nwaves ? 128 : 64;
     uint32_t u = gwave, u_next = gwave + nwaves;       // the counter starts behind both
     auto record = [&](uint32_t i) {
         const scalar_ptr<int32_t> p = as_scalar(a.unit_rec) + (size_t)(i >> slice_shift) * UNIT_REC_WORDS;
@@ -974,8 +976,10 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
             for (int w = 0; w < ND; w++) c[w] = cn[w];
             fetch();
             seg_items += (uint32_t)__popc(masks.y);
-            // (every fourth block is often enough: the bound moves rarely)
-            if (((b - first) & 3) == 0) {
+            // Every second block, at M = 16 every one.  (Every fourth: M = 48, 500 queries, 64 of 400 lists, bigK = 1,000 2,700 us, the
+            // log runs out, for 768; M = 64, 2,000 queries, 32 of 400 lists, bigK = 400 308 us for 289; M = 16, 10,000 queries, 16
+            // of 400 lists 807 us, 727 with every second, 703 with every one.  At M = 48 and 64 there are no registers for every one.)
+            if (((b - first) & (ND == 1 ? 0 : 1)) == 0) {
                 // the accumulators start at -(threshold + 1): a row passes iff it ends up negative
                 if (live) negth = -(bound_next + above + 1);
                 bound_next = __hip_atomic_load(at32(a.bound, q0 * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -1001,7 +1005,8 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
             interleave<Contraction<ND>::FRONT, 3>();
             __builtin_amdgcn_sched_barrier(0);
             k.back(B, x.acc);
-            stage_round(before, pm, here(lane));
+            // (the first round without a look whether there is one to make: five matrix instructions leave no room for it)
+            if (ND > 1) stage_round(before, pm, here(lane));
             interleave<Contraction<ND>::BACK, 4>();
             __builtin_amdgcn_sched_barrier(0);
             // (the next block's codes are waited for here: behind a flush it would be a wait for its stores and
