@@ -397,6 +397,18 @@ static __device__ __forceinline__ uint32_t hist_mul(uint32_t range)
     return (uint32_t)((float)RAIRS_HIST_BINS * 4294967296.0f * __builtin_amdgcn_rcpf((float)(range + 1u)));
 }
 
+// The bound once bins 0 .. b are the first with bigK entries (0xFFFF: none, the last bin also holds scores beyond the range).
+// A score of bin <= b is below (b + 1) 2^32 / mul.  The reciprocal, its two roundings and the
+// truncation leave mul within 2^-21 of BINS 2^32 / (range + 1), which is at least 2^22, so that is less than
+// x + 0.05, x = (b + 1) (range + 1) / BINS <= 65536, and the score at most floor(x + 4 / 64).
+static_assert(RAIRS_HIST_BINS == 64, "the slack is in 64ths");
+static __device__ __forceinline__ uint32_t bound_at_bin(uint32_t b, uint32_t range)
+{
+    if (b >= RAIRS_HIST_BINS - 1) return 0xFFFFu;
+    const uint32_t edge = ((b + 1u) * (range + 1u) + 4u) / RAIRS_HIST_BINS;
+    return edge < 0xFFFFu ? edge : 0xFFFFu;
+}
+
 // Tightest bound the histogram of query `qid` proves: the histogram counts queue entries, so once
 // bins 0..b hold >= bigK of them nothing scoring above the top edge of bin b can be among the
 // bigK best.
@@ -422,13 +434,7 @@ static __device__ __forceinline__ uint32_t histogram_bound(const MfmaScanArgs &a
             cum += h[i].w; b += cum < need ? 1 : 0;
         }
     }
-    if (b >= RAIRS_HIST_BINS - 1) return 0xFFFFu;      // the last bin also holds scores beyond the range
-    // A score of bin <= b is below (b + 1) 2^32 / mul.  The reciprocal, its two roundings and the
-    // truncation leave mul within 2^-21 of BINS 2^32 / (range + 1), which is at least 2^22, so that is less than
-    // x + 0.05, x = (b + 1) (range + 1) / BINS <= 65536, and the score at most floor(x + 4 / 64).
-    static_assert(RAIRS_HIST_BINS == 64, "the slack is in 64ths");
-    const uint32_t edge = ((uint32_t)(b + 1) * (range + 1u) + 4u) / RAIRS_HIST_BINS;
-    return edge < 0xFFFFu ? edge : 0xFFFFu;
+    return bound_at_bin((uint32_t)b, range);
 }
 
 // A passing (item, query) pair waits in a per-wave LDS queue until enough have gathered; then the
@@ -1038,6 +1044,30 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
     }
     // (a wave that never had a unit wrote nothing, and the chunk of its index may be another wave's)
     if (lane == 0 && lc.used > 0 && lc.chunk < (uint32_t)a.log_chunks) a.chunk_fill[lc.chunk] = lc.used;
+}
+
+// The bounds once more before the log is read, a wave per query: by now every survivor is counted.  The scanning waves
+// refresh a bound now and then, and a batch of few units is over before most of them have: of what they logged so
+// much stays at or below a stale bound that queries leave the wave's select for the workgroup's, or for the exact redo.
+// (28,000 x 100, M = 50, 500 queries, 64 of 97 lists, bigK = 1,000: 1,400 us, two queries redone, now 630; M = 48, 3,000 queries, 4 probes,
+// bigK = 40: 183 us, now 166.)  Few lists and a small bigK cannot fill a buffer: there its launch, 3 us, is saved.
+static bool final_bound_pays(const MfmaScanArgs &a) { return a.refine_k >= 32 || a.nprobe >= 8; }
+__global__ __launch_bounds__(WG) void final_bound_kernel(MfmaScanArgs a)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t q = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
+    if (q >= a.nq) return;
+    uint32_t upto = a.hist[q * RAIRS_HIST_BINS + lane];        // a bin per lane
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t x = __shfl_up(upto, off);
+        if (lane >= off) upto += x;
+    }
+    const uint32_t b = (uint32_t)__popcll(__ballot(upto < (uint32_t)a.refine_k));
+    if (lane == 0) {
+        const int32_t nb = (int32_t)bound_at_bin(b, hist_range((uint32_t)a.tau[q]));
+        if (nb < 0xFFFF && nb < a.bound[q]) a.bound[q] = nb;
+    }
 }
 
 // Distribute the survivor log to the per-query buffers (a workgroup takes one chunk at a time).  A chunk holds
@@ -1802,6 +1832,8 @@ int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_
 
 int rairs_launch_select(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
 {
+    if (final_bound_pays(a))
+        hipLaunchKernelGGL(final_bound_kernel, dim3((unsigned)((a.nq + WG / 64 - 1) / (WG / 64))), dim3(WG), 0, s, a);
     hipLaunchKernelGGL(collect_kernel, dim3((unsigned)(a.log_chunks < 4096 ? a.log_chunks : 4096)),
                        dim3(COLLECT_WG), 0, s, a);
     const int cap = rairs_select_wave_cap(a.refine_k);
