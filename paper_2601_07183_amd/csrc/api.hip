@@ -623,11 +623,15 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
         const int64_t active = rairs_scan_log_waves(v, units);
         w.log_chunks = (int)((nq * log_per_query_for(refine_k) + RAIRS_LOG_CHUNK - 128) / (RAIRS_LOG_CHUNK - 127) +
                              2 * active + 16);
-        // Units are cut into as many slices as there are chunks for, four at most, and no further than leaves a query
-        // with 16 pieces: the waves at a query's pieces learn of each other's survivors late, and with more of them
-        // at once so much stays above the final bound that buffers overflow.  (28,000 x 32, 97 lists: 1,000
-        // queries x 4 lists 236 us whole and 200 in four slices; 300 queries x 16 lists 252 and 286.)
-        w.split_max = nprobe <= 4 ? 4 : nprobe <= 8 ? 2 : 1;
+        // Units are cut into as many slices as there are chunks for, four at most.  The waves at a query's pieces
+        // learn of each other's survivors late, every slice loads its tables, and a long list is in several units already: so
+        // not beyond four probes a query, with two slices six, and eight where a unit has many queries and survivors to
+        // share out, and not where lists are longer than a part and a half.  (us whole / sliced, M = 48 to 64 unless said.
+        // 97 lists of 18 blocks, bigK = 100: 1,000 queries x 4 probes 230, 195; x 6 237, 202; x 8 240, 205; 100 x 8 145, 158;
+        // 3,000 x 8, bigK = 10 158, 168; 400 lists of 31, bigK = 100: 300 x 4 212, 182; 1,000 x 6 211, 203; 1,000 x 8 212, 223.
+        // 1,024 lists of 61: 300 x 1 195, 207.  M = 16, 400 lists: 1,000 x 1 289, 235, in four slices 217.)
+        w.split_max = nprobe <= 4 ? 4 : nprobe <= 6 || (nprobe <= 8 && refine_k >= 64 && nq * nprobe >= 24 * (int64_t)v.nlist) ? 2 : 1;
+        if (2 * v.nblocks > 3 * (int64_t)RAIRS_PART_BLOCKS * v.nlist) w.split_max = 1;
         if (nq * nprobe / 32 > 1024) w.split_max = 1;      // (the 2,048 waves have a unit each)
         if ((int64_t)w.split_max * units > 2 * active && 2 * active < 2048) w.split_max = (int)(2 * active / (units > 0 ? units : 1));
         if (!rairs_mfma_reg_tables(v)) w.split_max = 1;

@@ -107,6 +107,8 @@ static __device__ __forceinline__ int units_of(int nqueries, int part_cnt, int u
 // not walk unit -> list -> directory entry -> parts at the head of every unit: the list, the tile,
 // the unit's segments [seg0, seg1) as absolute segment numbers, and where the list's queries are.
 #define UNIT_REC_WORDS 8
+#define UNIT_MAX_SEGS 32     // runs per unit: up to 4 parts of RAIRS_PART_SEGS runs
+static_assert(4 * RAIRS_PART_SEGS == UNIT_MAX_SEGS, "a unit's runs fit half a wave");
 static __device__ __forceinline__ void write_unit_rec(const IndexView &v, int32_t *unit_rec, int u, int L,
                                                       int first_unit_of_list, int qbase, int qn, int unit_parts)
 {
@@ -870,13 +872,22 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
             return e;
         };
         if (slices > 1u) {                             // uniform
-            int n = 0;
-            for (int i = seg0; i < seg1; i++) n += as_scalar(v.segs)[i].nblk;
-            const int s = (int)(u & (slices - 1u));
+            // (a run per lane: one after the other, their lengths are a chain of up to 32 scalar loads)
+            const int i = here(lane), runs = seg1 - seg0;
+            int upto = i < runs ? v.segs[seg0 + i].nblk : 0;           // blocks of runs 0 .. i
+#pragma unroll
+            for (int off = 1; off < UNIT_MAX_SEGS; off <<= 1) {
+                const int x = __shfl_up(upto, off);
+                if (i >= off) upto += x;
+            }
+            const int n = __builtin_amdgcn_readlane(upto, UNIT_MAX_SEGS - 1), s = (int)(u & (slices - 1u));
             first = (n * s) >> slice_shift;
             left = ((n * (s + 1)) >> slice_shift) - first;
-            if (left > 0)
-                while (first >= as_scalar(v.segs)[seg0].nblk) first -= as_scalar(v.segs)[seg0++].nblk;
+            const int over = __popcll(__builtin_amdgcn_ballot_w64(i < runs && upto <= first));     // runs before the slice
+            if (over > 0 && left > 0) {
+                first -= __builtin_amdgcn_readlane(upto, over - 1);
+                seg0 += over;
+            }
         }
         if (left > 0) {
         const int unit_lane = here(lane);
@@ -1319,7 +1330,6 @@ __global__ __launch_bounds__(WG) void select_wave_kernel(IndexView v, MfmaScanAr
 // two.)  Codes come a pair of dwords ahead.  Survivors, bounds and the log work as in scan_mfma_kernel.
 // The dense instruction with one-hot rows from LDS, two reads each, took all of the LDS's time: 200,000 x 960,
 // M = 240, 1,000 queries, 45 probes: 865 us, now 570.
-#define LDSK_MAX_SEGS 32    // runs per unit: up to 4 parts of RAIRS_PART_SEGS runs
 #define LDSK_WAVES 8
 // matrix instructions a block whose tables are in LDS
 static __host__ __device__ __forceinline__ int ldsk_lds_ops(int nd) { return 5 * (nd < 16 ? nd : 15); }
@@ -1327,7 +1337,7 @@ template <bool LAST_IN_REGS>                           // sixteen dwords of code
 __global__ __launch_bounds__(64 * LDSK_WAVES, 2) void scan_mfma_lds_kernel(IndexView v, MfmaScanArgs a)
 {
     extern __shared__ __align__(16) unsigned char dyn_lds[];
-    __shared__ SegEntry segs_s[LDSK_MAX_SEGS];
+    __shared__ SegEntry segs_s[UNIT_MAX_SEGS];
     __shared__ uint32_t s_unit;
     const int ND = v.nd, ops = ldsk_lds_ops(ND);
     v4i *Bl = (v4i *)dyn_lds;                           // [ops][2][64]
@@ -1347,7 +1357,7 @@ __global__ __launch_bounds__(64 * LDSK_WAVES, 2) void scan_mfma_lds_kernel(Index
         const uint32_t u = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_unit);
         if (u >= nunits) break;                        // uniform for the workgroup; the counter only grows
         const int32_t *rec = a.unit_rec + (size_t)u * UNIT_REC_WORDS;
-        const int tile = rec[1], seg0 = rec[2], nseg = rec[3] - seg0;      // nseg <= LDSK_MAX_SEGS
+        const int tile = rec[1], seg0 = rec[2], nseg = rec[3] - seg0;      // nseg <= UNIT_MAX_SEGS
         const int q_at = rec[4] + tile * 32, qn = rec[5] - tile * 32;
         if ((int)threadIdx.x < nseg) segs_s[threadIdx.x] = v.segs[seg0 + threadIdx.x];
         const int qid = j < qn ? a.qlist[q_at + j] : -1;
