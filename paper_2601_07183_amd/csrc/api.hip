@@ -949,7 +949,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     }
     MfmaScanArgs ma;
     memset(&ma, 0, sizeof(ma));
-    ma.lut = lut; ma.tables = (const uint8_t *)(ws + w.tables); ma.probe_ids = probe_ids; ma.bitmap = bitmap; ma.bmwords = w.bmwords;
+    ma.lut = lut; ma.tables = (uint8_t *)(ws + w.tables); ma.probe_ids = probe_ids; ma.bitmap = bitmap; ma.bmwords = w.bmwords;
     ma.nprobe = nprobe; ma.refine_k = refine_k; ma.p_first = 1; ma.nq = n;
     ma.any_order = any_order ? 1 : 0;
     ma.lcount = (int32_t *)(ws + w.lcount); ma.loff = (int32_t *)(ws + w.loff);
@@ -1005,7 +1005,6 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     uint16_t *s_scores = (uint16_t *)(ws + w.s_scores);
     if (overlap) {
         if ((rc = rairs_launch_group(v, ma, h->side))) return rc;
-        if ((rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), h->side))) return rc;
         RAIRS_HIP(hipEventRecord(h->ev_group, h->side));
     }
     if (grouped && probed_on_side) {
@@ -1034,10 +1033,7 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
                                                (int32_t *)(ws + w.tau), ma.bound, s)))
         return rc;
     if (overlap) RAIRS_HIP(hipStreamWaitEvent(s, h->ev_group, 0));
-    else {
-        if ((rc = rairs_launch_group(v, ma, s))) return rc;
-        if ((rc = rairs_launch_scan_tables(v, lut, n, (uint8_t *)(ws + w.tables), s))) return rc;
-    }
+    else if ((rc = rairs_launch_group(v, ma, s))) return rc;
     if ((rc = rairs_launch_scan_mfma(v, ma, s, ev))) return rc;
     if ((rc = rairs_launch_select(v, ma, s))) return rc;
     // a query with more entries at or below its final bound than buffer and spill hold (thousands of

@@ -213,7 +213,7 @@ int rairs_launch_sample_scores(const IndexView &v, const uint8_t *lut, int sampl
 // list-major MFMA scan (scan_mfma.hip)
 struct MfmaScanArgs {
     const uint8_t *lut;
-    const uint8_t *tables;        // the same in the form of the scan with tables in registers (rairs_launch_scan_tables)
+    uint8_t *tables;              // the same in the form that the scan's matrix instructions take, made with the grouping
     const int32_t *probe_ids;
     const uint32_t *bitmap;
     int bmwords, nprobe, refine_k;
@@ -252,10 +252,7 @@ struct MfmaScanArgs {
 bool rairs_mfma_supported(const IndexView &v);
 bool rairs_mfma_reg_tables(const IndexView &v);    // the tile's tables fit the registers (sparse instruction)
 int64_t rairs_scan_log_waves(const IndexView &v, int64_t units);    // half of the chunks that waves may hold, for a pass of at most `units` units
-// the lookup tables in the form that the register-table scan's matrix instructions take
-size_t rairs_scan_tables_bytes(const IndexView &v, int64_t nq);
-int rairs_launch_scan_tables(const IndexView &v, const uint8_t *lut, int64_t nq, uint8_t *tables, hipStream_t s);
-// grouping of the (query, probed list) pairs by list and the unit table, then the scan itself
+// grouping of the (query, probed list) pairs by list, the unit table and the scan's form of the tables, then the scan itself
 int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s);
 int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_t s, hipEvent_t *ev);
 int rairs_launch_select(const IndexView &v, const MfmaScanArgs &a, hipStream_t s);

@@ -59,21 +59,6 @@ static __device__ __forceinline__ uint32_t log_first_free(uint32_t nunits, uint3
     return (n < starters ? n : starters) * waves_each;
 }
 
-// The scanning waves start on the units numbered by their own index (a second one each at index +
-// nwaves with the tables in registers), so the unit counter starts behind those.
-__global__ void lm_zero_kernel(int32_t *lcount, int32_t *lcursor, int nlist, uint32_t *next_task, uint32_t *surv_cnt,
-                               int64_t nq, uint32_t *chunk_fill, int log_chunks, uint32_t *log_cursor,
-                               uint32_t *log_overflow, uint32_t first_task, unsigned long long *dco,
-                               uint32_t *work)
-{
-    int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid < nlist) { lcount[gid] = 0; lcursor[gid] = 0; }
-    if (gid < nq) { surv_cnt[gid] = 0; if (dco) dco[gid] = 0ull; }
-    if (gid < log_chunks) chunk_fill[gid] = 0;
-    if (gid == 0) { *next_task = first_task; *log_cursor = 0u; log_overflow[0] = 0; log_overflow[1] = 0; }   // (the cursor: set again with the unit count)
-    if (gid == 0) { work[0] = 0u; work[1 + nq] = 0u; }   // the two lists of queries for the kernels behind the scan
-}
-
 __global__ void lm_count_kernel(const int32_t *__restrict__ probe_ids, int64_t nq, int nprobe,
                                 int p_first, int nlist, int32_t *lcount)
 {
@@ -659,13 +644,11 @@ static __device__ __forceinline__ int load_byte_tables(const uint8_t *lut, uint3
 // load_byte_tables describes, then what a contraction is above the score.
 static __host__ __device__ __forceinline__ int scan_tables_stride(int nd) { return nd * 320 + 16; }
 
-// One wave per query, a lane per sub-quantizer.
-__global__ __launch_bounds__(WG) void scan_tables_kernel(const uint8_t *__restrict__ lut, int M, int nd, int64_t nq,
+// One wave makes those of query q, a lane per sub-quantizer.
+static __device__ __forceinline__ void write_scan_tables(const uint8_t *__restrict__ lut, int M, int nd, int64_t q,
                                                          uint8_t *__restrict__ tables)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t q = (int64_t)blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
-    if (q >= nq) return;
     const int stride = scan_tables_stride(nd);
     uint32_t *out = (uint32_t *)(tables + (size_t)q * stride);
     int above = 0;
@@ -695,6 +678,25 @@ __global__ __launch_bounds__(WG) void scan_tables_kernel(const uint8_t *__restri
     }
     const uint32_t sum = wave_sum_u32((uint32_t)above);
     if (lane == 0) out[nd * 80] = sum;
+}
+
+// First kernel of the grouping: `zero_wgs` workgroups clear the counters, the others make the scan's tables, a wave per
+// query.  (Nobody before the scan reads either.  A launch of its own for the tables is 5 us more on the way to the scan.)
+// The scanning waves start on the units numbered by their own index (a second one each at index +
+// nwaves with the tables in registers), so the unit counter starts behind those.
+__global__ __launch_bounds__(WG) void lm_begin_kernel(int zero_wgs, IndexView v, MfmaScanArgs a, uint32_t first_task)
+{
+    if ((int)blockIdx.x >= zero_wgs) {
+        const int64_t q = (int64_t)(blockIdx.x - zero_wgs) * (WG / 64) + (threadIdx.x >> 6);
+        if (q < a.nq) write_scan_tables(a.lut, v.M, v.nd, q, a.tables);
+        return;
+    }
+    const int64_t gid = (int64_t)blockIdx.x * WG + threadIdx.x;
+    if (gid < v.nlist) { a.lcount[gid] = 0; a.lcursor[gid] = 0; }
+    if (gid < a.nq) { a.surv_cnt[gid] = 0; if (a.dco) a.dco[gid] = 0ull; }
+    if (gid < a.log_chunks) a.chunk_fill[gid] = 0;
+    if (gid == 0) { *a.next_task = first_task; *a.log_cursor = 0u; a.log_overflow[0] = 0; a.log_overflow[1] = 0; }   // (the cursor: set again with the unit count)
+    if (gid == 0) { a.work[0] = 0u; a.work[1 + a.nq] = 0u; }   // the two lists of queries for the kernels behind the scan
 }
 
 template <int ND>
@@ -790,7 +792,7 @@ using scalar_ptr = const __attribute__((address_space(4))) T *;
 template <typename T>
 static __device__ __forceinline__ scalar_ptr<T> as_scalar(const T *p) { return (scalar_ptr<T>)(uintptr_t)p; }
 
-// What bounds it: the matrix cores' power (2 waves a SIMD; see scan_tables_kernel) and the survivors' vector
+// What bounds it: the matrix cores' power (2 waves a SIMD; see write_scan_tables) and the survivors' vector
 // instructions, which run beside them a block behind.  Before (one-hot rows looked up in LDS, survivors after
 // each block): 1M x 128, M = 64, 10,000 queries, 23 probes: 695 us, now 645; 2,999 queries, bigK = 400: 515, 460;
 // 1M x 96, M = 48: 430, 400; 100 probes of 16,384 lists: 3.96 ms, 3.75.
@@ -1764,9 +1766,8 @@ int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
     const int64_t pairs = a.nq * np;
     int64_t nz = v.nlist > a.nq ? v.nlist : a.nq;
     nz = nz > a.log_chunks ? nz : a.log_chunks;
-    hipLaunchKernelGGL(lm_zero_kernel, dim3((unsigned)((nz + 255) / 256)), dim3(256), 0, s, a.lcount,
-                       a.lcursor, v.nlist, a.next_task, a.surv_cnt, a.nq, a.chunk_fill, a.log_chunks,
-                       a.log_cursor, a.log_overflow, reg_tables ? 2 * nwaves : gridx, a.dco, a.work);
+    const unsigned zero_wgs = (unsigned)((nz + WG - 1) / WG), table_wgs = (unsigned)((a.nq + WG / 64 - 1) / (WG / 64));
+    hipLaunchKernelGGL(lm_begin_kernel, dim3(zero_wgs + table_wgs), dim3(WG), 0, s, (int)zero_wgs, v, a, reg_tables ? 2 * nwaves : gridx);
     const bool lds_group = v.nlist <= LM_LDS_NLIST;
     const int qb = LM_PAIRS / np > 0 ? LM_PAIRS / np : 1;
     const unsigned lgrid = (unsigned)((a.nq + qb - 1) / qb);
@@ -1795,15 +1796,6 @@ int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
         hipLaunchKernelGGL(lm_fill_kernel, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, s,
                            a.probe_ids, a.nq, a.nprobe, a.p_first, v.nlist, a.loff, a.lcursor, a.qlist);
     }
-    RAIRS_HIP(hipGetLastError());
-    return RAIRS_OK;
-}
-
-size_t rairs_scan_tables_bytes(const IndexView &v, int64_t nq) { return (size_t)nq * scan_tables_stride(v.nd); }
-
-int rairs_launch_scan_tables(const IndexView &v, const uint8_t *lut, int64_t nq, uint8_t *tables, hipStream_t s)
-{
-    hipLaunchKernelGGL(scan_tables_kernel, dim3((unsigned)((nq + WG / 64 - 1) / (WG / 64))), dim3(WG), 0, s, lut, v.M, v.nd, nq, tables);
     RAIRS_HIP(hipGetLastError());
     return RAIRS_OK;
 }
