@@ -675,32 +675,28 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
 // large lists more often than small ones: the blocks of a probed list are taken as the list's that an
 // average block is in, which is within a factor of two of what was counted (the plain mean is ten times too
 // low on the 200,000 x 960 index below).  The list-major search of a small batch costs
-// its dozen dependent kernels: some 90 us, more with bigK, with more than four dwords of codes, with
-// eight probed lists and more and with a large directory; and several times that where most lists
-// are too short to give the scan a bound (fewer than two thirds of bigK items).  FEW_MAX_WORK, in which a
-// query counts 512 and a block the mean, is a limit on top (beyond it some batches over short lists with
-// many probes would gain as well).
+// its dozen dependent kernels: some 80 us, more with bigK, with a large directory, with every probe (up to 64 counted) and,
+// where probes have more than four dwords of codes each, with those.
+// The constants are fitted to 3,146 pairs of times (23 indexes of M = 4 to 240, 25 to 10,000 queries, 1 to 64 probes, bigK 10 to
+// 1,000): 146 choices are wrong by more than a tenth, 41 by more than a half, all of these batches over crowded short lists
+// that the few-query search would finish sooner (the worst 2.2 ms against 9.4); the few-query search is nowhere
+// wrongly taken by more than 1.37.
 // Measured (few-query / list-major, us; the line lies between the last two figures of each list):
-//   1M x 128, 1,024 lists    nprobe 23: 100 queries 104 / 362, 400: 350 / 335, 800: 633 / 342
-//                            nprobe 1: 1,600 queries 195 / 279, 3,200: 364 / 329
-//   2M x 96, 4,096 lists     nprobe 39: 400 queries 170 / 314, 800: 347 / 301
-//   1M x 128, 16,384 lists   nprobe 1, bigK 10: 400 queries 180 / 240, 3,200: 1,161 / 382 (800: 334 / 265)
-//   200,000 x 960, M = 240   nprobe 45: 100 queries 452 / 873, 200: 843 / 732; nprobe 1: 800: 319 / 396,
-//                            1,600: 565 / 470
-//   20,000 x 32, M = 16      nprobe 4: 1,600 queries 134 / 245, 6,400: 368 / 302
-#define FEW_MAX_WORK 2500000ll
-#define FEW_QUERY_WORK 512ll
+//   1M x 128, 1,024 lists    nprobe 45: 200 queries 327 / 366, 400: 552 / 381
+//                            nprobe 1: 1,600 queries 196 / 266, 3,200: 362 / 319
+//   500,000 x 96, 4,096 lists  nprobe 45: 800 queries 205 / 278, 1,600: 358 / 320
+//   1M x 128, 16,384 lists   nprobe 1, bigK 10: 400 queries 180 / 225, 800: 318 / 250
+//   200,000 x 960, M = 240   nprobe 45: 100 queries 453 / 694, 200: 799 / 616
+//                            nprobe 1: 400 queries 174 / 300, 800: 317 / 318
+//   60,000 x 256, M = 128    nprobe 8, bigK 10: 800 queries 156 / 158, 1,600: 265 / 163
+//   20,000 x 32, M = 16      nprobe 4: 3,200 queries 235 / 287, 6,400: 393 / 359
 static bool few_pays(const rairs_index *h, int64_t nq, int nprobe, int refine_k)
 {
     const IndexView &v = h->v;
-    const int64_t mean_blocks = (h->seg_blocks_total * nprobe + v.nlist - 1) / v.nlist;
-    if (nq * (mean_blocks * v.nd + FEW_QUERY_WORK) > FEW_MAX_WORK) return false;
     const int64_t blocks = std::min(std::min(h->seg_blocks_seen * nprobe, h->seg_blocks_total), (int64_t)h->seg_blocks_max[nprobe]);
     const int64_t work = blocks * v.nd + 350 + v.nlist / 7 + (int64_t)v.nlist * v.d / 550 + 5ll * refine_k + 5ll * v.M;
-    int64_t limit = 1800000 + 24000ll * refine_k + 90ll * v.nlist;
-    if (v.nd > 4) limit += 2400000;
-    if (nprobe >= 8) limit += v.nd > 4 ? 4800000 : 1450000;
-    if (nprobe > 1 && 48 * h->seg_blocks_total < (int64_t)refine_k * v.nlist) limit *= 4;
+    const int64_t more = v.nd > 4 ? v.nd - 4 : 0, probes = (nprobe < 64 ? nprobe : 64) - 1;
+    const int64_t limit = 1650000 + 25000ll * refine_k + 130ll * v.nlist + 30000 * more + (17000 + 8500 * more) * probes;
     return nq * work <= limit;
 }
 #define FEW_TARGET_WGS 2048         // scan workgroups that a batch is spread over
