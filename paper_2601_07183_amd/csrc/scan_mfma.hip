@@ -834,6 +834,11 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
     // costs more than the contraction of a block, so bounds come first: 200,000 x 32, 10,000 queries, 32 probes, bigK = 10: 603
     // with one row, 640 with two.)
     const int flush_above = ND == 1 ? 64 : a.refine_k >= 256 ? 192 : nunits >= (a.refine_k >= 64 ? 1u : 3u) * nwaves ? 128 : 64;
+    // A unit's bounds are looked up every second block, at M = 16 every one, and with many units a wave every fourth: by then they
+    // have settled.  (Every fourth / second: M = 48, 500 queries, 64 of 400 lists, bigK = 1,000 2,700 us, the log runs out, 768;
+    // M = 64, 2,000 queries, 32 of 400 lists, bigK = 400 308, 289; 2M x 96, 4,096 lists, 10,000 queries, 39 probes 382, 402; M = 16,
+    // 10,000 queries, 16 of 400 lists 807, 727 and with every one 703.  At M = 48 and 64 there are no registers for every one.)
+    const int bound_mask = ND == 1 ? 0 : nunits >= 3u * nwaves ? 3 : 1;
     uint32_t u = gwave, u_next = gwave + nwaves;       // the counter starts behind both
     auto record = [&](uint32_t i) {
         const scalar_ptr<int32_t> p = as_scalar(a.unit_rec) + (size_t)(i >> slice_shift) * UNIT_REC_WORDS;
@@ -995,10 +1000,7 @@ __global__ __launch_bounds__(WG, 2) void scan_mfma_kernel(IndexView v, MfmaScanA
             for (int w = 0; w < ND; w++) c[w] = cn[w];
             fetch();
             seg_items += (uint32_t)__popc(masks.y);
-            // Every second block, at M = 16 every one.  (Every fourth: M = 48, 500 queries, 64 of 400 lists, bigK = 1,000 2,700 us, the
-            // log runs out, for 768; M = 64, 2,000 queries, 32 of 400 lists, bigK = 400 308 us for 289; M = 16, 10,000 queries, 16
-            // of 400 lists 807 us, 727 with every second, 703 with every one.  At M = 48 and 64 there are no registers for every one.)
-            if (((b - first) & (ND == 1 ? 0 : 1)) == 0) {
+            if (((b - first) & bound_mask) == 0) {
                 // the accumulators start at -(threshold + 1): a row passes iff it ends up negative
                 if (live) negth = -(bound_next + above + 1);
                 bound_next = __hip_atomic_load(at32(a.bound, q0 * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
