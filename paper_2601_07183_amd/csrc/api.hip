@@ -543,7 +543,7 @@ static int log_per_query_for(int refine_k)
 
 struct WsLayout {
     size_t dmat, cflags, probe_ids, probe_dists, bitmap, lut, cand, dco;
-    size_t lcount, loff, lcursor, toff, unit_list, unit_rec, next_task, qlist, tau, bound, surv_cnt, flags, work, hist, surv_buf, log, chunk_fill, log_misc, total;
+    size_t lcount, loff, lcursor, toff, unit_rec, next_task, qlist, tau, bound, surv_cnt, flags, work, hist, surv_buf, log, chunk_fill, log_misc, total;
     size_t hmin;                  // 0: none (more lists than RAIRS_HMIN_MAX_NLIST)
     size_t tables;                // of the scan: behind sample scores and minima, in bytes that the survivor buffers get later
     size_t s_off, s_toff, s_q, s_tiles, s_scores, s_first;      // matrix-core sample (0 bytes when not used)
@@ -605,8 +605,7 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     w.lcursor = take((size_t)v.nlist * 4);
     w.toff = take((size_t)(v.nlist + 1) * 4);
     w.next_task = take(4);
-    w.unit_list = take(((size_t)nq * nprobe / 32 + (size_t)v.nlist) * (size_t)max_parts * 4);   // max_parts = most parts in a list
-    w.unit_rec = take(((size_t)nq * nprobe / 32 + (size_t)v.nlist) * (size_t)max_parts * 32);
+    w.unit_rec = take(((size_t)nq * nprobe / 32 + (size_t)v.nlist) * (size_t)max_parts * 32);   // max_parts = most parts in a list
     w.qlist = take((size_t)nq * nprobe * 4);
     w.tau = take((size_t)nq * 4);
     w.bound = take((size_t)nq * 4);
@@ -950,7 +949,6 @@ static int scan_pass(rairs_index *h, char *ws, const WsLayout &w, const uint8_t 
     ma.any_order = any_order ? 1 : 0;
     ma.lcount = (int32_t *)(ws + w.lcount); ma.loff = (int32_t *)(ws + w.loff);
     ma.lcursor = (int32_t *)(ws + w.lcursor); ma.toff = (int32_t *)(ws + w.toff);
-    ma.unit_list = (int32_t *)(ws + w.unit_list);
     ma.unit_rec = (int32_t *)(ws + w.unit_rec);
     {
         // parts per unit: large units save table reloads, small ones keep 2048 waves busy and the

@@ -225,7 +225,6 @@ struct MfmaScanArgs {
     int32_t *lcursor;             // [nlist]
     int32_t *qlist;               // [nq * nprobe] query ids grouped by list
     int32_t *toff;                // [nlist+1] exclusive prefix of work units per list
-    int32_t *unit_list;           // [units] list of every work unit
     int32_t *unit_rec;            // [units][8] {list, tile, first segment, end segment, first query of the list in qlist, its queries, 0, 0}
     int unit_parts;               // parts per unit, 1..4
     int unit_tail_from;           // lists from this one on: single-part units (nlist: none)

@@ -74,7 +74,7 @@ __global__ void lm_count_kernel(const int32_t *__restrict__ probe_ids, int64_t n
 // A unit of work is (list, tile of <= 32 of the queries probing it, run of unit_parts consecutive
 // parts of the list; a part is about 32 blocks, unit_parts is 1..4, smaller when there is little
 // work).  Exclusive prefixes over lists of queries (loff) and units
-// (toff), and the list of every unit; one workgroup of 1024.
+// (toff); one workgroup of 1024.
 // Parts per unit of list L: the lists from `tail_from` on are cut into single parts.  Waves take
 // units in order, so the last ones taken are small and the waves finish closer together (the
 // kernel ends with its slowest wave, and a two-part unit is 0.08 ms of work on the 1M x 128 workload).
@@ -112,7 +112,7 @@ static __device__ __forceinline__ void write_unit_rec(const IndexView &v, int32_
 __global__ __launch_bounds__(1024) void lm_prefix_kernel(IndexView v,
                                                          const int32_t *__restrict__ lcount,
                                                          int32_t *loff, int32_t *lcursor,
-                                                         int32_t *toff, int32_t *unit_list,
+                                                         int32_t *toff,
                                                          int unit_parts, int tail_from, int32_t *unit_rec,
                                                          uint32_t *log_cursor, uint32_t starters, uint32_t waves_each, uint32_t split_max)
 {
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(1024) void lm_prefix_kernel(IndexView v,
 __global__ __launch_bounds__(256) void lm_units_kernel(IndexView v, const int32_t *__restrict__ lcount,
                                                        const int32_t *__restrict__ loff,
                                                        const int32_t *__restrict__ toff,
-                                                       int32_t *unit_list, int unit_parts, int tail_from,
+                                                       int unit_parts, int tail_from,
                                                        int32_t *unit_rec)
 {
     const int L = (int)(blockIdx.x * blockDim.x + threadIdx.x);
@@ -170,10 +170,7 @@ __global__ __launch_bounds__(256) void lm_units_kernel(IndexView v, const int32_
     const int n = lcount[L], tb = toff[L], cb = loff[L];
     const int up = list_unit_parts(L, unit_parts, tail_from);
     const int nu = units_of(n, v.lists[L].part_cnt, up);
-    for (int u = 0; u < nu; u++) {
-        unit_list[tb + u] = L;
-        write_unit_rec(v, unit_rec, tb + u, L, tb, cb, n, up);
-    }
+    for (int u = 0; u < nu; u++) write_unit_rec(v, unit_rec, tb + u, L, tb, cb, n, up);
 }
 
 __global__ void lm_fill_kernel(const int32_t *__restrict__ probe_ids, int64_t nq, int nprobe,
@@ -251,12 +248,12 @@ static __device__ __forceinline__ int wg256_exclusive(int mine, int32_t *wsum, i
 // Second step for directories of up to LM_LDS_NLIST lists.  No separate prefix kernel sits between
 // counting and filling: every workgroup derives the list offsets from the counts itself (a few KB,
 // from L2), and LM_UNIT_WGS extra workgroups (the last ones) write them out for the scan together
-// with the unit table (toff, unit_list).
+// with the unit table (toff, unit_rec).
 __global__ __launch_bounds__(256) void lm_fill_lds_kernel(IndexView v, const int32_t *__restrict__ probe_ids,
                                                           int64_t nq, int nprobe, int p_first,
                                                           const int32_t *__restrict__ lcount,
                                                           int32_t *loff, int32_t *lcursor, int32_t *qlist,
-                                                          int qb, int32_t *toff, int32_t *unit_list,
+                                                          int qb, int32_t *toff,
                                                           int unit_parts, int tail_from, int32_t *unit_rec,
                                                           uint32_t *log_cursor, uint32_t starters, uint32_t waves_each, uint32_t split_max)
 {
@@ -281,7 +278,7 @@ __global__ __launch_bounds__(256) void lm_fill_lds_kernel(IndexView v, const int
     const int nfill = (int)gridDim.x - LM_UNIT_WGS;
     if ((int)blockIdx.x >= nfill) {
         // The unit table: every one of these workgroups derives the unit offsets of all lists
-        // (into LDS), the first writes the offsets out, and each fills its share of unit_list,
+        // (into LDS), the first writes the offsets out, and each fills its share of the records,
         // finding a unit's list by bisection on the offsets.
         const int ub = (int)blockIdx.x - nfill;
         int32_t *toff_s = lm_hist;                     // [nlist]
@@ -312,7 +309,6 @@ __global__ __launch_bounds__(256) void lm_fill_lds_kernel(IndexView v, const int
                 const int mid = (a0 + b0 + 1) >> 1;
                 if (toff_s[mid] <= e) a0 = mid; else b0 = mid - 1;
             }
-            unit_list[e] = a0;
             write_unit_rec(v, unit_rec, e, a0, toff_s[a0], loff_s[a0], lcount[a0], list_unit_parts(a0, unit_parts, tail_from));
         }
         return;
@@ -714,11 +710,12 @@ static __device__ __forceinline__ void load_scan_tables(const uint8_t *tables, u
 // acc += the contraction of a block's codes with the tables, in two parts.
 template <int ND>
 struct Contraction {
+    static_assert(ND == 1 || ND == 3 || ND == 4, "the kernels' shapes");
     static constexpr int FRONT = ND >= 3 ? 10 : 5, BACK = 5 * ND - FRONT;      // matrix instructions
     uint32_t s[2][5];                                  // position words of the two parts
     __device__ __forceinline__ void front_words(const uint32_t (&c)[ND])
     {
-        if (ND > 1) select_words_pair(c[0], c[ND > 1 ? 1 : 0], s[0]);
+        if (ND >= 3) select_words_pair(c[0], c[ND >= 3 ? 1 : 0], s[0]);
         else select_words_one(c[0], s[0]);
     }
     __device__ __forceinline__ void back_words(const uint32_t (&c)[ND])
@@ -733,7 +730,6 @@ struct Contraction {
     }
     __device__ __forceinline__ void back(const v8i (&B)[5 * ND], v16i &acc)
     {
-        if (ND == 2) five<(ND == 2 ? 1 : 0)>(s[0], B, acc);
         if (ND >= 3) five<(ND >= 3 ? 2 : 0)>(s[1], B, acc);
         if (ND == 4) five<(ND == 4 ? 3 : 0)>(s[1], B, acc);
     }
@@ -1789,12 +1785,12 @@ int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL(lm_fill_lds_kernel, dim3(lgrid + LM_UNIT_WGS), dim3(256), lds, s, v, a.probe_ids, a.nq,
                            a.nprobe, a.p_first, a.lcount, a.loff, a.lcursor, a.qlist, qb, a.toff,
-                           a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each, (uint32_t)a.split_max);
+                           a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each, (uint32_t)a.split_max);
     } else {
         hipLaunchKernelGGL(lm_prefix_kernel, dim3(1), dim3(1024), 0, s, v, a.lcount, a.loff, a.lcursor,
-                           a.toff, a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each, (uint32_t)a.split_max);
+                           a.toff, a.unit_parts, a.unit_tail_from, a.unit_rec, a.log_cursor, starters, waves_each, (uint32_t)a.split_max);
         hipLaunchKernelGGL(lm_units_kernel, dim3((unsigned)((v.nlist + 255) / 256)), dim3(256), 0, s, v, a.lcount,
-                           a.loff, a.toff, a.unit_list, a.unit_parts, a.unit_tail_from, a.unit_rec);
+                           a.loff, a.toff, a.unit_parts, a.unit_tail_from, a.unit_rec);
         hipLaunchKernelGGL(lm_fill_kernel, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, s,
                            a.probe_ids, a.nq, a.nprobe, a.p_first, v.nlist, a.loff, a.lcursor, a.qlist);
     }
