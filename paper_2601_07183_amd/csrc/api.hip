@@ -615,8 +615,8 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     w.work = take((size_t)2 * (1 + nq) * 4);
     w.surv_cap = surv_cap_for(refine_k);
     {
-        // Chunks of RAIRS_LOG_CHUNK entries: log_per_query_for for every query, and what the waves hold that get
-        // a unit or a slice of one, a chunk each and some for the next.
+        // Chunks of RAIRS_LOG_CHUNK entries: log_per_query_for for every query, and those that waves hold half filled, one for each
+        // with a unit or a slice of one, and as many again.
         const int64_t units = (nq * nprobe < nq * nprobe / 32 + v.nlist ? nq * nprobe : nq * nprobe / 32 + v.nlist) *
                               (int64_t)(max_parts > 0 ? max_parts : 1);
         const int64_t active = rairs_scan_log_waves(v, units);
@@ -652,14 +652,17 @@ static WsLayout ws_layout(const IndexView &v, int64_t nq, int64_t nq_total, int 
     const size_t samp_bytes = align_up(grouped ? (size_t)nq * w.sample_blocks * 64 : 0, 256);
     const size_t hmin_bytes = v.nlist <= RAIRS_HMIN_MAX_NLIST ? (size_t)nq * rairs_half_tiles(v.nlist) * 4 : 0;
     const size_t surv_bytes = (size_t)nq * w.surv_cap * 8;
-    w.s_scores = w.surv_buf = take(samp_bytes + hmin_bytes > surv_bytes ? samp_bytes + hmin_bytes : surv_bytes);
-    w.hmin = hmin_bytes ? w.s_scores + samp_bytes : 0;
     // The scan's tables (5,136 bytes a query at most, 1,296 for M <= 64) live from the selection of the probe lists
     // to the end of the scan, the survivor buffers from there on.  With the sample on the matrix cores (M <= 64) its
     // scores and the minima may still be in use when the tables are made (on the other stream), else the minima are
-    // not.  That sample takes at most max(3,072, 10 bigK) bytes a query and the minima 2,048 then: all three
-    // together stay below the survivors' max(8,192, 64 bigK).
-    w.tables = w.s_scores + (grouped ? samp_bytes + align_up(hmin_bytes, 256) : 0);
+    // not.  That sample takes at most 3,072 bytes a query up to bigK = 128 and 8,192 beyond, and the minima 2,048; the survivors
+    // take 8,192 and 16,384 to 32,768: the tables fit behind both.  (If they did not, the buffer would grow here.)
+    const size_t tables_at = grouped ? samp_bytes + align_up(hmin_bytes, 256) : 0;
+    size_t shared_bytes = samp_bytes + hmin_bytes > surv_bytes ? samp_bytes + hmin_bytes : surv_bytes;
+    if (rairs_mfma_supported(v)) shared_bytes = std::max(shared_bytes, tables_at + rairs_scan_tables_bytes(v, nq));
+    w.s_scores = w.surv_buf = take(shared_bytes);
+    w.hmin = hmin_bytes ? w.s_scores + samp_bytes : 0;
+    w.tables = w.s_scores + tables_at;
     w.total = off;
     return w;
 }

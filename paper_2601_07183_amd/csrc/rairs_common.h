@@ -249,8 +249,9 @@ struct MfmaScanArgs {
     int32_t *cand_score;          // may be null
 };
 bool rairs_mfma_supported(const IndexView &v);
-bool rairs_mfma_reg_tables(const IndexView &v);    // the tile's tables fit the registers (sparse instruction)
-int64_t rairs_scan_log_waves(const IndexView &v, int64_t units);    // half of the chunks that waves may hold, for a pass of at most `units` units
+bool rairs_mfma_reg_tables(const IndexView &v);    // the scan keeps a tile's tables in registers (else in LDS)
+size_t rairs_scan_tables_bytes(const IndexView &v, int64_t nq);    // of the scan's form of the tables
+int64_t rairs_scan_log_waves(const IndexView &v, int64_t units);    // half of the log's chunks beyond the entries' own, for a pass of at most `units` units
 // grouping of the (query, probed list) pairs by list, the unit table and the scan's form of the tables, then the scan itself
 int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s);
 int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_t s, hipEvent_t *ev);

@@ -600,8 +600,8 @@ static __device__ __forceinline__ void select_words_one(uint32_t a, uint32_t (&w
 
 // The table operand straight from the bytes T (the sample's kernel): lane (query, half) holds, for dword w,
 // sub-quantizers 16 w + 8 half .. + 7, even ones in the first four registers, four table entries (signed:
-// value - 128) to a register.  Sub-quantizers from M on are zero.  Returns what a contraction is above the
-// score (the same number in both lanes of a query).
+// value - 128) to a register.  M must be 16 ND: all of 16 ND rows are read and picked from.  Returns what a
+// contraction is above the score (the same number in both lanes of a query).
 template <int ND>
 static __device__ __forceinline__ int load_byte_tables(const uint8_t *lut, uint32_t qid, int M, int half, v8i (&B)[5 * ND])
 {
@@ -1675,7 +1675,7 @@ __global__ __launch_bounds__(WG) void sample_mfma_kernel(IndexView v, const uint
 
 bool rairs_sample_scores_supported(const IndexView &v, int64_t nq)
 {
-    return (v.M == 16 || v.M == 48 || v.M == 64) && v.nlist <= SAMPLE_GROUP_MAX_NLIST &&
+    return v.M == 16 * v.nd && (v.nd == 1 || v.nd == 3 || v.nd == 4) && v.nlist <= SAMPLE_GROUP_MAX_NLIST &&
            nq >= SAMPLE_GROUP_MIN_QUERIES;
 }
 
@@ -1723,10 +1723,13 @@ int rairs_launch_sample_scores(const IndexView &v, const uint8_t *lut, int sampl
 
 bool rairs_mfma_supported(const IndexView &v) { return v.T >= 1 && v.nd <= 16; }
 
-// Up to 64 sub-quantizers the tables fit into registers.  At two dwords of codes (and below 16 sub-quantizers) the
-// eight waves that share a tile in LDS are faster all the same where a few units hold most survivors, which a wave
-// alone works off one after the other: 26,578 x 48, M = 24, 1,370 queries, 69 probes 326 us in registers, 192 in LDS;
-// 28,000 x 64, M = 32, 1,000 queries, 16 probes 97 and 62; 10,000 queries 228 and 248.
+// Up to 64 sub-quantizers the tables fit into registers.  Which kernel is faster then is more a matter of load than of M: a
+// wave with a tile of its own contracts faster, eight waves that share one work a crowded unit's survivors off sooner and are
+// at fewer units at once, so bounds come earlier.  At two dwords of codes the second weighs more, from three on the first; at
+// sixteen sub-quantizers it is about even, and the smaller bigK counts.  (us in registers / in LDS.  10,000 queries, 32 probes, bigK =
+// 10: M = 16 771 / 910, 32 428 / 565, 48 409 / 556, 64 489 / 670; 10,000, 16, 100: M = 16 990 / 1,030, 24 1,253 / 1,103 and 1,193 / 1,265, 32
+// 488 / 600, 48 463 / 532; 3,000, 16, 40: M = 16 418 / 406 and 346 / 270, 24 597 / 472 and 453 / 512, 32 265 / 241, 48 246 / 229, 64 281 / 256;
+// 300, 16, 100: M = 16 277 / 330, 24 430 / 421 and 324 / 405, 48 190 / 200; 2,000, 8, 40: M = 8 227 / 188, 16 311 / 289, 24 399 / 331, 32 199 / 191.)
 bool rairs_mfma_reg_tables(const IndexView &v) { return v.nd <= 4 && (v.nd >= 3 || v.M == 16); }
 
 // persistent grids: 256 compute units x 2 workgroups of 4 waves with the tables in registers; one
@@ -1737,12 +1740,12 @@ static void scan_launch_shape(const IndexView &v, bool *reg_tables, unsigned *gr
     *grid = *reg_tables ? 512u : 256u;
 }
 
-// Most waves that can own chunks of the survivor log at once when the pass has at most `units` units.
+// Half of the chunks of the survivor log beyond those for the entries themselves, when the pass has at most `units` units.
 int64_t rairs_scan_log_waves(const IndexView &v, int64_t units)
 {
-    // 2,048 with the tables in registers, eight for each of 256 workgroups with the tables in LDS.  (Programs size
-    // workspaces by this, and the few-query search has to fit into them: but for three shapes the figure stays that
-    // of sixteen waves a workgroup.)
+    // At most 2,048 waves hold a chunk, whichever kernel.  That many and once more are for those with three shapes, and twice that
+    // for the others (sixteen waves a workgroup once): what waves leave is where survivors beyond their buffers go, and
+    // programs size workspaces by it, which the few-query search has to fit as well.
     if (v.M == 16 || v.M == 48 || v.M == 64) return units < 2048 ? units : 2048;
     return (units < 256 ? units : 256) * 16;
 }
@@ -1797,6 +1800,8 @@ int rairs_launch_group(const IndexView &v, const MfmaScanArgs &a, hipStream_t s)
     RAIRS_HIP(hipGetLastError());
     return RAIRS_OK;
 }
+
+size_t rairs_scan_tables_bytes(const IndexView &v, int64_t nq) { return (size_t)nq * scan_tables_stride(v.nd); }
 
 int rairs_launch_scan_mfma(const IndexView &v, const MfmaScanArgs &a, hipStream_t s, hipEvent_t *ev)
 {
