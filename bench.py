@@ -554,7 +554,7 @@ def main():
     # What bounds the dominant kernel.  One table lookup is 16 int8 multiply-adds of the one-hot
     # contraction = 32 ops, so the ops the kernel stands for are items x M x 32 (partly filled
     # query tiles and list tails count as lost).  Both matrix kernels issue the 2:4-sparse int8
-    # instruction and are priced against its peak.  The exact kernel and that of small batches do their lookups on the vector units.
+    # instruction and are priced against its peak (of which a code's five picks leave 4/5 at most).  The exact kernel and that of small batches do their lookups on the vector units.
     kernel = ix.scan_kernel_name()
     kms = stage["scan_kernel"]
     lookups = float(dco.sum()) * w.M

@@ -634,8 +634,8 @@ static __device__ __forceinline__ int load_byte_tables(const uint8_t *lut, uint3
 // The scan's own form of the tables, made once per query.  A group's entries may be shifted by a number of
 // its own, so the entry that the groups not meant pick is made zero wherever the other three fit into a
 // signed byte then: four of five picks are zeros.  What a matrix instruction costs is power: with random
-// table bytes picked everywhere the chip holds 1.5 GHz (21.5 ns each, every SIMD at it), with four of five
-// picks zero 2.05 GHz (16.0 ns; the one-hot expansion 1.6 GHz, 20.6 ns).
+// table bytes picked everywhere the chip holds 1.66 GHz (19.7 ns each, every SIMD at it), with four of five
+// picks zero 2.03 GHz (16.1 ns; the one-hot expansion 1.72 GHz, 19.0 ns).
 // Per query scan_tables_stride bytes: for dword w and half the five registers of eight words each that
 // load_byte_tables describes, then what a contraction is above the score.
 static __host__ __device__ __forceinline__ int scan_tables_stride(int nd) { return nd * 320 + 16; }

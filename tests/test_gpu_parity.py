@@ -279,9 +279,9 @@ def test_both_repairs_in_one_launch(binding):
         ix.free()
 
 
-def test_survivor_log_runs_out_of_chunks(binding):
-    # 120,000 identical vectors: every scanned item passes any bound, the survivor log of a small
-    # batch runs out of chunks, every query is flagged and the exact kernel redoes them all
+def test_every_query_redone(binding):
+    # 120,000 identical vectors: every scanned item passes any bound, every query has more survivors than
+    # the selects take, is flagged and redone by the exact kernel (a log that runs out: test_gpu_spill.py)
     count = 120_000
     x = np.tile(datagen.random_vectors(54, 1, 8), (count, 1))
     q = datagen.random_vectors(55, 30, 8)
@@ -295,7 +295,7 @@ def test_survivor_log_runs_out_of_chunks(binding):
     try:
         ix.search(_dev(q), 10, 4, 64)
         torch.cuda.synchronize()
-        assert ix.scan_stats()["redone"] == len(q)       # the log did run out
+        assert ix.scan_stats()["redone"] == len(q)
     finally:
         ix.free()
 
