@@ -25,7 +25,7 @@
 // queue, so once bins 0..b hold >= bigK of them, no item scoring above the top edge of bin b can be
 // among the bigK best: that edge is a valid, tighter bound.  Lanes that file survivors re-derive
 // the query's bound now and then and lower it with an atomic minimum; scanning waves re-read it
-// for every block.  A stale view is only looser.
+// every few blocks, and once the scan has ended final_bound_kernel derives it from all counts.  A stale view is only looser.
 #include <limits.h>
 
 #include <type_traits>
